@@ -93,8 +93,7 @@ enum {
                                  * Two-step and fused single-step launches take only
                                  * the other tiles (the two-kernel step of
                                  * TETE_KERNEL_SPLIT and batches take all); with tuning
-                                 * x-chunk 0 the two-step launches use chunks of 32
-                                 * planes.
+                                 * x-chunk 0 these launches use chunks of 32 planes.
                                  * The tile list is built, and the stream synchronised,
                                  * at the first such launch after the codes or the
                                  * tiling (rows, x-chunk, order; witness set or not)
@@ -446,13 +445,13 @@ tete_status tete_charges(tete_grid* g, double* max_res_e, double* max_abs_h);
  * FP32, 12 for FP64); of the two-step kernel, 16 (16 rows of 64 lanes for
  * FP32, of 32 lanes for FP64, the default) or 32 (FP32: 32 rows of 32
  * lanes); 32 leaves the single step at its default.  xchunk: x-planes
- * per workgroup of either fused kernel (0: chosen from the grid size).
+ * per workgroup of either fused kernel (0: chosen from the grid size so that the
+ * workgroups fill whole rounds of 256, one per CU).
  * depth: x-planes of old data the fused single step prefetches ahead, 1..3
  * (0: 2; the two-step kernel prefetches one).  order: order in which the
  * fused kernels' tiles are scheduled: 1 (j-tiles first), 2 (k-tiles first),
  * 3, 4, 5 or 6 (blocks of 8 k-tiles by 4 j-tiles, 16 by 2, 4 by 8 or 2 by
- * 16); 0: 4 where the grid has at least 16 k-tiles and 2 j-tiles and the
- * launch at least 2048 workgroups, else 2 (batches: 2).  tete_set_materials
+ * 16); 0: 2.  tete_set_materials
  * turns a forced FUSED or FUSED2 back into AUTO.  tete_get_tuning reports the kernel
  * that tete_step will use (FUSED2, FUSED or SPLIT). */
 enum { TETE_KERNEL_AUTO = 0, TETE_KERNEL_FUSED = 1, TETE_KERNEL_SPLIT = 2, TETE_KERNEL_FUSED2 = 3,

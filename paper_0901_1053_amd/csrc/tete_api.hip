@@ -292,10 +292,10 @@ int fused2_rows(const tete_grid* g)
     return r == 16 || ((r == 24 || r == 32) && g->fp32) ? r : 0;
 }
 
-// X-chunk of the two-step kernel: the tuning's, else for grids that skip
+// X-chunk of the fused kernels: the tuning's, else for grids that skip
 // static tiles chunks of 32 planes (short chunks find more tiles wholly in
 // the metal, at seven halo planes per chunk), else the library's choice (0).
-int fused2_xchunk(const tete_grid* g)
+int fused_xchunk(const tete_grid* g)
 {
     return g->tune.xchunk != 0 ? g->tune.xchunk : g->skip ? 32 : 0;
 }
@@ -328,10 +328,10 @@ tete_status static_table(tete_grid* g, bool wit, bool single)
     int rows, xc, order = g->tune.order;
     if (single) {   // the fused single step's tiling; kappa marks the PEC edges of materials
         rows = g->mat_set || g->tune.rows == 24 || g->tune.rows == 32 ? 0 : g->tune.rows;
-        xc = g->tune.xchunk;
+        xc = fused_xchunk(g);
     } else {        // the instance that keeps witness lines has the default rows only
         rows = wit ? 0 : fused2_rows(g);
-        xc = fused2_xchunk(g);
+        xc = fused_xchunk(g);
     }
     if (g->skip_rows[kind] == rows && g->skip_xc[kind] == xc && g->skip_order[kind] == order) return TETE_OK;
     if (single) {
@@ -367,7 +367,7 @@ tete_status do_steps(tete_grid* g, int64_t nsteps)
     // launches of at most EN_PARTS workgroups
     int64_t en_blocks = 0;
     const bool en_fuse = two && g->diag_every > 0 && (!g->mat_set || g->mat_cls) && !g->skip &&
-                         (en_blocks = fused2_blocks<R>(g->geo, fused2_xchunk(g), g->tune.order)) > 0 &&
+                         (en_blocks = fused2_blocks<R>(g->geo, fused_xchunk(g), g->tune.order)) > 0 &&
                          en_blocks <= EN_PARTS;
     for (int64_t s = 0; s < nsteps; ++s) {
         const bool at_n = g->diag_every > 0 && g->n % g->diag_every == 0;
@@ -416,7 +416,7 @@ tete_status do_steps(tete_grid* g, int64_t nsteps)
                              g->mat_cls ? g->craw : nullptr};
             HIPCHK(launch_step_fused2<R>(fields<R>(g, g->cur), fields<R>(g, 1 - g->cur), M, g->geo, (R)g->alpha,
                                          source(g, g->n), wit ? &wm : nullptr, fused2_rows(g), g->tune.depth,
-                                         fused2_xchunk(g), g->tune.order, g->stream, ev, act, g->skip_nact[0],
+                                         fused_xchunk(g), g->tune.order, g->stream, ev, act, g->skip_nact[0],
                                          en_pair ? &en : nullptr));
             if (en_pair) g->ecount += (at_n ? 1 : 0) + (at_n1 ? 1 : 0);
             g->skip_live = 1;
@@ -453,8 +453,7 @@ tete_status do_steps(tete_grid* g, int64_t nsteps)
             }
             HIPCHK(launch_step_fused<R>(fields<R>(g, g->cur), fields<R>(g, 1 - g->cur), M, g->geo, (R)g->alpha,
                                         source(g, g->n), g->tune.rows == 24 || g->tune.rows == 32 ? 0 : g->tune.rows,
-                                        g->tune.xchunk,
-                                        g->tune.depth, g->tune.order, g->stream, ev, act, g->skip_nact[1]));
+                                        fused_xchunk(g), g->tune.depth, g->tune.order, g->stream, ev, act, g->skip_nact[1]));
         }
         else
             HIPCHK(launch_step<R>(fields<R>(g, g->cur), fields<R>(g, 1 - g->cur), M, g->geo, (R)g->alpha,
@@ -1336,7 +1335,8 @@ bool batch_two_args(tete_grid* g, BatchItem<R>& it, int phase, int& total2)
     FArgs<R> b2 = fused_args<R>(fields<R>(g, 1 - g->cur), fields<R>(g, g->cur), mats<R>(g), g->geo, (R)g->alpha,
                                 source(g, g->n));
     const int xc = g->tune.kernel == TETE_KERNEL_FUSED2 ? g->tune.xchunk : 0;
-    if (!fused2_setup<R>(f2, 0, xc, batch_order(g)) || !fused2_setup<R>(b2, 0, xc, batch_order(g))) return false;
+    if (!fused2_setup<R>(f2, 0, xc, batch_order(g), 0, true) || !fused2_setup<R>(b2, 0, xc, batch_order(g), 0, true))
+        return false;
     it.a2[phase] = f2;
     it.a2[1 - phase] = b2;
     total2 += f2.nblk;
@@ -1367,8 +1367,8 @@ tete_status batch_build(tete_batch* b)
         Src src = source(g, g->n);
         FArgs<R> fwd = fused_args<R>(fields<R>(g, g->cur), fields<R>(g, 1 - g->cur), M, g->geo, (R)g->alpha, src);
         FArgs<R> bwd = fused_args<R>(fields<R>(g, 1 - g->cur), fields<R>(g, g->cur), M, g->geo, (R)g->alpha, src);
-        if (!fused_setup<R>(fwd, b->rows, g->tune.xchunk, batch_order(g)) ||
-            !fused_setup<R>(bwd, b->rows, g->tune.xchunk, batch_order(g)))
+        if (!fused_setup<R>(fwd, b->rows, g->tune.xchunk, batch_order(g), true) ||
+            !fused_setup<R>(bwd, b->rows, g->tune.xchunk, batch_order(g), true))
             return TETE_ERR_ARG;
         // at the current phase the grid reads its current set
         H->item[i].a[b->phase] = fwd;

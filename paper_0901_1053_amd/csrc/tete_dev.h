@@ -5,6 +5,8 @@
 
 #include <stdint.h>
 
+#include <algorithm>
+
 #include <hip/hip_runtime.h>
 
 #include "tete_impl.h"
@@ -75,14 +77,28 @@ __device__ __forceinline__ int xcd_remap(int b, int n)
     return x < extra ? x * (base + 1) + r : extra * (base + 1) + (x - extra) * base + r;
 }
 
+// The same for a launch whose workgroups fill a CU each: kRound of them run at
+// a time, and the remap is taken within each round.  The running workgroups
+// then cover one contiguous range of tiles (whole rows of neighbouring bands),
+// an eighth of it per XCD.  With the range split over the whole launch the
+// eight XCDs worked in eight distant bands: 4.14 against 3.90 ms per step on
+// the 512 x 512 x 2048 grid in FP32 (k-tiles first), 7.44 against 7.00 ms in FP64.
+constexpr int kRound = 256;   // workgroups running at a time: one per CU
+__device__ __forceinline__ int xcd_rounds(int b, int n)
+{
+    const int r0 = b / kRound * kRound;
+    return r0 + xcd_remap(b - r0, min(kRound, n - r0));
+}
+
 // Tile (ty, tz) and x-chunk cx of logical workgroup lb.  order 2: k-tiles
 // fastest, so the tiles of one band of rows, which together cover whole
 // contiguous rows, run together; order 1: j-tiles fastest; orders 3-6: blocks
 // of BZ k-tiles by BY j-tiles (8 x 4, 16 x 2, 4 x 8, 2 x 16: 32 workgroups, one
 // XCD's worth) fastest, so that neighbouring row bands, which share halo rows,
-// also run together and share the XCD's L2.  Order 0 is resolved on the host
-// before launch.  Returns false for the padding workgroups of the blocked
-// orders.
+// also run together and share the XCD's L2.  Order 0 is order 2: with the
+// rounds above it is the fastest (the blocks read up to 13 % fewer bytes but
+// took 1 to 5 % longer, padded or not).  Returns false for the padding
+// workgroups of the blocked orders.
 __host__ __device__ __forceinline__ bool blocked_order(int order) { return order >= 3 && order <= 6; }
 __host__ __device__ __forceinline__ int block_z(int order)
 {
@@ -96,15 +112,6 @@ __host__ __device__ __forceinline__ int launch_tiles(int order, int nyt, int nzt
     if (!blocked_order(order)) return nyt * nzt * nxc;
     const int BZ = block_z(order), BY = block_y(order);
     return ((nzt + BZ - 1) / BZ) * ((nyt + BY - 1) / BY) * BZ * BY * nxc;
-}
-// Default tile order: 16 x 2 blocks (order 4) where a block row is filled
-// and the launch spans at least eight rounds of 256 workgroups, so that the
-// padding of partial blocks averages out over the rounds; otherwise k-tiles
-// first (order 2).
-inline int default_order(int nyt, int nzt, int nxc)
-{
-    const bool fill = nzt >= block_z(4) && nyt >= block_y(4);
-    return fill && (int64_t)nyt * nzt * nxc >= 8 * 256 ? 4 : 2;
 }
 __host__ __device__ __forceinline__ bool tile_of(int lb, int order, int nyt, int nzt, int& ty, int& tz, int& cx)
 {
@@ -127,6 +134,127 @@ __host__ __device__ __forceinline__ bool tile_of(int lb, int order, int nyt, int
     tz = (lb / nyt) % nzt;
     cx = lb / (nyt * nzt);
     return true;
+}
+
+// A work item: tile (ty, tz), planes xs .. xe-1.
+struct Tile {
+    int ty, tz, xs, xe;
+};
+
+// Work item lb of a launch of A.nblk; false for an item without planes (the
+// padding of the blocked orders, a tail item past the end of a short chunk).
+template <typename R>
+__device__ __forceinline__ bool tile_at(const FArgs<R>& A, int lb, Tile& t)
+{
+    int sub = -1;
+    if (lb >= A.nfull) {
+        const int ntail = (A.nblk - A.nfull) / A.tsplit, q = lb - A.nfull;
+        sub = q / ntail;
+        lb = A.nfull + q % ntail;
+    }
+    int cx;
+    if (!tile_of(lb, A.order, A.nyt, A.nzt, t.ty, t.tz, cx)) return false;
+    t.xs = cx * A.xchunk;
+    t.xe = min(t.xs + A.xchunk, A.g.nx + 1);
+    if (sub >= 0) {
+        t.xs += sub * A.tchunk;
+        t.xe = min(t.xs + A.tchunk, t.xe);
+    }
+    return t.xs < t.xe;
+}
+
+// Work item of an entry of a list of active tiles, (cx nyt + ty) nzt + tz.
+template <typename R>
+__device__ __forceinline__ Tile listed_tile(const FArgs<R>& A, int e)
+{
+    Tile t;
+    t.tz = e % A.nzt;
+    t.ty = (e / A.nzt) % A.nyt;
+    t.xs = e / (A.nzt * A.nyt) * A.xchunk;
+    t.xe = min(t.xs + A.xchunk, A.g.nx + 1);
+    return t;
+}
+
+// X-chunks of a launch whose workgroups fill a CU each.  A workgroup's time is
+// the planes of its chunk and `fill` more (the pipeline's lead-in and drain),
+// in steps of `unroll` planes.  The launch takes as many rounds of kRound
+// workgroups; the items of a last, partly filled round are cut along x so that
+// they fill it (the tail).  Chosen is the count of chunks with the smallest
+// time; a quarter of the work over all CUs is added, which decides between
+// equal times for the fewer chunks.  Measured with chunks as few as fill half
+// the CUs against this rule, us per step (two-step kernel): 24 x 24 x 48
+// FP64 24.9, 10.6; 64 x 64 x 256 FP32 20.4, 16.4; 192 x 192 x 1024 FP32 371, 295;
+// 192 x 192 x 768 FP32 by class 363, 249; 97 x 131 x 801 FP64 179, 163; with the
+// rounds above 512 x 512 x 2048 FP32 4144, 3723.
+struct ChunkPlan {
+    int xchunk, nxc, nfull, nblk, tsplit, tchunk;
+};
+inline ChunkPlan plan_chunks(int64_t tiles, int nplanes, int64_t xmax, int fill, int unroll, bool tail)
+{
+    auto planes = [&](int xc) { return (double)((xc + fill + unroll - 1) / unroll * unroll); };
+    ChunkPlan best = {};
+    double best_cost = 0.0;
+    for (int nxc = (int)((nplanes + xmax - 1) / xmax); nxc <= nplanes; ++nxc) {
+        const int xc = (nplanes + nxc - 1) / nxc;
+        if ((nplanes + xc - 1) / xc != nxc) continue;   // no such count of equal chunks
+        const int64_t items = tiles * nxc;
+        // beyond 32 rounds more chunks only add lead-in planes
+        if (best.nblk > 0 && items > 32 * (int64_t)kRound) break;
+        if (items > 0x3fffffff) break;
+        const int rem = (int)(items % kRound);
+        ChunkPlan p = {xc, nxc, (int)items, (int)items, 1, xc};
+        double rounds = (double)((items + kRound - 1) / kRound) * planes(xc);
+        if (tail && rem > 0 && items > kRound) {
+            const double base = (double)(items / kRound) * planes(xc);
+            for (int s = 2; s * rem <= kRound && s <= xc; ++s) {
+                const int tc = (xc + s - 1) / s;
+                if (base + planes(tc) < rounds) {
+                    rounds = base + planes(tc);
+                    p.nfull = (int)(items - rem);
+                    p.tsplit = (xc + tc - 1) / tc;
+                    p.tchunk = tc;
+                    p.nblk = p.nfull + rem * p.tsplit;
+                }
+            }
+        }
+        const double cost = rounds + 0.25 * (double)items * planes(xc) / kRound;
+        if (best.nblk == 0 || cost < best_cost) {
+            best = p;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+// Fills the tiling of A: the x-chunk asked for (clipped to xmax planes), or
+// where xchunk is 0 the plan above.  A member of a batch shares the rounds with
+// other members' items: as few chunks as possible, but at least 128 items,
+// chunks of at least 16 planes, and each within xmax.
+template <typename R>
+inline void set_chunks(FArgs<R>& A, int xchunk, int order, int64_t xmax, int fill, int unroll, bool member)
+{
+    A.order = order != 0 ? order : 2;
+    const int nplanes = A.g.nx + 1, tiles = launch_tiles(A.order, A.nyt, A.nzt, 1);
+    if (xchunk <= 0 && member) {
+        int chunks = std::min((128 + tiles - 1) / tiles, std::max(1, nplanes / 16));
+        chunks = (int)std::max<int64_t>(chunks, (nplanes + xmax - 1) / xmax);
+        xchunk = (nplanes + chunks - 1) / chunks;
+    }
+    if (xchunk <= 0) {
+        const ChunkPlan p = plan_chunks(tiles, nplanes, xmax, fill, unroll, !blocked_order(A.order));
+        A.xchunk = p.xchunk;
+        A.nxc = p.nxc;
+        A.nfull = p.nfull;
+        A.nblk = p.nblk;
+        A.tsplit = p.tsplit;
+        A.tchunk = p.tchunk;
+        return;
+    }
+    A.xchunk = (int)std::min<int64_t>(xchunk, xmax);
+    A.nxc = (nplanes + A.xchunk - 1) / A.xchunk;
+    A.nblk = A.nfull = launch_tiles(A.order, A.nyt, A.nzt, A.nxc);
+    A.tsplit = 1;
+    A.tchunk = A.xchunk;
 }
 
 }  // namespace

@@ -50,15 +50,14 @@ struct MatA {
     const R* m[6];
 };
 
-// One tile (ty, tz) and x-chunk cx of one step of the grid described by A.
+// One work item (tile and x-chunk) of one step of the grid described by A.
 // Every thread of the workgroup must call it (it contains barriers).  MAT:
 // the coefficients come from the per-entry arrays of MA, loaded with the
 // fields of each plane and carried to the lags where the sub-updates use them
 // (kappa_z to p-1, mu_x to p-2, mu_y to p-2, kappa_y to p-3, mu_z to p-3,
 // kappa_x to p-4), instead of the vacuum scalars and the PEC codes.
 template <typename R, int TYH, int PD, bool MAT = false>
-__device__ __forceinline__ void fused_tile(const FArgs<R>& A, const int ty, const int tz, const int cx,
-                                           Lds<R, TYH>& L, const MatA<R>& MA = MatA<R>{})
+__device__ __forceinline__ void fused_tile(const FArgs<R>& A, const Tile& t, Lds<R, TYH>& L, const MatA<R>& MA = MatA<R>{})
 {
     constexpr int TY = TYH - 4;
     auto& sEZ = L.sEZ;
@@ -71,8 +70,8 @@ __device__ __forceinline__ void fused_tile(const FArgs<R>& A, const int ty, cons
 
     const int kl = threadIdx.x & 63;
     const int jl = threadIdx.x >> 6;
-    const int j = ty * TY - 2 + jl;
-    const int k = tz * KT - 1 + kl;
+    const int j = t.ty * TY - 2 + jl;
+    const int k = t.tz * KT - 1 + kl;
     const bool jin = (unsigned)j <= (unsigned)g.ny;
     const bool kin = (unsigned)k <= (unsigned)g.nz;
     const bool node = jin && kin;
@@ -84,8 +83,7 @@ __device__ __forceinline__ void fused_tile(const FArgs<R>& A, const int ty, cons
     const bool hy_k = node && k < g.nz;
     const bool hz_j = node && j < g.ny;
 
-    const int xs = cx * A.xchunk;
-    const int xe = min(xs + A.xchunk, g.nx + 1);
+    const int xs = t.xs, xe = t.xe;
     const int xload_end = min(xe + 1, g.nx);    // last plane whose old data is needed
 
     const R a = A.a, a2 = A.a + A.a;
@@ -319,16 +317,10 @@ template <typename R, int TYH, int PD>
 __global__ __launch_bounds__(64 * TYH) void k_fused(FArgs<R> A, const int* act)
 {
     __shared__ Lds<R, TYH> L;
-    int ty, tz, cx;
-    if (act) {   // the active tiles only, as in the materials instance below
-        const int t = act[xcd_remap(blockIdx.x, gridDim.x)];
-        tz = t % A.nzt;
-        ty = (t / A.nzt) % A.nyt;
-        cx = t / (A.nzt * A.nyt);
-    } else if (!tile_of(xcd_remap(blockIdx.x, A.nblk), A.order, A.nyt, A.nzt, ty, tz, cx)) {
-        return;   // whole group
-    }
-    fused_tile<R, TYH, PD>(A, ty, tz, cx, L);
+    Tile t;
+    if (act) t = listed_tile(A, act[xcd_rounds(blockIdx.x, gridDim.x)]);   // the active tiles only
+    else if (!tile_at(A, xcd_rounds(blockIdx.x, A.nblk), t)) return;       // whole group
+    fused_tile<R, TYH, PD>(A, t, L);
 }
 
 // The same step with per-entry materials.  act (or null): the tiles that are
@@ -338,16 +330,10 @@ template <typename R, int TYH, int PD>
 __global__ __launch_bounds__(64 * TYH) void k_fused_mat(FArgs<R> A, MatA<R> MA, const int* act)
 {
     __shared__ Lds<R, TYH> L;
-    int ty, tz, cx;
-    if (act) {
-        const int t = act[xcd_remap(blockIdx.x, gridDim.x)];
-        tz = t % A.nzt;
-        ty = (t / A.nzt) % A.nyt;
-        cx = t / (A.nzt * A.nyt);
-    } else if (!tile_of(xcd_remap(blockIdx.x, A.nblk), A.order, A.nyt, A.nzt, ty, tz, cx)) {
-        return;   // whole group
-    }
-    fused_tile<R, TYH, PD, true>(A, ty, tz, cx, L, MA);
+    Tile t;
+    if (act) t = listed_tile(A, act[xcd_rounds(blockIdx.x, gridDim.x)]);
+    else if (!tile_at(A, xcd_rounds(blockIdx.x, A.nblk), t)) return;   // whole group
+    fused_tile<R, TYH, PD, true>(A, t, L, MA);
 }
 
 // A tile of the materials step is static when every entry it loads (rows
@@ -426,8 +412,8 @@ __global__ __launch_bounds__(64 * TYH) void k_fused_batch(const BatchTable<R>* T
             for (int i = 0; i < (int)(sizeof(FArgs<R>) / 4); ++i) dst[i] = src[i];
         }
         A.src.n = T->step[inst] + steps;
-        int ty, tz, cx;
-        if (tile_of(w - T->offset[inst], A.order, A.nyt, A.nzt, ty, tz, cx)) fused_tile<R, TYH, PD>(A, ty, tz, cx, L);
+        Tile t;
+        if (tile_at(A, w - T->offset[inst], t)) fused_tile<R, TYH, PD>(A, t, L);
         __syncthreads();   // the LDS is reused by the next item
     }
 }
@@ -455,31 +441,18 @@ hipError_t launch_fused_t(const FArgs<R>& A, const int* act, int nact, hipStream
 int fused_default_rows(int real_bytes) { return real_bytes == 8 ? 12 : 16; }   // FP64 at 16 rows spills
 
 template <typename R>
-bool fused_setup(FArgs<R>& A, int rows, int xchunk, int order)
+bool fused_setup(FArgs<R>& A, int rows, int xchunk, int order, bool member)
 {
     if (rows == 0) rows = fused_default_rows(sizeof(R));
     if (rows != 12 && rows != 16) return false;
     const int TY = rows - 4;
     A.nyt = (A.g.ny + 1 + TY - 1) / TY;
     A.nzt = (A.g.nz + 1 + KT - 1) / KT;
-    const int nplanes = A.g.nx + 1;
-    int xc = xchunk;
-    if (xc <= 0) {
-        // enough workgroups to fill the chip several times over
-        const int tiles = A.nyt * A.nzt;
-        int chunks = (4096 + tiles - 1) / tiles;
-        chunks = std::max(1, std::min(chunks, (nplanes + 31) / 32));
-        xc = (nplanes + chunks - 1) / chunks;
-    }
     // every buffer range must stay below 2^31 bytes: (xchunk + 4) planes
     const int64_t plane_bytes = (int64_t)A.g.sp * sizeof(R);
     const int64_t xmax = ((int64_t(1) << 31) - 1) / plane_bytes - 4;
     if (xmax < 1) return false;
-    xc = (int)std::min<int64_t>(std::max(xc, 1), xmax);
-    A.xchunk = xc;
-    A.nxc = (nplanes + xc - 1) / xc;
-    A.order = order != 0 ? order : default_order(A.nyt, A.nzt, A.nxc);
-    A.nblk = launch_tiles(A.order, A.nyt, A.nzt, A.nxc);
+    set_chunks(A, xchunk, order, xmax, 6, 3, member);   // planes xs-2 .. xe+3
     return true;
 }
 
@@ -497,7 +470,7 @@ FArgs<R> fused_args(Fields<R> o, Fields<R> nf, Mat<R> M, Geo g, R alpha, Src src
     A.kx = M.k[0]; A.ky = M.k[1]; A.kz = M.k[2];
     A.mx = M.m[0]; A.my = M.m[1]; A.mz = M.m[2];
     A.src = src;
-    A.nyt = A.nzt = A.nxc = A.xchunk = A.nblk = A.order = 0;
+    A.nyt = A.nzt = A.nxc = A.xchunk = A.nblk = A.order = A.nfull = A.tsplit = A.tchunk = 0;
     return A;
 }
 
@@ -557,7 +530,8 @@ hipError_t fused_static_tiles(const R* const kap[3], const uint8_t* code, Geo g,
     // the active tiles in the order the full launch takes them
     std::vector<int> list;
     list.reserve((size_t)nt);
-    for (int lb = 0; lb < A.nblk; ++lb) {
+    const int nlb = launch_tiles(A.order, A.nyt, A.nzt, A.nxc);
+    for (int lb = 0; lb < nlb; ++lb) {
         int ty, tz, cx;
         if (!tile_of(lb, A.order, A.nyt, A.nzt, ty, tz, cx)) continue;
         const int t = (cx * A.nyt + ty) * A.nzt + tz;
@@ -612,7 +586,7 @@ hipError_t launch_step_fused(Fields<R> o, Fields<R> nf, Mat<R> M, Geo g, R alpha
 }
 
 #define TETE_FUSED_INST(R)                                                                                     \
-    template bool fused_setup<R>(FArgs<R>&, int, int, int);                                                    \
+    template bool fused_setup<R>(FArgs<R>&, int, int, int, bool);                                                 \
     template FArgs<R> fused_args<R>(Fields<R>, Fields<R>, Mat<R>, Geo, R, Src);                                 \
     template hipError_t launch_batch_step<R>(BatchTable<R>*, int, int, int, int, int, hipStream_t);            \
     template hipError_t launch_batch_advance<R>(BatchTable<R>*, int, int, hipStream_t);

@@ -176,7 +176,7 @@ template <> struct Default2<float> { static constexpr int rows = 16, lw = 64, pd
 template <> struct Default2<double> { static constexpr int rows = 16, lw = 32, pd = 2; };
 inline int lanes2(int real_bytes, int rows) { return real_bytes == 8 || rows == 24 || rows == 32 ? 32 : 64; }
 
-// Two steps of one tile (ty, tz) and x-chunk cx.  Every thread of the
+// Two steps of one work item (tile and x-chunk).  Every thread of the
 // workgroup must call it (it contains barriers).
 // WIT: also keep stage A's e_z^{n+1/2} on the witness lines of wm (a
 // separate instance; the kernel without witness lines is unchanged).
@@ -224,7 +224,7 @@ struct EnOut {
 enum { ET_SKX, ET_SKY, ET_SKZ, ET_SMX, ET_SMY, ET_SMZ, ET_DKX, ET_DKY, ET_DMX, ET_DMY, ET_N };
 template <typename R, int TYH, int NB, int LW, int PD, bool WIT = false, bool CLS = false, bool ARR = false,
           class LDS, bool EN = false>
-__device__ __forceinline__ void fused2_tile(const FArgs<R>& A, const int ty, const int tz, const int cx, LDS& L,
+__device__ __forceinline__ void fused2_tile(const FArgs<R>& A, const Tile& t, LDS& L,
                                             const WitMid<R>& wm = WitMid<R>{}, const Arr6<R>& MA = Arr6<R>{},
                                             const EnOut& eo = EnOut{})
 {
@@ -238,8 +238,8 @@ __device__ __forceinline__ void fused2_tile(const FArgs<R>& A, const int ty, con
 
     const int kl = threadIdx.x % LW;
     const int jl = threadIdx.x / LW;
-    const int j = ty * TY - 3 + jl;
-    const int k = tz * KT2 - 2 + kl;
+    const int j = t.ty * TY - 3 + jl;
+    const int k = t.tz * KT2 - 2 + kl;
     const bool jin = (unsigned)j <= (unsigned)g.ny;
     const bool kin = (unsigned)k <= (unsigned)g.nz;
     const bool node = jin && kin;
@@ -252,8 +252,7 @@ __device__ __forceinline__ void fused2_tile(const FArgs<R>& A, const int ty, con
     const bool hy_k = node && k < g.nz;
     const bool hz_j = node && j < g.ny;
 
-    const int xs = cx * A.xchunk;
-    const int xe = min(xs + A.xchunk, g.nx + 1);
+    const int xs = t.xs, xe = t.xe;
     const int xload_end = min(xe + 3, g.nx);    // last plane whose old data is needed
 
     const R a2 = A.a + A.a;
@@ -263,7 +262,7 @@ __device__ __forceinline__ void fused2_tile(const FArgs<R>& A, const int ty, con
     const bool src_row = A.src.on && jrow == A.src.j0;
     // the source row lies in this wave (uniform over the wave: lane shifts
     // below run with every lane active)
-    const int wj0 = ty * TY - 3 + (int)(threadIdx.x / 64) * (64 / LW);
+    const int wj0 = t.ty * TY - 3 + (int)(threadIdx.x / 64) * (64 / LW);
     const bool src_wave = A.src.on && A.src.j0 >= wj0 && A.src.j0 < wj0 + 64 / LW;
     const bool src_k = kin && k < g.nz;                 // lane holds an e_z edge
 
@@ -682,16 +681,13 @@ __device__ __forceinline__ void fused2_tile(const FArgs<R>& A, const int ty, con
 // together in the metal, are not launched at all.  False for the padding
 // workgroups of a full launch.
 template <typename R>
-__device__ __forceinline__ bool fused2_tile_of(const FArgs<R>& A, const int* act, int& ty, int& tz, int& cx)
+__device__ __forceinline__ bool fused2_tile_of(const FArgs<R>& A, const int* act, Tile& t)
 {
     if (act) {
-        const int t = act[xcd_remap(blockIdx.x, gridDim.x)];
-        tz = t % A.nzt;
-        ty = (t / A.nzt) % A.nyt;
-        cx = t / (A.nzt * A.nyt);
+        t = listed_tile(A, act[xcd_rounds(blockIdx.x, gridDim.x)]);
         return true;
     }
-    return tile_of(xcd_remap(blockIdx.x, A.nblk), A.order, A.nyt, A.nzt, ty, tz, cx);
+    return tile_at(A, xcd_rounds(blockIdx.x, A.nblk), t);
 }
 
 template <typename R, int TYH, int LW, int PD>
@@ -699,9 +695,9 @@ __global__ __launch_bounds__(TYH * LW) void k_fused2(FArgs<R> A, const int* act)
 {
     typedef Shape2<R, TYH, LW> S;
     __shared__ Lds2<R, S::rows, S::nb, S::lw> L;
-    int ty, tz, cx;
-    if (!fused2_tile_of(A, act, ty, tz, cx)) return;   // whole group
-    fused2_tile<R, S::rows, S::nb, S::lw, PD>(A, ty, tz, cx, L);
+    Tile t;
+    if (!fused2_tile_of(A, act, t)) return;   // whole group
+    fused2_tile<R, S::rows, S::nb, S::lw, PD>(A, t, L);
 }
 
 // The two-step kernel that also sums the energy of its input and of the
@@ -714,12 +710,12 @@ __global__ __launch_bounds__(TYH * LW) void k_fused2_en(FArgs<R> A, EnOut eo)
     typedef Shape2<R, TYH, LW> S;
     typedef Lds2<R, S::rows, S::nb, S::lw> LT;
     __shared__ LT L;
-    int ty, tz, cx;
-    if (!fused2_tile_of(A, nullptr, ty, tz, cx)) {      // whole group
+    Tile t;
+    if (!fused2_tile_of(A, nullptr, t)) {      // whole group
         if (threadIdx.x == 0) eo.part[2 * blockIdx.x] = eo.part[2 * blockIdx.x + 1] = 0.0;
         return;
     }
-    fused2_tile<R, S::rows, S::nb, S::lw, PD, false, false, false, LT, true>(A, ty, tz, cx, L, WitMid<R>{},
+    fused2_tile<R, S::rows, S::nb, S::lw, PD, false, false, false, LT, true>(A, t, L, WitMid<R>{},
                                                                                Arr6<R>{}, eo);
 }
 
@@ -730,12 +726,12 @@ __global__ __launch_bounds__(TYH * LW) void k_fused2_en_wit(FArgs<R> A, EnOut eo
     typedef Shape2<R, TYH, LW> S;
     typedef Lds2<R, S::rows, S::nb, S::lw> LT;
     __shared__ LT L;
-    int ty, tz, cx;
-    if (!fused2_tile_of(A, nullptr, ty, tz, cx)) {      // whole group
+    Tile t;
+    if (!fused2_tile_of(A, nullptr, t)) {      // whole group
         if (threadIdx.x == 0) eo.part[2 * blockIdx.x] = eo.part[2 * blockIdx.x + 1] = 0.0;
         return;
     }
-    fused2_tile<R, S::rows, S::nb, S::lw, PD, true, false, false, LT, true>(A, ty, tz, cx, L, wm, Arr6<R>{}, eo);
+    fused2_tile<R, S::rows, S::nb, S::lw, PD, true, false, false, LT, true>(A, t, L, wm, Arr6<R>{}, eo);
 }
 
 // The same with materials by class: the class table and the energy
@@ -750,16 +746,16 @@ __global__ __launch_bounds__(TYH * LW) void k_fused2_en_cls(FArgs<R> A, EnOut eo
     typedef Lds2<R, S::rows, NBC, S::lw, true> LT;
     __shared__ LT L;
     __shared__ double et[TETE_MAX_CLASSES * ET_N];
-    int ty, tz, cx;
-    if (!fused2_tile_of(A, nullptr, ty, tz, cx)) {      // whole group
+    Tile t;
+    if (!fused2_tile_of(A, nullptr, t)) {      // whole group
         if (threadIdx.x == 0) eo.part[2 * blockIdx.x] = eo.part[2 * blockIdx.x + 1] = 0.0;
         return;
     }
     const double ha2 = 0.5 * eo.a * eo.a;
-    for (int t = threadIdx.x; t < TETE_MAX_CLASSES; t += TYH * LW) {
+    for (int m = threadIdx.x; m < TETE_MAX_CLASSES; m += TYH * LW) {
         double v[6];
-        for (int c = 0; c < 6; ++c) v[c] = (double)(R)eo.craw[6 * t + c];
-        double* o = et + ET_N * t;
+        for (int c = 0; c < 6; ++c) v[c] = (double)(R)eo.craw[6 * m + c];
+        double* o = et + ET_N * m;
         o[ET_SKX] = v[0] > 0.0 ? 0.5 / v[0] : 0.0;
         o[ET_SKY] = v[1] > 0.0 ? 0.5 / v[1] : 0.0;
         o[ET_SKZ] = v[2] > 0.0 ? 0.5 / v[2] : 0.0;
@@ -773,7 +769,7 @@ __global__ __launch_bounds__(TYH * LW) void k_fused2_en_cls(FArgs<R> A, EnOut eo
     }
     __syncthreads();
     eo.et = et;
-    fused2_tile<R, S::rows, NBC, S::lw, PD, false, true, false, LT, true>(A, ty, tz, cx, L, WitMid<R>{}, Arr6<R>{},
+    fused2_tile<R, S::rows, NBC, S::lw, PD, false, true, false, LT, true>(A, t, L, WitMid<R>{}, Arr6<R>{},
                                                                             eo);
 }
 
@@ -784,9 +780,9 @@ __global__ __launch_bounds__(TYH * LW) void k_fused2_arr(FArgs<R> A, Arr6<R> MA,
 {
     typedef Shape2<R, TYH, LW> S;
     __shared__ Lds2<R, S::rows, S::nb, S::lw> L;
-    int ty, tz, cx;
-    if (!fused2_tile_of(A, act, ty, tz, cx)) return;   // whole group
-    fused2_tile<R, S::rows, S::nb, S::lw, PD, false, false, true>(A, ty, tz, cx, L, WitMid<R>{}, MA);
+    Tile t;
+    if (!fused2_tile_of(A, act, t)) return;   // whole group
+    fused2_tile<R, S::rows, S::nb, S::lw, PD, false, false, true>(A, t, L, WitMid<R>{}, MA);
 }
 
 // The two-step kernel with materials by class.
@@ -795,9 +791,9 @@ __global__ __launch_bounds__(TYH * LW) void k_fused2_cls(FArgs<R> A, const int* 
 {
     typedef Shape2<R, TYH, LW> S;
     __shared__ Lds2<R, S::rows, S::nb, S::lw, true> L;
-    int ty, tz, cx;
-    if (!fused2_tile_of(A, act, ty, tz, cx)) return;   // whole group
-    fused2_tile<R, S::rows, S::nb, S::lw, PD, false, true>(A, ty, tz, cx, L);
+    Tile t;
+    if (!fused2_tile_of(A, act, t)) return;   // whole group
+    fused2_tile<R, S::rows, S::nb, S::lw, PD, false, true>(A, t, L);
 }
 
 // A tile of the two-step kernel is static when every entry it loads (its rows
@@ -839,9 +835,9 @@ __global__ __launch_bounds__(TYH * LW) void k_fused2_wit(FArgs<R> A, WitMid<R> w
 {
     typedef Shape2<R, TYH, LW> S;
     __shared__ Lds2<R, S::rows, S::nb, S::lw> L;
-    int ty, tz, cx;
-    if (!fused2_tile_of(A, act, ty, tz, cx)) return;   // whole group
-    fused2_tile<R, S::rows, S::nb, S::lw, Default2<R>::pd, true>(A, ty, tz, cx, L, wm);
+    Tile t;
+    if (!fused2_tile_of(A, act, t)) return;   // whole group
+    fused2_tile<R, S::rows, S::nb, S::lw, Default2<R>::pd, true>(A, t, L, wm);
 }
 
 // Two steps of every active instance of a batch, by a persistent grid, as the
@@ -884,9 +880,8 @@ __global__ __launch_bounds__(Default2<R>::rows * Default2<R>::lw) void k_fused2_
             for (int i = 0; i < (int)(sizeof(FArgs<R>) / 4); ++i) dst[i] = src[i];
         }
         A.src.n = T->step[inst] + steps;
-        int ty, tz, cx;
-        if (tile_of(w - T->offset2[inst], A.order, A.nyt, A.nzt, ty, tz, cx))
-            fused2_tile<R, S::rows, S::nb, S::lw, Default2<R>::pd>(A, ty, tz, cx, L);
+        Tile t;
+        if (tile_at(A, w - T->offset2[inst], t)) fused2_tile<R, S::rows, S::nb, S::lw, Default2<R>::pd>(A, t, L);
         __syncthreads();   // the LDS is reused by the next item
     }
 }
@@ -901,7 +896,7 @@ hipError_t launch_batch_step2(BatchTable<R>* T, int grid, int flips, int steps, 
 }
 
 template <typename R>
-bool fused2_setup(FArgs<R>& A, int rows, int xchunk, int order, int lanes)
+bool fused2_setup(FArgs<R>& A, int rows, int xchunk, int order, int lanes, bool member)
 {
     if (rows == 0) rows = Default2<R>::rows;
     if (rows != 16 && !((rows == 24 || rows == 32) && sizeof(R) == 4)) return false;
@@ -909,27 +904,12 @@ bool fused2_setup(FArgs<R>& A, int rows, int xchunk, int order, int lanes)
     const int TY = rows - 6, KT2 = (lanes ? lanes : lanes2(sizeof(R), rows)) - 4;
     A.nyt = (A.g.ny + 1 + TY - 1) / TY;
     A.nzt = (A.g.nz + 1 + KT2 - 1) / KT2;
-    const int nplanes = A.g.nx + 1;
     // every buffer range must stay below 2^31 bytes: (xchunk + 8) planes
     const int64_t plane_bytes = (int64_t)A.g.sp * sizeof(R);
     const int64_t xmax = ((int64_t(1) << 31) - 1) / plane_bytes - 8;
     if (xmax < 1) return false;
-    int xc = xchunk;
-    if (xc <= 0) {
-        // as few chunks as possible (each re-reads seven halo planes and
-        // refills the pipeline), but enough workgroups for half of the CUs,
-        // chunks of at least 16 planes, and each within the buffer limit
-        const int tiles = A.nyt * A.nzt;
-        int chunks = (128 + tiles - 1) / tiles;
-        chunks = std::min(chunks, std::max(1, nplanes / 16));
-        chunks = (int)std::max<int64_t>(chunks, (nplanes + xmax - 1) / xmax);
-        xc = (nplanes + chunks - 1) / chunks;
-    }
-    xc = (int)std::min<int64_t>(std::max(xc, 1), xmax);
-    A.xchunk = xc;
-    A.nxc = (nplanes + xc - 1) / xc;
-    A.order = order != 0 ? order : default_order(A.nyt, A.nzt, A.nxc);
-    A.nblk = launch_tiles(A.order, A.nyt, A.nzt, A.nxc);
+    // planes xs-4 .. xe+7, of which the first and the last few are cheaper
+    set_chunks(A, xchunk, order, xmax, 10, KT2 == 28 ? 3 : 2, member);
     return true;
 }
 
@@ -967,7 +947,8 @@ hipError_t fused2_static_tiles(const uint8_t* code, Geo g, int rows, int xchunk,
     // the active tiles in the order the full launch takes them
     std::vector<int> list;
     list.reserve((size_t)nt);
-    for (int lb = 0; lb < A.nblk; ++lb) {
+    const int nlb = launch_tiles(A.order, A.nyt, A.nzt, A.nxc);
+    for (int lb = 0; lb < nlb; ++lb) {
         int ty, tz, cx;
         if (!tile_of(lb, A.order, A.nyt, A.nzt, ty, tz, cx)) continue;
         const int t = (cx * A.nyt + ty) * A.nzt + tz;
@@ -1113,7 +1094,7 @@ hipError_t launch_step_fused2(Fields<R> o, Fields<R> nf, Mat<R> M, Geo g, R alph
 
 #define TETE_FUSED2_INST(R)                                                                                    \
     template hipError_t launch_batch_step2<R>(BatchTable<R>*, int, int, int, hipStream_t);                     \
-    template bool fused2_setup<R>(FArgs<R>&, int, int, int, int);                                              \
+    template bool fused2_setup<R>(FArgs<R>&, int, int, int, int, bool);                                           \
     template hipError_t launch_step_fused2<R>(Fields<R>, Fields<R>, Mat<R>, Geo, R, Src, const WitMid<R>*, int, \
                                               int, int, int, hipStream_t, hipEvent_t*, const int*, int,      \
                                               const EnergyPair*);                                            \

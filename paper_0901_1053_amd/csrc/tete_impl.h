@@ -90,6 +90,9 @@ struct FArgs {
     int nyt, nzt, nxc, xchunk;   // tiles along j, k; chunks along x; planes per chunk
     int order;                   // tile order
     int nblk;                    // work items (workgroups) of one step
+    // work items from nfull on are the tail: the last tile-chunks of the launch,
+    // each cut along x into tsplit items of tchunk planes (nfull = nblk: none)
+    int nfull, tsplit, tchunk;
 };
 
 // Device-resident table of a batch (tete_batch_*): the active instances, their
@@ -166,14 +169,15 @@ FArgs<R> fused_args(Fields<R> oldf, Fields<R> newf, Mat<R> mat, Geo g, R alpha, 
 // Fills the tiling of A for a launch shape; false if the shape is invalid or
 // the grid's planes are too large for the fused kernel.
 template <typename R>
-bool fused_setup(FArgs<R>& A, int rows, int xchunk, int order);
+bool fused_setup(FArgs<R>& A, int rows, int xchunk, int order, bool member = false);
 int fused_default_rows(int real_bytes);
 // Two steps in one launch (tete_fused2.hip): the fused step temporally
 // blocked; xchunk and order as for the single step.
 bool fused2_fits(Geo g, int real_bytes);
 // rows: 0 (default), 16, or 24 or 32 (FP32 only: rows of 32 lanes).
 template <typename R>
-bool fused2_setup(FArgs<R>& A, int rows, int xchunk, int order, int lanes = 0);
+// member: the grid steps as a member of a batch
+bool fused2_setup(FArgs<R>& A, int rows, int xchunk, int order, int lanes = 0, bool member = false);
 // Energy samples taken by a two-step launch: want bit 0 the energy of its
 // input y^n, bit 1 that of y^{n+1}; written to out[0], out[1] (only the ones
 // wanted, in that order); part: cap pairs of FP64 partial sums.

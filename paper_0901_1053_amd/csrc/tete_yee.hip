@@ -28,14 +28,14 @@ struct LdsY {
 };
 
 template <typename R, int TYH, int PD>
-__device__ __forceinline__ void yee_tile(const FArgs<R>& A, const int ty, const int tz, const int cx, LdsY<R, TYH>& L)
+__device__ __forceinline__ void yee_tile(const FArgs<R>& A, const Tile& t, LdsY<R, TYH>& L)
 {
     constexpr int TY = TYH - 2;
     const Geo g = A.g;
     const int kl = threadIdx.x & 63;
     const int jl = threadIdx.x >> 6;
-    const int j = ty * TY - 1 + jl;
-    const int k = tz * KTY - 1 + kl;
+    const int j = t.ty * TY - 1 + jl;
+    const int k = t.tz * KTY - 1 + kl;
     const bool jin = (unsigned)j <= (unsigned)g.ny;
     const bool kin = (unsigned)k <= (unsigned)g.nz;
     const bool node = jin && kin;
@@ -46,8 +46,7 @@ __device__ __forceinline__ void yee_tile(const FArgs<R>& A, const int ty, const 
     const bool hy_k = node && k < g.nz;
     const bool hz_j = node && j < g.ny;
 
-    const int xs = cx * A.xchunk;
-    const int xe = min(xs + A.xchunk, g.nx + 1);
+    const int xs = t.xs, xe = t.xe;
     const int xload_end = min(xe, g.nx);         // last plane whose old data is needed
 
     const R dt = A.a + A.a;                      // dtau
@@ -158,9 +157,9 @@ template <typename R, int TYH, int PD>
 __global__ __launch_bounds__(64 * TYH) void k_yee(FArgs<R> A)
 {
     __shared__ LdsY<R, TYH> L;
-    int ty, tz, cx;
-    if (!tile_of(xcd_remap(blockIdx.x, A.nblk), A.order, A.nyt, A.nzt, ty, tz, cx)) return;   // whole group
-    yee_tile<R, TYH, PD>(A, ty, tz, cx, L);
+    Tile t;
+    if (!tile_at(A, xcd_rounds(blockIdx.x, A.nblk), t)) return;   // whole group
+    yee_tile<R, TYH, PD>(A, t, L);
 }
 
 // Two steps of (7) per launch, temporally blocked as the TE/TM two-step
@@ -180,15 +179,14 @@ struct LdsY2 {
 };
 
 template <typename R, int TYH, int PD>
-__device__ __forceinline__ void yee2_tile(const FArgs<R>& A, const int ty, const int tz, const int cx,
-                                          LdsY2<R, TYH>& L)
+__device__ __forceinline__ void yee2_tile(const FArgs<R>& A, const Tile& t, LdsY2<R, TYH>& L)
 {
     constexpr int TY = TYH - 4;
     const Geo g = A.g;
     const int kl = threadIdx.x & 63;
     const int jl = threadIdx.x >> 6;
-    const int j = ty * TY - 2 + jl;
-    const int k = tz * KTY2 - 2 + kl;
+    const int j = t.ty * TY - 2 + jl;
+    const int k = t.tz * KTY2 - 2 + kl;
     const bool jin = (unsigned)j <= (unsigned)g.ny;
     const bool kin = (unsigned)k <= (unsigned)g.nz;
     const bool node = jin && kin;
@@ -199,8 +197,7 @@ __device__ __forceinline__ void yee2_tile(const FArgs<R>& A, const int ty, const
     const bool hy_k = node && k < g.nz;
     const bool hz_j = node && j < g.ny;
 
-    const int xs = cx * A.xchunk;
-    const int xe = min(xs + A.xchunk, g.nx + 1);
+    const int xs = t.xs, xe = t.xe;
     const int xload_end = min(xe + 1, g.nx);     // last plane whose old data is needed
 
     const R dt = A.a + A.a;                      // dtau
@@ -333,9 +330,9 @@ template <typename R, int TYH, int PD>
 __global__ __launch_bounds__(64 * TYH) void k_yee2(FArgs<R> A)
 {
     __shared__ LdsY2<R, TYH> L;
-    int ty, tz, cx;
-    if (!tile_of(xcd_remap(blockIdx.x, A.nblk), A.order, A.nyt, A.nzt, ty, tz, cx)) return;   // whole group
-    yee2_tile<R, TYH, PD>(A, ty, tz, cx, L);
+    Tile t;
+    if (!tile_at(A, xcd_rounds(blockIdx.x, A.nblk), t)) return;   // whole group
+    yee2_tile<R, TYH, PD>(A, t, L);
 }
 
 constexpr int ROWSY = 16;
@@ -348,25 +345,11 @@ bool yee_setup(FArgs<R>& A, int xchunk, int order)
     constexpr int TY = ROWSY - 2;
     A.nyt = (A.g.ny + 1 + TY - 1) / TY;
     A.nzt = (A.g.nz + 1 + KTY - 1) / KTY;
-    const int nplanes = A.g.nx + 1;
     // every buffer range must stay below 2^31 bytes: (xchunk + 2) planes
     const int64_t plane_bytes = (int64_t)A.g.sp * sizeof(R);
     const int64_t xmax = ((int64_t(1) << 31) - 1) / plane_bytes - 2;
     if (xmax < 1) return false;
-    int xc = xchunk;
-    if (xc <= 0) {
-        // as in the fused single step: enough workgroups to fill the chip
-        // several times over, chunks of at least 32 planes
-        const int tiles = A.nyt * A.nzt;
-        int chunks = (4096 + tiles - 1) / tiles;
-        chunks = std::max(1, std::min(chunks, (nplanes + 31) / 32));
-        xc = (nplanes + chunks - 1) / chunks;
-    }
-    xc = (int)std::min<int64_t>(std::max(xc, 1), xmax);
-    A.xchunk = xc;
-    A.nxc = (nplanes + xc - 1) / xc;
-    A.order = order != 0 ? order : default_order(A.nyt, A.nzt, A.nxc);
-    A.nblk = launch_tiles(A.order, A.nyt, A.nzt, A.nxc);
+    set_chunks(A, xchunk, order, xmax, 2, 3, false);
     return true;
 }
 
@@ -397,23 +380,11 @@ bool yee2_setup(FArgs<R>& A, int xchunk, int order)
     constexpr int TY = ROWSY - 4;
     A.nyt = (A.g.ny + 1 + TY - 1) / TY;
     A.nzt = (A.g.nz + 1 + KTY2 - 1) / KTY2;
-    const int nplanes = A.g.nx + 1;
     // every buffer range must stay below 2^31 bytes: (xchunk + 3) planes
     const int64_t plane_bytes = (int64_t)A.g.sp * sizeof(R);
     const int64_t xmax = ((int64_t(1) << 31) - 1) / plane_bytes - 3;
     if (xmax < 1) return false;
-    int xc = xchunk;
-    if (xc <= 0) {
-        const int tiles = A.nyt * A.nzt;
-        int chunks = (4096 + tiles - 1) / tiles;
-        chunks = std::max(1, std::min(chunks, (nplanes + 31) / 32));
-        xc = (nplanes + chunks - 1) / chunks;
-    }
-    xc = (int)std::min<int64_t>(std::max(xc, 1), xmax);
-    A.xchunk = xc;
-    A.nxc = (nplanes + xc - 1) / xc;
-    A.order = order != 0 ? order : default_order(A.nyt, A.nzt, A.nxc);
-    A.nblk = launch_tiles(A.order, A.nyt, A.nzt, A.nxc);
+    set_chunks(A, xchunk, order, xmax, 4, 3, false);
     return true;
 }
 
