@@ -629,7 +629,7 @@ typedef struct {
 } tete_rz_bunch;
 tete_status tete_rz_set_bunch(tete_rz* g, const tete_rz_bunch* b);
 
-/* Enqueue nsteps steps of (24) (asynchronous; one or two steps per launch).
+/* Enqueue nsteps steps of (24) (asynchronous; four, two or one per launch).
  * Errors: TETE_ERR_ARG (nsteps < 0), TETE_ERR_DEVICE. */
 tete_status tete_rz_step(tete_rz* g, int64_t nsteps);
 
@@ -670,10 +670,10 @@ tete_status tete_rz_wake(tete_rz* g, double* W_par, double* W_perp, int32_t nw);
 tete_status tete_rz_energy(tete_rz* g, double* W, int64_t* n);
 
 /* Launch tuning of the r-z kernel: kernel TETE_KERNEL_AUTO or
- * TETE_KERNEL_FUSED2 (two steps per launch: a second march stage follows the
- * first two rows behind it in the same wave, so each cell is read and written
- * once per two steps; an odd last step runs alone) or TETE_KERNEL_FUSED (one
- * step per launch); rows per r-chunk (0 = automatic, else 8 .. 4096), rows
+ * TETE_KERNEL_FUSED2 (four steps per launch: three further march stages follow
+ * the first, each two rows behind the one before in the same wave, so each cell
+ * is read and written once per four steps; what is left of nsteps takes two
+ * steps, then one) or TETE_KERNEL_FUSED (one step per launch); rows per r-chunk (0 = automatic, else 8 .. 4096), rows
  * loaded ahead (0 = automatic, else 1 .. 4) and the workgroup order (0 =
  * automatic, 1 = the r-chunks of a z-column consecutive, 2 = the z-strips of
  * a chunk consecutive).  Results do not depend on it. */

@@ -19,6 +19,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "tete_dev.h"
@@ -30,7 +31,8 @@ constexpr double kEps0 = 8.8541878128e-12;   // vacuum permittivity [F/m] (CODAT
 constexpr double kPi = 3.14159265358979323846;
 constexpr int kLanes = 64;                   // lanes per wave
 constexpr int kWaves = 4;                    // waves (z-strips) per workgroup
-constexpr int kPad = 4;                      // coefficient rows below 0 and above nr
+constexpr int kSteps = 4;                    // most steps per launch
+constexpr int kPad = 2 * kSteps + 4;         // coefficient rows below 0 and above nr
 constexpr int kRedBlocks = 1024, kRedThreads = 256;
 
 // Node code bits: e edge PEC or absent; HK = no h_phi / h_r at this k (k = nz).
@@ -63,7 +65,7 @@ struct RZArgs {
     int kend;               // the wake quadrature takes edges k < kend
     int64_t n;              // step being taken
     const double* lamw;     // 2M+1: harmonic weight * cell charge / dtau
-    double* acc;            // [step parity][line jw, jw+1][nw] wake accumulators
+    double* acc;            // [step mod kSteps][line jw, jw+1][nw] wake accumulators
 };
 
 template <typename R>
@@ -78,55 +80,75 @@ struct Fin {
     R hp, hr, ez, ep, er, hz;
 };
 
+// v, or 0 where bit b of the mask is clear
+template <typename R>
+__device__ __forceinline__ R keep(uint32_t mask, int b, R v)
+{
+    const uint32_t m = (uint32_t)((int32_t)(mask << (31 - b)) >> 31);
+    if constexpr (sizeof(R) == 4) {
+        return __builtin_bit_cast(R, __builtin_bit_cast(uint32_t, v) & m);
+    } else {
+        const uint64_t m2 = ((uint64_t)m << 32) | m;
+        return __builtin_bit_cast(R, __builtin_bit_cast(uint64_t, v) & m2);
+    }
+}
+
+// a b + c with one rounding: the terms in m are written with it, since a
+// product used twice may else be rounded in one instance of the kernel and not
+// in another, and the steps per launch would show in the results.
+__device__ __forceinline__ float madd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double madd(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // March state of one step along r.  With q the row it takes in: old values
 // of row q-1, the partial results of row q-2 and the new h_z of row q-3.
 // advance() runs S1, S2, S3, S5, S6 at row q-1 and S4, S7, S8, S9, S10 at row
-// q-2, which it returns final.  The PEC / absence bits zero the coefficient of
-// a masked entry (x + 0 * d == x) instead of selecting the result: a select
+// q-2, which it returns final.  PEC and absence zero the coefficient of a
+// masked entry (x + 0 * d == x) instead of selecting the result: a select
 // around an update can be compiled into a branch, and a lane shift inside it
-// would then read 0 from the lanes the branch disables.
+// would then read 0 from the lanes the branch disables.  The coefficients of
+// e_phi and h_phi are used at rows q-1 and q-2 and carried masked between the
+// two.
 template <typename R>
 struct Stage {
     R EZ1 = 0, ER1 = 0, EP1 = 0, HP1 = 0, HR1 = 0, HZ1 = 0;
-    uint32_t C1 = C_ALL;
     R HZ2 = 0, HPn2 = 0, EZh2 = 0, ER2 = 0, HRh2 = 0, EPh2 = 0;
-    uint32_t C2 = C_ALL;
     R HZn3 = 0;
+    R cp2 = 0, dp2 = 0;     // masked a kappa_phi, a mu_phi of row q-2
 
-    // src(C1, cz1, ez_old, ez_new) adds the current to e_z of row q-1 and
-    // accumulates the wake there.
+    // c1, c2: the coefficients of rows q-1, q-2; fr: bit 3 r + b set where e
+    // component b (phi, r, z) of row q-r is free; hk: h_phi and h_r exist at
+    // this k.  src(e_z free, cz1, ez_old, ez_new) adds the current to e_z of
+    // row q-1 and accumulates the wake there.
     template <typename F>
-    __device__ __forceinline__ Fin<R> advance(const Row<R>& cur, uint32_t cq, const Coef<R>& c1,
+    __device__ __forceinline__ Fin<R> advance(const Row<R>& cur, uint32_t fr, uint32_t hk, const Coef<R>& c1,
                                               const Coef<R>& c2, R m, F&& src)
     {
-        const R hp1 = (C1 & C_HK) ? (R)0 : c1.dp, hr1c = (C1 & C_HK) ? (R)0 : c1.dr;
-        const R ez1c = (C1 & C_EZ) ? (R)0 : c1.cz, ep1c = (C1 & C_EPHI) ? (R)0 : c1.cp;
-        const R hp2 = (C2 & C_HK) ? (R)0 : c2.dp, er2c = (C2 & C_ER) ? (R)0 : c2.cr;
-        const R ep2c = (C2 & C_EPHI) ? (R)0 : c2.cp;
+        const R hp1 = keep(hk, 0, c1.dp), hr1c = keep(hk, 0, c1.dr);
+        const R ez1c = keep(fr, 5, c1.cz), ep1c = keep(fr, 3, c1.cp), er2c = keep(fr, 7, c2.cr);
 
         // S1 at q-1: h_phi^n = h_phi^{n-1/2} + a mu_phi [P_z e_r^n - P_r e_z^{n-1/2}]
         const R hpn1 = HP1 + hp1 * ((lane_next(ER1) - ER1) - (cur.ez - EZ1));
         // S2 at q-1: h_r^n = h_r^{n-1/2} + a mu_r [-P_z e_phi^n + m e_z^{n-1/2}]
         const R pzEP1 = lane_next(EP1) - EP1;
-        const R hrn1 = HR1 + hr1c * (m * EZ1 - pzEP1);
+        const R hrn1 = HR1 + hr1c * madd(m, EZ1, -pzEP1);
         // S3 at q-1: e_z^{n+1/2} = e_z^{n-1/2} + f_e 2a kappa_z [P_r^* h_phi^n - m h_r^n - j_z^n]
-        R ezh1 = EZ1 + ez1c * ((HPn2 - hpn1) - m * hrn1);
-        src(C1, c1.cz, EZ1, ezh1);
+        R ezh1 = EZ1 + ez1c * madd(-m, hrn1, HPn2 - hpn1);
+        src((fr & 32u) != 0, c1.cz, EZ1, ezh1);
         // S5 at q-1: h_r^{n+1/2} = h_r^n + a mu_r [-P_z e_phi^n + m e_z^{n+1/2}]
-        const R hrh1 = hrn1 + hr1c * (m * ezh1 - pzEP1);
+        const R hrh1 = hrn1 + hr1c * madd(m, ezh1, -pzEP1);
         // S6 at q-1: e_phi^{n+1/2} = e_phi^n + a kappa_phi [P_z^* h_r^{n+1/2} - P_r^* h_z^n]
         const R eph1 = EP1 + ep1c * ((lane_prev(hrh1) - hrh1) - (HZ2 - HZ1));
         // S4 at q-2: h_phi^{n+1/2} = h_phi^n + a mu_phi [P_z e_r^n - P_r e_z^{n+1/2}]
-        const R hph2 = HPn2 + hp2 * ((lane_next(ER2) - ER2) - (ezh1 - EZh2));
+        const R hph2 = HPn2 + dp2 * ((lane_next(ER2) - ER2) - (ezh1 - EZh2));
         // S7 at q-2: e_r^{n+1/2} = e_r^n + a kappa_r [-P_z^* h_phi^{n+1/2} + m h_z^n]
         const R pzsHP2 = lane_prev(hph2) - hph2;
-        const R erh2 = ER2 + er2c * (m * HZ2 - pzsHP2);
+        const R erh2 = ER2 + er2c * madd(m, HZ2, -pzsHP2);
         // S8 at q-2: h_z^{n+1} = h_z^n + f_h 2a mu_z [P_r e_phi^{n+1/2} - m e_r^{n+1/2}]
-        const R hzn2 = HZ2 + c2.dz * ((eph1 - EPh2) - m * erh2);
+        const R hzn2 = HZ2 + c2.dz * madd(-m, erh2, eph1 - EPh2);
         // S9 at q-2: e_phi^{n+1} = e_phi^{n+1/2} + a kappa_phi [P_z^* h_r^{n+1/2} - P_r^* h_z^{n+1}]
-        const R ep2 = EPh2 + ep2c * ((lane_prev(HRh2) - HRh2) - (HZn3 - hzn2));
+        const R ep2 = EPh2 + cp2 * ((lane_prev(HRh2) - HRh2) - (HZn3 - hzn2));
         // S10 at q-2: e_r^{n+1} = e_r^{n+1/2} + a kappa_r [-P_z^* h_phi^{n+1/2} + m h_z^{n+1}]
-        const R er2 = erh2 + er2c * (m * hzn2 - pzsHP2);
+        const R er2 = erh2 + er2c * madd(m, hzn2, -pzsHP2);
         const Fin<R> f{hph2, HRh2, EZh2, ep2, er2, hzn2};
 
         // advance by one row
@@ -137,22 +159,30 @@ struct Stage {
         EZh2 = ezh1;
         HPn2 = hpn1;
         HZ2 = HZ1;
-        C2 = C1;
+        cp2 = ep1c;
+        dp2 = hp1;
         EZ1 = cur.ez;
         ER1 = cur.er;
         EP1 = cur.ep;
         HP1 = cur.hp;
         HR1 = cur.hr;
         HZ1 = cur.hz;
-        C1 = cq;
         return f;
     }
 };
 
-// NS steps per launch (1 or 2).  With two, a second stage marches two rows
-// behind the first and takes its final rows (step n+1) as input, so that a
-// cell is read and written once per two steps; each step costs two rows of
-// halo on either side of a chunk and one lane on either side of the strip.
+// NS steps per launch (1, 2 or 4).  Each further stage marches two rows behind
+// the one before and takes its final rows as input, so that a cell is read and
+// written once per NS steps; each step costs two rows of halo on either side of
+// a chunk and one lane on either side of the strip.  HBM bounds one and two
+// steps per launch; with four it is the instructions issued, 244 vector
+// instructions per row and wave in FP32.  Scalar registers are short (the
+// arrays' resources, six coefficients per stage and row), and what does not
+// fit is kept in vector lanes at an instruction per use: so the stores take no
+// resources, the masks are bit operations on a history of three bits per row,
+// and the march of chunks without the ring or a wake line has no test for them.
+// Per step on 1000 x 18183, m = 1: FP32 121 us with two steps per launch, 60
+// with four; FP64 211, 101; 333 x 4001, m = 0, FP64 19.1, 11.0.
 template <typename R, int PF, int NS>
 __global__ __launch_bounds__(kLanes * kWaves) void k_rz(RZArgs<R> A)
 {
@@ -182,8 +212,6 @@ __global__ __launch_bounds__(kLanes * kWaves) void k_rz(RZArgs<R> A)
     };
     const auto rEP = mk(A.o[0], np * RB), rER = mk(A.o[1], np * RB), rEZ = mk(A.o[2], np * RB),
                rHP = mk(A.o[3], np * RB), rHR = mk(A.o[4], np * RB), rHZ = mk(A.o[5], np * RB);
-    const auto sEP = mk(A.w[0], np * RB), sER = mk(A.w[1], np * RB), sEZ = mk(A.w[2], np * RB),
-               sHP = mk(A.w[3], np * RB), sHR = mk(A.w[4], np * RB), sHZ = mk(A.w[5], np * RB);
     const auto rC = mk(A.code, np + 4);
 
     auto load = [&](int p) {
@@ -203,10 +231,12 @@ __global__ __launch_bounds__(kLanes * kWaves) void k_rz(RZArgs<R> A)
         v.c = __builtin_amdgcn_raw_buffer_load_b32(rC, ok ? (idx & ~3u) : OOB, 0, 0);
         return v;
     };
-    auto code_of = [&](int p, uint32_t cw) {
-        const bool ok = kin && p <= A.nr;
+    const uint32_t kfree = kin ? 7u : 0u, hk = kin && k < A.nz ? 1u : 0u;
+    // e components of row p that are free here (bits phi, r, z); rows outside
+    // the grid have zero coefficients in the table
+    auto free_of = [&](int p, uint32_t cw) {
         const uint32_t idx = (uint32_t)p * (uint32_t)A.sz + (uint32_t)k;
-        return ((cw >> (8 * (idx & 3u))) & 0xffu) | (ok ? 0u : (uint32_t)C_ALL);
+        return ~(cw >> (8 * (idx & 3u))) & kfree;
     };
     // The coefficient table is read through the constant address space with a
     // uniform row index: scalar loads, outside the vector-memory counter that
@@ -214,21 +244,21 @@ __global__ __launch_bounds__(kLanes * kWaves) void k_rz(RZArgs<R> A)
     // prefetched rows too).
     typedef const __attribute__((address_space(4))) R* CR;
     const CR ctab = (CR)(const void*)A.coef;
-    auto coef = [&](int row) {
-        const int o = __builtin_amdgcn_readfirstlane(row + kPad) * 6;
+    auto coef = [&](CR r) {
         Coef<R> c;
-        c.cp = ctab[o + 0];
-        c.cr = ctab[o + 1];
-        c.cz = ctab[o + 2];
-        c.dp = ctab[o + 3];
-        c.dr = ctab[o + 4];
-        c.dz = ctab[o + 5];
+        c.cp = r[0];
+        c.cr = r[1];
+        c.cz = r[2];
+        c.dp = r[3];
+        c.dr = r[4];
+        c.dz = r[5];
         return c;
     };
     // bunch current and wake lines of the step with index n at row j1
-    auto source = [&](int j1, int64_t n) {
-        return [&, j1, n](uint32_t C1, R cz1, R ezold, R& ezh1) {
-            if (A.src && j1 == A.j0 && !(C1 & C_EZ) && k < A.nz) {
+    auto source = [&](auto with, int j1, int64_t n) {
+        return [&, j1, n](bool free, R cz1, R ezold, R& ezh1) {
+            if constexpr (!decltype(with)::value) return;
+            if (j1 == A.j0 && free) {
                 const int64_t mm = (int64_t)k - n + A.M;         // cell mm crosses edge k in step n
                 if (mm >= -A.M && mm <= A.M) {
                     // the current term is rounded on its own, as in the 3-D kernels
@@ -236,53 +266,66 @@ __global__ __launch_bounds__(kLanes * kWaves) void k_rz(RZArgs<R> A)
                     ezh1 -= (R)((double)cz1 * A.lamw[mm + A.M]);
                 }
             }
-            if (A.src && (j1 == A.jw || j1 == A.jw + 1) && j1 >= ra && j1 < rb && own_k && k < A.kend) {
+            if ((j1 == A.jw || j1 == A.jw + 1) && j1 >= ra && j1 < rb && own_k && k < A.kend) {
                 const int64_t js = n - k - A.M;                  // wake sample of edge k
-                // even and odd steps accumulate into separate arrays: in a two-step
-                // launch lane k's step n and lane k+1's step n+1 meet at one sample
+                // the steps of a launch accumulate into separate arrays: lane k's
+                // step n and lane k+1's step n+1 meet at one sample
                 if (js >= A.jmin && js < (int64_t)A.jmin + A.nw)
-                    A.acc[((int)(n & 1) * 2 + (j1 - A.jw)) * A.nw + (js - A.jmin)] +=
+                    A.acc[((int)(n & (kSteps - 1)) * 2 + (j1 - A.jw)) * A.nw + (js - A.jmin)] +=
                         -0.5 * ((double)ezold + (double)ezh1);
             }
         };
     };
+    // plain stores, a scalar base and a 32-bit offset each (no buffer resources,
+    // whose scalar registers the stages' coefficients need)
     auto store = [&](int q, const Fin<R>& f) {
-        const bool st = own_k && q >= ra && q < rb;
-        const uint32_t so = st ? ((uint32_t)q * (uint32_t)A.sz + (uint32_t)k) * RB : OOB;
-        bstore<R>(sHP, so, f.hp);
-        bstore<R>(sHR, so, f.hr);
-        bstore<R>(sEZ, so, f.ez);
-        bstore<R>(sEP, so, f.ep);
-        bstore<R>(sER, so, f.er);
-        bstore<R>(sHZ, so, f.hz);
+        if (own_k && q >= ra && q < rb) {
+            const uint32_t so = ((uint32_t)q * (uint32_t)A.sz + (uint32_t)k) * RB;
+            *(R*)((char*)A.w[3] + so) = f.hp;
+            *(R*)((char*)A.w[4] + so) = f.hr;
+            *(R*)((char*)A.w[2] + so) = f.ez;
+            *(R*)((char*)A.w[0] + so) = f.ep;
+            *(R*)((char*)A.w[1] + so) = f.er;
+            *(R*)((char*)A.w[5] + so) = f.hz;
+        }
     };
 
     const R m = A.m;
-    Stage<R> SA, SB;
-    Row<R> ring[PF];
+    Stage<R> S[NS];
+    uint32_t fr = 0;   // free e components of rows p, p-1, ... (3 bits each)
+    auto row = [&](auto with, const int p, const Row<R>& cur, Row<R>& nxt) {
+        nxt = load(p + PF);
+        Row<R> in = cur;
+        fr = (fr << 3) | free_of(p, cur.c);
+        // coefficients of row p-2NS (stage t uses rows p-1-2t and p-2-2t)
+        const CR c0 = ctab + __builtin_amdgcn_readfirstlane(p - 2 * NS + kPad) * 6;
+        Fin<R> f;
 #pragma unroll
-    for (int u = 0; u < PF; ++u) ring[u] = load(L0 + u);
-
-    for (int p0 = L0; p0 <= pend; p0 += PF) {
-#pragma unroll
-        for (int u = 0; u < PF; ++u) {
-            const int p = p0 + u;
-            if (p > pend) break;
-            const Row<R> cur = ring[u];
-            ring[u] = load(p + PF);
-            const uint32_t c_m2 = SA.C2;                 // code of row p-2
-            const Fin<R> fa = SA.advance(cur, code_of(p, cur.c), coef(p - 1), coef(p - 2), m,
-                                         source(p - 1, A.n));
-            if constexpr (NS == 1) {
-                store(p - 2, fa);
-            } else {
-                // row p-2 after step n is the second stage's input row
-                const Row<R> rin{fa.ez, fa.er, fa.ep, fa.hp, fa.hr, fa.hz, 0u};
-                const Fin<R> fb = SB.advance(rin, c_m2, coef(p - 3), coef(p - 4), m, source(p - 3, A.n + 1));
-                store(p - 4, fb);
-            }
+        for (int t = 0; t < NS; ++t) {
+            const CR c = c0 + 12 * (NS - 1 - t);
+            f = S[t].advance(in, fr >> (6 * t), hk, coef(c + 6), coef(c), m, source(with, p - 2 * t - 1, A.n + t));
+            // row p-2t-2 after this step is the next stage's input row
+            in = Row<R>{f.ez, f.er, f.ep, f.hp, f.hr, f.hz, 0u};
         }
-    }
+        store(p - 2 * NS, f);
+    };
+    // the PF+1 row buffers are used in turn by a loop unrolled as often, so that
+    // neither they nor the carried state are copied from row to row; the trip
+    // count is rounded up (rows past the chunk are read as absent, not stored)
+    auto march = [&](auto with) {
+        Row<R> buf[PF + 1];
+#pragma unroll
+        for (int u = 0; u < PF; ++u) buf[u] = load(L0 + u);
+        for (int p = L0; p <= pend; p += PF + 1) {
+#pragma unroll
+            for (int u = 0; u <= PF; ++u) row(with, p + u, buf[u], buf[(u + PF) % (PF + 1)]);
+        }
+    };
+    // most chunks hold neither the ring nor a wake line: their march carries no
+    // test for them
+    auto inside = [&](int j) { return j >= L0 && j <= pend; };
+    if (A.src && (inside(A.j0) || inside(A.jw) || inside(A.jw + 1))) march(std::true_type{});
+    else march(std::false_type{});
 }
 
 // Node codes from a cell mask (NULL: empty pillbox).  Cells outside r < nr dr
@@ -401,21 +444,42 @@ __global__ __launch_bounds__(kRedThreads) void k_rz_finish(const double* partial
     if (threadIdx.x == 0) *out = s;
 }
 
-// Wakes in V/C: W_par = (even + odd step sums) / (Q eps0) on both lines;
-// W_perp by the trapezoidal s-integral of (line jw+1 - line jw) / dr from the
-// first sample.
-__global__ void k_rz_wakes(const double* acc, int nw, double scale, double dr, double ds, double* wpar,
-                           double* wperp)
+// Wakes in V/C: W_par = (the sum over the kSteps step arrays) / (Q eps0) on both
+// lines; W_perp by the trapezoidal s-integral of (line jw+1 - line jw) / dr from
+// the first sample.  One workgroup: thread t integrates a run of consecutive
+// samples, and the runs' sums are scanned in order (a single thread's pass over
+// the samples waited for memory at each: 145 us for 551 samples).
+__global__ __launch_bounds__(kRedThreads) void k_rz_wakes(const double* acc, int nw, double scale, double dr,
+                                                        double ds, double* wpar, double* wperp)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double prev = 0.0, run = 0.0;
-    for (int j = 0; j < nw; ++j) {
-        const double a0 = (acc[j] + acc[2 * nw + j]) * scale, a1 = (acc[nw + j] + acc[3 * nw + j]) * scale;
-        wpar[j] = a0;
-        wpar[nw + j] = a1;
-        const double d = (a1 - a0) / dr;
-        if (j > 0) run += 0.5 * (d + prev) * ds;
-        wperp[j] = run;
+    __shared__ double sum[kRedThreads];
+    auto line = [&](int l, int j) {
+        double a = 0.0;
+#pragma unroll
+        for (int t = 0; t < kSteps; ++t) a += acc[(2 * t + l) * nw + j];
+        return a * scale;
+    };
+    for (int j = threadIdx.x; j < nw; j += kRedThreads) {
+        wpar[j] = line(0, j);
+        wpar[nw + j] = line(1, j);
+    }
+    const int run = (nw + kRedThreads - 1) / kRedThreads, lo = min(nw, (int)threadIdx.x * run), hi = min(nw, lo + run);
+    auto diff = [&](int j) { return (line(1, j) - line(0, j)) / dr; };
+    double prev = lo > 0 && lo < hi ? diff(lo - 1) : 0.0, s = 0.0;
+    for (int j = lo; j < hi; ++j) {
+        const double d = diff(j);
+        if (j > 0) s += 0.5 * (d + prev) * ds;
+        prev = d;
+    }
+    sum[threadIdx.x] = s;
+    __syncthreads();
+    double before = 0.0;
+    for (int t = 0; t < (int)threadIdx.x; ++t) before += sum[t];
+    prev = lo > 0 && lo < hi ? diff(lo - 1) : 0.0;
+    for (int j = lo; j < hi; ++j) {
+        const double d = diff(j);
+        if (j > 0) before += 0.5 * (d + prev) * ds;
+        wperp[j] = before;
         prev = d;
     }
 }
@@ -530,7 +594,7 @@ RZLayout rz_layout(const tete_rz_desc* d)
     L.coef = o;    o = up(o + 6 * rb * (size_t)(d->nr + 1 + 2 * kPad));
     L.raw = o;     o = up(o + sizeof(Raw) * (size_t)(d->nr + 1));
     L.lamw = o;    o = up(o + sizeof(double) * TETE_MAX_BUNCH_CELLS);
-    L.acc = o;     o = up(o + sizeof(double) * 4 * TETE_MAX_WAKE);
+    L.acc = o;     o = up(o + sizeof(double) * 2 * kSteps * TETE_MAX_WAKE);
     L.partial = o; o = up(o + sizeof(double) * kRedBlocks);
     L.scal = o;    o = up(o + sizeof(double) * 8);
     L.wout = o;    o = up(o + sizeof(double) * 3 * TETE_MAX_WAKE);
@@ -625,15 +689,33 @@ int rz_nzt(const tete_rz_desc* d, int ns)
     return (d->nz + 1 + own - 1) / own;
 }
 
-// Rows per r-chunk: 16 by default.  Short chunks give many workgroups (about
-// 19 rounds of 256 on the 1000 x 18183 deflector-like grid), so the last
-// round's tail is small; their halo rows are re-read mostly from L2.  On that
-// grid 16 rows measured within 3 % of the best of 16 .. 256 for both kernels
-// and precisions, while automatic chunks of 72 rows were 8 % slower.
+// Rows per r-chunk.  One and two steps per launch are bound by HBM and take 16
+// (measured within 3 % of the best of 16 .. 256 on the 1000 x 18183 grid).  Four
+// steps are bound by issue: a wave marches its rows and 16 halo rows, each SIMD
+// holds `held` waves (the registers of the instance), which share its issue,
+// and below two waves a SIMD waits instead.  Taken are the rows with the
+// smallest sum over the rounds; they spend few halo rows and leave no round
+// nearly empty (1000 x 18183: 84 rows fill one round in FP32, 60 us per step
+// against 67 with 64 rows; 333 x 4001 FP64: 12 rows, 10.5 us against 14.7 with 32).
 int rz_rows(const tete_rz* g, int ns)
 {
-    (void)ns;
-    return g->chunk_rows > 0 ? g->chunk_rows : 16;
+    if (g->chunk_rows > 0) return g->chunk_rows;
+    if (ns < 4) return 16;
+    const int nr1 = g->d.nr + 1, held = g->fp32 ? 4 : 2, simds = 1024;
+    const int64_t strips = rz_nzt(&g->d, ns);
+    int best = 16;
+    int64_t best_cost = 0;
+    for (int chunks = 1; chunks <= std::max(1, nr1 / 8); ++chunks) {
+        const int rows = std::max(8, (nr1 + chunks - 1) / chunks);
+        const int64_t waves = strips * ((nr1 + rows - 1) / rows), slots = (int64_t)simds * held;
+        const int64_t rem = waves % slots;
+        const int64_t cost = (rows + 4 * ns) * (waves / slots * held + (rem ? std::max<int64_t>(2, (rem + simds - 1) / simds) : 0));
+        if (best_cost == 0 || cost < best_cost) {
+            best = rows;
+            best_cost = cost;
+        }
+    }
+    return best;
 }
 
 template <typename R, int NS>
@@ -647,7 +729,7 @@ void rz_kernel(int pf, dim3 grid, dim3 block, hipStream_t s, const RZArgs<R>& A)
     }
 }
 
-// One launch taking ns (1 or 2) steps from y^n in set cur to the other set.
+// One launch taking ns (1, 2 or 4) steps from y^n in set cur to the other set.
 template <typename R>
 hipError_t rz_launch(tete_rz* g, int ns, hipStream_t s)
 {
@@ -680,8 +762,10 @@ hipError_t rz_launch(tete_rz* g, int ns, hipStream_t s)
     A.nrc = nrc;
     A.order = g->order > 0 ? g->order : 2;
     const dim3 grid((unsigned)(A.nzb * nrc)), block(kLanes * kWaves);
-    const int pf = g->prefetch > 0 ? g->prefetch : 2;
-    if (ns == 2) rz_kernel<R, 2>(pf, grid, block, s, A);
+    // four steps: one row ahead leaves registers for more waves
+    const int pf = g->prefetch > 0 ? g->prefetch : ns == 4 ? 1 : 2;
+    if (ns == 4) rz_kernel<R, 4>(pf, grid, block, s, A);
+    else if (ns == 2) rz_kernel<R, 2>(pf, grid, block, s, A);
     else rz_kernel<R, 1>(pf, grid, block, s, A);
     return hipGetLastError();
 }
@@ -837,7 +921,7 @@ tete_status tete_rz_set_fields(tete_rz* g, const void* const f[6], int32_t dtype
         RZCHK(hipGetLastError());
     }
     RZCHK(rz_sanitize_any(g, g->cur));
-    RZCHK(hipMemsetAsync(g->acc, 0, sizeof(double) * 4 * TETE_MAX_WAKE, g->stream));
+    RZCHK(hipMemsetAsync(g->acc, 0, sizeof(double) * 2 * kSteps * TETE_MAX_WAKE, g->stream));
     g->n = 0;
     g->kend = 0;
     return TETE_OK;
@@ -892,7 +976,7 @@ tete_status tete_rz_set_bunch(tete_rz* g, const tete_rz_bunch* b)
         lam[mm + M] = w * b->charge_C * v / g->d.cdt;
     }
     RZCHK(hipMemcpyAsync(g->lamw, lam.data(), sizeof(double) * lam.size(), hipMemcpyHostToDevice, g->stream));
-    RZCHK(hipMemsetAsync(g->acc, 0, sizeof(double) * 4 * TETE_MAX_WAKE, g->stream));
+    RZCHK(hipMemsetAsync(g->acc, 0, sizeof(double) * 2 * kSteps * TETE_MAX_WAKE, g->stream));
     RZCHK(hipStreamSynchronize(g->stream));
     g->b = *b;
     g->has_bunch = 1;
@@ -905,9 +989,9 @@ tete_status tete_rz_step(tete_rz* g, int64_t nsteps)
     if (!g || nsteps < 0) return TETE_ERR_ARG;
     Guard dg(g->device);
     if (!dg.ok) return TETE_ERR_DEVICE;
-    const bool two = g->kernel != TETE_KERNEL_FUSED;
+    const bool many = g->kernel != TETE_KERNEL_FUSED;
     for (int64_t s = 0; s < nsteps;) {
-        const int ns = two && nsteps - s >= 2 ? 2 : 1;
+        const int ns = many && nsteps - s >= 4 ? 4 : many && nsteps - s >= 2 ? 2 : 1;
         const bool rec = g->timing && g->ev_used < g->ev_cap;
         if (rec) RZCHK(hipEventRecord(g->ev[2 * g->ev_used], g->stream));
         RZCHK(g->fp32 ? rz_launch<float>(g, ns, g->stream) : rz_launch<double>(g, ns, g->stream));
@@ -965,7 +1049,7 @@ tete_status tete_rz_set_open_pipes(tete_rz* g, int64_t start_step, int32_t kend)
     RZCHK(rz_sanitize_any(g, g->cur));
     const size_t bytes = (size_t)(g->fp32 ? 4 : 8) * (size_t)(nr + 1) * (size_t)(nz + 1);
     for (int c = 0; c < 6; ++c) RZCHK(launch_zero_bytes(g->f[o][c], bytes, g->stream));
-    RZCHK(launch_zero_bytes(g->acc, sizeof(double) * 4 * TETE_MAX_WAKE, g->stream));
+    RZCHK(launch_zero_bytes(g->acc, sizeof(double) * 2 * kSteps * TETE_MAX_WAKE, g->stream));
     RZCHK(hipStreamSynchronize(g->stream));
     g->n = start_step;
     g->kend = kend;
@@ -985,7 +1069,7 @@ tete_status tete_rz_wake(tete_rz* g, double* W_par, double* W_perp, int32_t nw)
     Guard dg(g->device);
     if (!dg.ok) return TETE_ERR_DEVICE;
     const int n = g->b.nw;
-    k_rz_wakes<<<1, 64, 0, g->stream>>>(g->acc, n, 1.0 / (g->b.charge_C * kEps0), g->d.dr, g->d.dz, g->wout,
+    k_rz_wakes<<<1, kRedThreads, 0, g->stream>>>(g->acc, n, 1.0 / (g->b.charge_C * kEps0), g->d.dr, g->d.dz, g->wout,
                                         g->wout + 2 * n);
     RZCHK(hipGetLastError());
     RZCHK(hipMemcpyAsync(W_par, g->wout, sizeof(double) * nw, hipMemcpyDeviceToHost, g->stream));
