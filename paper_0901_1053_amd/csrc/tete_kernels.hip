@@ -15,6 +15,7 @@
 
 #include <algorithm>
 
+#include "tete_copy.h"
 #include "tete_dev.h"
 #include "tete_impl.h"
 
@@ -147,38 +148,48 @@ __device__ __forceinline__ bool e_pec(const Mat<R>& M, int c, int id)
     return kap(M, c, id) == R(0);
 }
 
-template <typename R>
-__global__ void k_import(Fields<R> dst, const void* s0, const void* s1, const void* s2, const void* s3,
-                         const void* s4, const void* s5, int src_fp32, Mat<R> M, Geo g)
-{
-    int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= g.np) return;
-    int i, j, k;
-    decomp(idx, g, i, j, k);
-    const void* src[6] = {s0, s1, s2, s3, s4, s5};
+// Entries kept on import: each component inside its index range, e where its
+// kappa is not zero.  MAT: kappa from the per-entry arrays (zero outside the
+// ranges), else from the PEC codes (set outside the ranges).
+template <typename R, bool MAT>
+struct KeepXYZ {
+    Mat<R> M;
+    Geo g;
+    __device__ __forceinline__ void operator()(int64_t e, uint32_t (&m)[4]) const
+    {
+        int i, j, k;
+        decomp((int)e, g, i, j, k);
+        uint32_t cw = 0;
+        if constexpr (MAT) {
 #pragma unroll
-    for (int c = 0; c < 6; ++c) {
-        R v = src_fp32 ? (R)((const float*)src[c])[idx] : (R)((const double*)src[c])[idx];
-        bool keep = comp_ok(c, g, i, j, k) && (c >= 3 || !e_pec(M, c, idx));
-        dst.c[c][idx] = keep ? v : R(0);
-    }
-}
-
-template <typename R>
-__global__ void k_export(void* d0, void* d1, void* d2, void* d3, void* d4, void* d5, int dst_fp32,
-                         Fields<R> src, Geo g)
-{
-    int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= g.np) return;
-    void* dst[6] = {d0, d1, d2, d3, d4, d5};
+            for (int c = 0; c < 3; ++c) {
+                R v[4] = {};
+                if (e + 4 <= g.np) load4<true>(M.arr[c], e, v);
+                else
+                    for (int u = 0; e + u < g.np; ++u) v[u] = M.arr[c][e + u];
 #pragma unroll
-    for (int c = 0; c < 6; ++c) {
-        if (dst_fp32)
-            ((float*)dst[c])[idx] = (float)src.c[c][idx];
-        else
-            ((double*)dst[c])[idx] = (double)src.c[c][idx];
+                for (int u = 0; u < 4; ++u) cw |= v[u] != R(0) ? 0u : 1u << (8 * u + c);
+            }
+        } else {
+            cw = *(const uint32_t*)(M.code + e);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            uint32_t b = ~(cw >> (8 * u)) & 7u;
+            if (j < g.ny && k < g.nz) b |= 8u;
+            if (i < g.nx && k < g.nz) b |= 16u;
+            if (i < g.nx && j < g.ny) b |= 32u;
+            m[u] = b;
+            if (++k > g.nz) {
+                k = 0;
+                if (++j > g.ny) {
+                    j = 0;
+                    ++i;
+                }
+            }
+        }
     }
-}
+};
 
 template <typename R>
 __global__ void k_import_mat(R* d0, R* d1, R* d2, R* d3, R* d4, R* d5, const void* s0, const void* s1,
@@ -826,11 +837,6 @@ __global__ void k_expand_classes(R* d0, R* d1, R* d2, R* d3, R* d4, R* d5, const
     }
 }
 
-template <typename R>
-struct Six {
-    R* c[6];
-};
-
 // Classes recognised in per-entry arrays (tete_set_materials): entries with
 // the same six coefficients share a class.  A table of CLS_SLOTS slots keyed
 // by a 64-bit hash of the tuple's bits (open addressing, linear probing)
@@ -1065,14 +1071,22 @@ hipError_t launch_lambda(double* lam, double Q, double sigma, double dz, int M, 
 template <typename R>
 hipError_t launch_import(Fields<R> dst, const void* const src[6], int src_fp32, Mat<R> mat, Geo g, hipStream_t s)
 {
-    k_import<R><<<nblocks(g.np, TB), TB, 0, s>>>(dst, src[0], src[1], src[2], src[3], src[4], src[5], src_fp32, mat, g);
+    auto run = [&](auto keep) {
+        if (src_fp32) run_import6<R, float>(six(dst.c), src, g.np, keep, s);
+        else run_import6<R, double>(six(dst.c), src, g.np, keep, s);
+    };
+    if (mat.arr[0]) run(KeepXYZ<R, true>{mat, g});
+    else run(KeepXYZ<R, false>{mat, g});
     return hipGetLastError();
 }
 
 template <typename R>
 hipError_t launch_export(void* const dst[6], int dst_fp32, Fields<R> src, Geo g, hipStream_t s)
 {
-    k_export<R><<<nblocks(g.np, TB), TB, 0, s>>>(dst[0], dst[1], dst[2], dst[3], dst[4], dst[5], dst_fp32, src, g);
+    Six<const R> a;
+    for (int c = 0; c < 6; ++c) a.c[c] = src.c[c];
+    if (dst_fp32) run_export6<float, R>(dst, a, g.np, s);
+    else run_export6<double, R>(dst, a, g.np, s);
     return hipGetLastError();
 }
 

@@ -22,6 +22,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "tete_copy.h"
 #include "tete_dev.h"
 
 namespace tete {
@@ -33,7 +34,8 @@ constexpr int kLanes = 64;                   // lanes per wave
 constexpr int kWaves = 4;                    // waves (z-strips) per workgroup
 constexpr int kSteps = 4;                    // most steps per launch
 constexpr int kPad = 2 * kSteps + 4;         // coefficient rows below 0 and above nr
-constexpr int kRedBlocks = 1024, kRedThreads = 256;
+constexpr int kRedBlocks = 2048, kRedThreads = 256;
+constexpr int kEnRows = 16;                  // rows a workgroup of the energy sum marches
 
 // Node code bits: e edge PEC or absent; HK = no h_phi / h_r at this k (k = nz).
 enum { C_EPHI = 1, C_ER = 2, C_EZ = 4, C_HK = 8, C_ALL = 15 };
@@ -49,6 +51,7 @@ struct Coef {
 // kappa and mu of one radius (FP64, for the energy and set-up).
 struct Raw {
     double kp, kr, kz, mp, mr, mz;
+    double ikp, ikr, ikz, imp, imr, imz;   // reciprocals, 0 of 0
 };
 
 template <typename R>
@@ -373,12 +376,31 @@ __global__ void k_rz_sanitize(R* const* f, const uint8_t* code, const Raw* raw, 
     }
 }
 
-template <typename D, typename S>
-__global__ void k_rz_convert(D* dst, const S* src, int64_t n)
-{
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        dst[i] = (D)src[i];
-}
+// Entries kept by tete_rz_set_fields, by the same rules (kappa is zero on the
+// axis for e_phi and, for m >= 1, e_z; elsewhere only on edges the codes mark).
+struct KeepRZ {
+    const uint8_t* code;
+    int nr, nz, axis_ez;
+    __device__ __forceinline__ void operator()(int64_t e, uint32_t (&m)[4]) const
+    {
+        const uint32_t sz = (uint32_t)nz + 1u;
+        int j = (int)((uint32_t)e / sz), k = (int)((uint32_t)e - (uint32_t)j * sz);
+        const uint32_t cw = *(const uint32_t*)(code + e);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            uint32_t b = ~(cw >> (8 * u)) & 7u;
+            if (j == 0) b &= axis_ez ? 6u : 2u;
+            if (j < nr && k < nz) b |= 8u;
+            if (j > 0 && k < nz) b |= 16u;
+            if (j < nr) b |= 32u;
+            m[u] = b;
+            if (++k > nz) {
+                k = 0;
+                ++j;
+            }
+        }
+    }
+};
 
 __device__ double block_sum(double v)
 {
@@ -396,41 +418,59 @@ __device__ double block_sum(double v)
 //   1/2 [sum h^2/mu + sum_{kappa>0} e^2/kappa]
 //   - a^2/2 [sum_{h_phi} mu_phi (P_r e_z)^2 + sum_{e_phi, kappa>0} kappa_phi (P_r^T h_z)^2]
 //   + a [sum_{h_phi} h_phi P_z e_r - sum_{h_r} h_r P_z e_phi]
+//
+// A work item is kRedThreads consecutive k over kEnRows rows, marched along r:
+// e_z of the next row is loaded ahead and h_z of the row before kept, the
+// coefficients and their reciprocals of a row are scalar loads, and no index is
+// divided per entry.  HBM bounds it (1000 x 18183, FP32: 294 -> 121 us
+// against a grid-stride sum with divisions, 3.8 TB/s).
 template <typename R>
-__global__ __launch_bounds__(kRedThreads) void k_rz_energy(const R* const* f, const uint8_t* code, const Raw* raw,
-                                                         int nr, int nz, double a, double* partial)
+__global__ __launch_bounds__(kRedThreads) void k_rz_energy(Six<const R> f, const uint8_t* code, const Raw* rawp,
+                                                         int nr, int nz, int nzb, int items, double a, double* partial)
 {
-    const R *ep = f[0], *er = f[1], *ez = f[2], *hp = f[3], *hr = f[4], *hz = f[5];
+    typedef const __attribute__((address_space(4))) Raw* CRaw;
+    const CRaw raw = (CRaw)(const void*)rawp;
+    const R *ep = f.c[0], *er = f.c[1], *ez = f.c[2], *hp = f.c[3], *hr = f.c[4], *hz = f.c[5];
     const int sz = nz + 1;
-    const int64_t np = (int64_t)(nr + 1) * sz;
     double acc = 0.0;
-    for (int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; idx < np;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const int j = (int)(idx / sz), k = (int)(idx % sz);
-        const uint32_t c = code[idx];
-        const Raw w = raw[j];
-        double sq = 0.0, r = 0.0, lc = 0.0;
-        const double kp = (c & C_EPHI) ? 0.0 : w.kp, kr = (c & C_ER) ? 0.0 : w.kr, kz = (c & C_EZ) ? 0.0 : w.kz;
-        if (kp > 0.0) {
-            const double e = ep[idx], d = (j > 0 ? (double)hz[idx - sz] : 0.0) - (double)hz[idx];
-            sq += e * e / kp;
-            r += kp * d * d;
+    for (int it = blockIdx.x; it < items; it += gridDim.x) {
+        const int k = it % nzb * kRedThreads + (int)threadIdx.x;
+        const int ja = it / nzb * kEnRows, jb = min(ja + kEnRows, nr + 1);
+        if (k > nz) continue;
+        const int kn = k < nz ? 1 : 0;                    // the k-neighbour, or the entry itself
+        int64_t idx = (int64_t)ja * sz + k;
+        double hzm = ja > 0 ? (double)hz[idx - sz] : 0.0, ez0 = (double)ez[idx];
+        for (int j = ja; j < jb; ++j, idx += sz) {
+            const uint32_t c = code[idx];
+            const double epv = ep[idx], erv = er[idx], hpv = hp[idx], hrv = hr[idx], hzv = hz[idx];
+            const double epn = ep[idx + kn], ern = er[idx + kn];
+            const double ezn = j < nr ? (double)ez[idx + sz] : 0.0;
+            const CRaw w = raw + j;
+            double sq = 0.0, r = 0.0, lc = 0.0;
+            const double d = hzm - hzv;
+            if (!(c & C_EPHI)) {
+                sq += epv * epv * w->ikp;
+                r += w->kp * d * d;
+            }
+            if (!(c & C_ER)) sq += erv * erv * w->ikr;
+            if (!(c & C_EZ)) sq += ez0 * ez0 * w->ikz;
+            if (kn) {
+                const double de = ezn - ez0;
+                if (j < nr) {
+                    sq += hpv * hpv * w->imp;
+                    r += w->mp * de * de;
+                    lc += hpv * (ern - erv);
+                }
+                if (j > 0) {
+                    sq += hrv * hrv * w->imr;
+                    lc -= hrv * (epn - epv);
+                }
+            }
+            if (j < nr) sq += hzv * hzv * w->imz;
+            acc += 0.5 * sq - 0.5 * a * a * r + a * lc;
+            hzm = hzv;
+            ez0 = ezn;
         }
-        if (kr > 0.0) sq += (double)er[idx] * (double)er[idx] / kr;
-        if (kz > 0.0) sq += (double)ez[idx] * (double)ez[idx] / kz;
-        if (j < nr && k < nz && w.mp > 0.0) {
-            const double h = hp[idx], d = (double)ez[idx + sz] - (double)ez[idx];
-            sq += h * h / w.mp;
-            r += w.mp * d * d;
-            lc += h * ((double)er[idx + 1] - (double)er[idx]);
-        }
-        if (j > 0 && k < nz && w.mr > 0.0) {
-            const double h = hr[idx];
-            sq += h * h / w.mr;
-            lc -= h * ((double)ep[idx + 1] - (double)ep[idx]);
-        }
-        if (j < nr && w.mz > 0.0) sq += (double)hz[idx] * (double)hz[idx] / w.mz;
-        acc += 0.5 * sq - 0.5 * a * a * r + a * lc;
     }
     const double s = block_sum(acc);
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
@@ -650,7 +690,7 @@ void rz_raw(const tete_rz_desc* d, std::vector<Raw>& raw)
 {
     const int nr = d->nr;
     const double dr = d->dr, dz = d->dz;
-    raw.assign(nr + 1, Raw{0, 0, 0, 0, 0, 0});
+    raw.assign(nr + 1, Raw{});
     for (int j = 0; j <= nr; ++j) {
         const double r = j * dr, rh = (j + 0.5) * dr;
         Raw& w = raw[j];
@@ -660,6 +700,13 @@ void rz_raw(const tete_rz_desc* d, std::vector<Raw>& raw)
         w.mp = j < nr ? rh / (dr * dz) : 0.0;
         w.mr = j > 0 ? dr / (r * dz) : 0.0;
         w.mz = j < nr ? dz / (rh * dr) : 0.0;
+        auto inv = [](double v) { return v > 0.0 ? 1.0 / v : 0.0; };
+        w.ikp = inv(w.kp);
+        w.ikr = inv(w.kr);
+        w.ikz = inv(w.kz);
+        w.imp = inv(w.mp);
+        w.imr = inv(w.mr);
+        w.imz = inv(w.mz);
     }
 }
 
@@ -908,19 +955,17 @@ tete_status tete_rz_set_fields(tete_rz* g, const void* const f[6], int32_t dtype
     Guard dg(g->device);
     if (!dg.ok) return TETE_ERR_DEVICE;
     const int64_t np = (int64_t)(g->d.nr + 1) * (g->d.nz + 1);
-    for (int c = 0; c < 6; ++c) {
-        void* dst = g->f[g->cur][c];
-        if (g->fp32 && dtype == TETE_FP32)
-            k_rz_convert<float, float><<<512, 256, 0, g->stream>>>((float*)dst, (const float*)f[c], np);
-        else if (g->fp32)
-            k_rz_convert<float, double><<<512, 256, 0, g->stream>>>((float*)dst, (const double*)f[c], np);
-        else if (dtype == TETE_FP32)
-            k_rz_convert<double, float><<<512, 256, 0, g->stream>>>((double*)dst, (const float*)f[c], np);
-        else
-            k_rz_convert<double, double><<<512, 256, 0, g->stream>>>((double*)dst, (const double*)f[c], np);
-        RZCHK(hipGetLastError());
-    }
-    RZCHK(rz_sanitize_any(g, g->cur));
+    const KeepRZ keep = {g->code, g->d.nr, g->d.nz, g->d.mode == 0};
+    auto run = [&](auto tag) {
+        typedef decltype(tag) R;
+        Six<R> dst;
+        for (int c = 0; c < 6; ++c) dst.c[c] = (R*)g->f[g->cur][c];
+        if (dtype == TETE_FP32) run_import6<R, float>(dst, f, np, keep, g->stream);
+        else run_import6<R, double>(dst, f, np, keep, g->stream);
+    };
+    if (g->fp32) run(float(0));
+    else run(double(0));
+    RZCHK(hipGetLastError());
     RZCHK(hipMemsetAsync(g->acc, 0, sizeof(double) * 2 * kSteps * TETE_MAX_WAKE, g->stream));
     g->n = 0;
     g->kend = 0;
@@ -935,18 +980,16 @@ tete_status tete_rz_get_fields(tete_rz* g, void* const f[6], int32_t dtype)
     Guard dg(g->device);
     if (!dg.ok) return TETE_ERR_DEVICE;
     const int64_t np = (int64_t)(g->d.nr + 1) * (g->d.nz + 1);
-    for (int c = 0; c < 6; ++c) {
-        const void* src = g->f[g->cur][c];
-        if (g->fp32 && dtype == TETE_FP32)
-            k_rz_convert<float, float><<<512, 256, 0, g->stream>>>((float*)f[c], (const float*)src, np);
-        else if (g->fp32)
-            k_rz_convert<double, float><<<512, 256, 0, g->stream>>>((double*)f[c], (const float*)src, np);
-        else if (dtype == TETE_FP32)
-            k_rz_convert<float, double><<<512, 256, 0, g->stream>>>((float*)f[c], (const double*)src, np);
-        else
-            k_rz_convert<double, double><<<512, 256, 0, g->stream>>>((double*)f[c], (const double*)src, np);
-        RZCHK(hipGetLastError());
-    }
+    auto run = [&](auto tag) {
+        typedef decltype(tag) R;
+        Six<const R> src;
+        for (int c = 0; c < 6; ++c) src.c[c] = (const R*)g->f[g->cur][c];
+        if (dtype == TETE_FP32) run_export6<float, R>(f, src, np, g->stream);
+        else run_export6<double, R>(f, src, np, g->stream);
+    };
+    if (g->fp32) run(float(0));
+    else run(double(0));
+    RZCHK(hipGetLastError());
     RZCHK(hipStreamSynchronize(g->stream));
     return TETE_OK;
 }
@@ -1086,14 +1129,19 @@ tete_status tete_rz_energy(tete_rz* g, double* W, int64_t* n)
     Guard dg(g->device);
     if (!dg.ok) return TETE_ERR_DEVICE;
     const double a = 0.5 * g->d.cdt;
-    if (g->fp32)
-        k_rz_energy<float><<<kRedBlocks, kRedThreads, 0, g->stream>>>(
-            (const float* const*)(g->dptr + 6 * g->cur), g->code, g->raw, g->d.nr, g->d.nz, a, g->partial);
-    else
-        k_rz_energy<double><<<kRedBlocks, kRedThreads, 0, g->stream>>>(
-            (const double* const*)(g->dptr + 6 * g->cur), g->code, g->raw, g->d.nr, g->d.nz, a, g->partial);
+    const int nzb = (g->d.nz + kRedThreads) / kRedThreads, items = nzb * ((g->d.nr + kEnRows) / kEnRows);
+    const int grid = std::min(items, (int)kRedBlocks);
+    auto run = [&](auto tag) {
+        typedef decltype(tag) R;
+        Six<const R> f;
+        for (int c = 0; c < 6; ++c) f.c[c] = (const R*)g->f[g->cur][c];
+        k_rz_energy<R><<<grid, kRedThreads, 0, g->stream>>>(f, g->code, g->raw, g->d.nr, g->d.nz, nzb, items, a,
+                                                            g->partial);
+    };
+    if (g->fp32) run(float(0));
+    else run(double(0));
     RZCHK(hipGetLastError());
-    k_rz_finish<<<1, kRedThreads, 0, g->stream>>>(g->partial, kRedBlocks, g->scal);
+    k_rz_finish<<<1, kRedThreads, 0, g->stream>>>(g->partial, grid, g->scal);
     RZCHK(hipGetLastError());
     RZCHK(hipMemcpyAsync(W, g->scal, sizeof(double), hipMemcpyDeviceToHost, g->stream));
     RZCHK(hipStreamSynchronize(g->stream));
