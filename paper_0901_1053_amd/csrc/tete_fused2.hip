@@ -21,11 +21,23 @@
 // (S4, S5) from two iterations back and e_z (S3) from three; delay lines in
 // LDS (one slot per thread) hold the older ones.
 //
-// Register budget.  Two stages of carried state fill the 128 VGPRs a
+// Register budget.  Two stages of carried state nearly fill the 128 VGPRs a
 // 1024-thread workgroup allows, so the coefficients are pre-multiplied by
 // their factor a or 2a, PEC selects are two bit operations, the delay lines
-// live in LDS and one plane is prefetched (a second one spills 23 registers).
+// live in LDS and one plane is prefetched (a second one spills 13 registers).
 // The FP64 shape (512 threads, 256 VGPRs per wave) prefetches two.
+//
+// Vector instructions.  One plane costs 72 subtractions and multiply-adds, 8
+// lane shifts and 20 for the PEC selects per wave; with 16 waves these alone
+// take 0.7 us, so the march spends next to none on anything else: plane
+// addresses are scalar (a buffer resource per access), stores are predicated by
+// the resource's range, LDS slots are immediate offsets, the loop is unrolled
+// by four or six planes so that the carried values keep their registers, and
+// only a tile that holds the source row tests for it.  112 instructions per
+// plane against 175 before; us per step 509 -> 426 (256 x 256 x 1024 FP32), 3724
+// -> 3372 (512 x 512 x 2048 FP32), 290 -> 274 (256 x 256 x 512 FP32 by class), 447
+// -> 432 (256 x 256 x 512 FP64), 831 -> 657 (256 x 256 x 1024 FP32, energies of
+// every second step).
 //
 // Wake.  The update of sample s at step n+1 from edge k and the update of the
 // same sample at step n from edge k-1 coincide.  The lane of node k applies
@@ -91,7 +103,7 @@ struct Out {
 // One iteration of a stage: the ten sub-updates at their lags, then the
 // rotation of the carried state by one plane.  inj is the bunch current term
 // taken off e_z^{n+1/2} (zero off the source line; x - 0 is exact).
-template <typename R>
+template <bool SRC, typename R>
 __device__ __forceinline__ Out<R> stage_plane(Stage<R>& S, const In<R>& c, const Nb<R>& nb, const Co<R>& f,
                                               const R inj)
 {
@@ -103,7 +115,7 @@ __device__ __forceinline__ Out<R> stage_plane(Stage<R>& S, const In<R>& c, const
     const R hyn_m1 = S.HYm1 + f.my1 * (-pzEXm1 + (c.ez - S.EZm1));
     // S3 at q-1: e_z^{n+1/2} = e_z^{n-1/2} + 2a kappa_z [P_y^T h_x^n - P_x^T h_y^n - j_z^n]
     R ezh_m1 = S.EZm1 + f.kz1 * ((nb.hxn1_jm - S.hxn_m1) - (S.hyn_m2 - hyn_m1));
-    {
+    if constexpr (SRC) {
 #pragma clang fp contract(off)
         ezh_m1 -= inj;
     }
@@ -151,9 +163,8 @@ __device__ __forceinline__ Out<R> stage_plane(Stage<R>& S, const In<R>& c, const
 // With materials by class (TAB) the class table is staged here too.
 template <typename R, int TYH, int NB, int LW, bool TAB = false>
 struct Lds2 {
-    R a[6][NB][TYH + 2][LW];
-    R b[6][NB][TYH + 2][LW];
     R d[3][2][LW * TYH];
+    R x[12][NB][TYH + 2][LW];
     R tab[TAB ? TETE_MAX_CLASSES * CLS_STRIDE : 1];
 };
 
@@ -266,49 +277,32 @@ __device__ __forceinline__ void fused2_tile(const FArgs<R>& A, const Tile& t, LD
     const bool src_wave = A.src.on && A.src.j0 >= wj0 && A.src.j0 < wj0 + 64 / LW;
     const bool src_k = kin && k < g.nz;                 // lane holds an e_z edge
 
-    // Buffer resources over the chunk's planes, as in the single-step kernel:
-    // loads cover planes pb = max(0, xs - 4) .. xload_end and out-of-range
-    // loads return 0.  The
-    // host keeps (xchunk + 8) planes below 2^31 bytes.
+    // Loads through buffer resources made per plane from scalar registers: the
+    // plane's address as the base and its bytes as the range (0 for a plane
+    // without old data), the entry's place in the plane as the offset, so that a
+    // load costs no vector instruction.  Out-of-range loads (lanes outside the
+    // grid, planes before pb = max(0, xs - 4) or past xload_end) return 0;
+    // out-of-range stores (entries not owned, planes outside the chunk) are
+    // dropped.
     constexpr uint32_t RB = sizeof(R);
     constexpr uint32_t OOB = 0x80000000u;
-    const uint32_t plane_bytes = (uint32_t)g.sp * RB;
+    const uint32_t plane_bytes = (uint32_t)g.sp * RB;   // below 2^31 (fused2_fits)
     const int pb = max(0, xs - 4);
-    const int nload = xload_end >= pb ? xload_end - pb + 1 : 0;
-    auto mk = [](const void* base, uint32_t bytes) {
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
+    auto mk = [](const void* base, int64_t off, uint32_t bytes) {
+        return __builtin_amdgcn_make_buffer_rsrc((char*)const_cast<void*>(base) + off, (short)0, (int)bytes, 0x00020000);
     };
-    const int64_t ld0 = (int64_t)pb * g.sp;
-    const auto rEX = mk(A.ex + ld0, nload * plane_bytes), rEY = mk(A.ey + ld0, nload * plane_bytes),
-               rEZ = mk(A.ez + ld0, nload * plane_bytes), rHX = mk(A.hx + ld0, nload * plane_bytes),
-               rHY = mk(A.hy + ld0, nload * plane_bytes), rHZ = mk(A.hz + ld0, nload * plane_bytes);
-    const auto rC = mk(A.code, (uint32_t)std::min<int64_t>((int64_t)g.np + 4, 0x7fffffff));
-    __amdgpu_buffer_rsrc_t rK = rC;
-    __amdgpu_buffer_rsrc_t rM[ARR ? 6 : 1];
-    if constexpr (ARR) {
-#pragma unroll
-        for (int c = 0; c < 6; ++c) rM[c] = mk(MA.m[c] + ld0, nload * plane_bytes);
-    }
+    auto xown = [&](int q) { return q >= xs && q < xe; };
     if constexpr (CLS) {
-        rK = mk(A.cls, (uint32_t)std::min<int64_t>((int64_t)g.np + 4, 0x7fffffff));
         // the class table into LDS; the barrier of the first j-exchange
         // orders these writes before any read
         for (int t = threadIdx.x; t < TETE_MAX_CLASSES * CLS_STRIDE; t += TYH * LW) L.tab[t] = A.ctab[t];
     }
-    // Stores are plain global stores: the chunk's first plane as a scalar base
-    // plus a 32-bit byte offset, predicated on the plane lying in the chunk
-    // (uniform) and the entry being owned; this keeps six buffer resources
-    // (24 scalar registers) free.
-    const int64_t st0 = (int64_t)xs * g.sp;
-    char* const gEX = (char*)(A.ex1 + st0);
-    char* const gEY = (char*)(A.ey1 + st0);
-    char* const gEZ = (char*)(A.ez1 + st0);
-    char* const gHX = (char*)(A.hx1 + st0);
-    char* const gHY = (char*)(A.hy1 + st0);
-    char* const gHZ = (char*)(A.hz1 + st0);
     const uint32_t in_ld = (uint32_t)roff * RB;
-    auto gstore = [](char* base, uint32_t off, R v) { *(R*)(base + off) = v; };
-    auto xown = [&](int q) { return q >= xs && q < xe; };
+    const uint32_t vld = node ? in_ld : OOB, vcode = node ? (uint32_t)roff : OOB, vst = owned ? in_ld : OOB;
+    auto st = [&](R* base, int q, R v) {
+        bstore(mk(base, (int64_t)q * plane_bytes, xown(q) ? plane_bytes : 0u), vst, v);
+    };
+    auto has_old = [&](int q) { return q >= pb && q <= xload_end; };
     const uint32_t cfix = node ? 0u : 7u;              // outside the grid: PEC
 
     struct PR {
@@ -318,26 +312,23 @@ __device__ __forceinline__ void fused2_tile(const FArgs<R>& A, const Tile& t, LD
         R m[ARR ? 6 : 0];
     };
     auto load_plane = [&](int i, PR& d) {
-        const uint32_t po = (uint32_t)(i - pb);
-        const uint32_t off = node ? in_ld + po * plane_bytes : OOB;
-        d.ex = bload<R>(rEX, off);
-        d.ey = bload<R>(rEY, off);
-        d.ez = bload<R>(rEZ, off);
-        d.hx = bload<R>(rHX, off);
-        d.hy = bload<R>(rHY, off);
-        d.hz = bload<R>(rHZ, off);
+        const bool pv = has_old(i);
+        const uint32_t nb = pv ? plane_bytes : 0u, nc = pv ? (uint32_t)g.sp : 0u;
+        const int64_t po = (int64_t)i * plane_bytes, pc = (int64_t)i * g.sp;
+        d.ex = bload<R>(mk(A.ex, po, nb), vld);
+        d.ey = bload<R>(mk(A.ey, po, nb), vld);
+        d.ez = bload<R>(mk(A.ez, po, nb), vld);
+        d.hx = bload<R>(mk(A.hx, po, nb), vld);
+        d.hy = bload<R>(mk(A.hy, po, nb), vld);
+        d.hz = bload<R>(mk(A.hz, po, nb), vld);
         if constexpr (ARR) {
 #pragma unroll
-            for (int c = 0; c < 6; ++c) d.m[c] = bload<R>(rM[c], off);
+            for (int c = 0; c < 6; ++c) d.m[c] = bload<R>(mk(MA.m[c], po, nb), vld);
             d.c = 0u;
         } else {
-            const uint32_t offc = node ? ((uint32_t)(roff + i * g.sp) & ~3u) : OOB;
-            d.c = __builtin_amdgcn_raw_buffer_load_b32(rC, offc, 0, 0);   // byte extracted when used
+            d.c = __builtin_amdgcn_raw_buffer_load_b8(mk(A.code, pc, nc), vcode, 0, 0);
         }
-        if constexpr (CLS) {
-            const uint32_t offc = node ? ((uint32_t)(roff + i * g.sp) & ~3u) : OOB;
-            d.k[0] = __builtin_amdgcn_raw_buffer_load_b32(rK, offc, 0, 0);
-        }
+        if constexpr (CLS) d.k[0] = __builtin_amdgcn_raw_buffer_load_b8(mk(A.cls, pc, nc), vcode, 0, 0);
     };
 
     Stage<R> SA = {}, SB = {};
@@ -349,7 +340,22 @@ __device__ __forceinline__ void fused2_tile(const FArgs<R>& A, const Tile& t, LD
     R hKX[ARR ? 9 : 1] = {}, hKY[ARR ? 8 : 1] = {}, hKZ[ARR ? 6 : 1] = {}, hMX[ARR ? 7 : 1] = {},
       hMY[ARR ? 7 : 1] = {}, hMZ[ARR ? 8 : 1] = {};
     const int tid = threadIdx.x;
-    for (int q = 0; q < 3; ++q) L.d[q][0][tid] = L.d[q][1][tid] = R(0);   // stage B's delay lines
+    // LDS through two bases 64 KiB apart, so that every slot of the thread is an
+    // immediate offset from one of them.  Delay-line slot of quantity q and
+    // parity s; exchange slot of quantity q (stage B's from 6 on), parity s, row
+    // jl + r.
+    typedef __attribute__((address_space(3))) R* LP;
+    LP lp0 = (LP)&L.d[0][0][0] + tid, lp1 = lp0 + 65536 / sizeof(R);
+    asm("" : "+v"(lp0));
+    asm("" : "+v"(lp1));
+    auto slot = [&](int off) -> LP {
+        return off * (int)sizeof(R) < 65536 ? lp0 + off : lp1 + (off - 65536 / (int)sizeof(R));
+    };
+    auto dl = [&](int q, int s) -> LP { return slot((2 * q + s) * (LW * TYH)); };
+    auto ex = [&](int q, int s, int r) -> LP {
+        return slot(6 * LW * TYH + ((NB * q + (NB == 2 ? s : 0)) * (TYH + 2) + r) * LW);
+    };
+    for (int q = 0; q < 3; ++q) *dl(q, 0) = *dl(q, 1) = R(0);   // stage B's delay lines
     R d_ey4 = 0;                 // e_y^{n+1} of plane p-4
     uint32_t ch = 0x77777777u;   // PEC codes of planes p-1 .. p-8, four bits each
     R ezA = 0;                   // e_z^{n-1/2} of edge k on the source plane
@@ -358,9 +364,11 @@ __device__ __forceinline__ void fused2_tile(const FArgs<R>& A, const Tile& t, LD
     // h component in j and k, a kappa and 2a kappa
     const R amx = hx_jk ? A.a * A.mx : R(0), amy = hy_k ? A.a * A.my : R(0), a2mz = hz_j ? a2 * A.mz : R(0);
     const R akx = A.a * A.kx, aky = A.a * A.ky, a2kz = a2 * A.kz;
-    // v, or 0 where bit b of the code history is set (a PEC edge)
+    // v, or 0 where bit b of the code history is set (a PEC edge): two vector
+    // instructions (written as shifts, the mask becomes a compare and a select)
     auto sel = [](uint32_t hist, int b, R v) {
-        const uint32_t m = (uint32_t)(((int32_t)(hist << (31 - b))) >> 31);
+        uint32_t m;
+        asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(m) : "v"(hist), "n"(b));
         if constexpr (sizeof(R) == 4) {
             return __builtin_bit_cast(R, __builtin_bit_cast(uint32_t, v) & ~m);
         } else {
@@ -500,15 +508,15 @@ __device__ __forceinline__ void fused2_tile(const FArgs<R>& A, const Tile& t, LD
     };
 
     const int pend = xe + 7;
-    auto body = [&](const int p, const PR& cur, PR& nxt) {
+    auto body = [&](auto src_tile, const int p, const int s, const PR& cur, PR& nxt) {
+        constexpr bool SRC = decltype(src_tile)::value;
         load_plane(p + PD, nxt);
         // outside the grid, or a plane without old data: PEC on all edges
-        const uint32_t bsh = ((uint32_t)(roff + p * g.sp) & 3u) * 8u;
-        const uint32_t c0 = ((cur.c >> bsh) & 7u) | cfix | ((p >= pb && p <= xload_end) ? 0u : 7u);
+        const uint32_t c0 = (cur.c & 7u) | cfix | (has_old(p) ? 0u : 7u);
         if constexpr (CLS) {
             kh2 = kh1 >> 24;
             kh1 = (kh1 << 8) | (kh0 >> 24);
-            kh0 = (kh0 << 8) | ((cur.k[0] >> bsh) & 0xffu);
+            kh0 = (kh0 << 8) | cur.k[0];
         }
         if constexpr (ARR) {
             hKX[0] = cur.m[0]; hKY[0] = cur.m[1]; hKZ[0] = cur.m[2];
@@ -518,30 +526,26 @@ __device__ __forceinline__ void fused2_tile(const FArgs<R>& A, const Tile& t, LD
         // stage B's input plane p-4, except e_x (stage A's S9 of this
         // iteration); the delay-line slot of this parity holds plane p-4 and
         // is refilled with plane p-2
-        const int s = p & 1;
-        const R bEY = d_ey4, bEZ = L.d[0][s][tid], bHX = L.d[1][s][tid], bHY = L.d[2][s][tid], bHZ = SA.hzn_m4;
-        L.d[0][s][tid] = SA.ezh_m2;
+        const R bEY = d_ey4, bEZ = *dl(0, s), bHX = *dl(1, s), bHY = *dl(2, s), bHZ = SA.hzn_m4;
+        *dl(0, s) = SA.ezh_m2;
 
         // j-exchange through LDS (row r of the tile is LDS row r+1; rows 0 and
         // TYH+1 are never written and reach only halo results)
-        const int x = NB == 2 ? s : 0;   // exchange buffer
-        L.a[0][x][jl + 1][kl] = cur.ez;
-        L.a[1][x][jl + 1][kl] = SA.hxn_m1;
-        L.a[2][x][jl + 1][kl] = SA.ezh_m2;
-        L.a[3][x][jl + 1][kl] = SA.HZm2;
-        L.a[4][x][jl + 1][kl] = SA.exh_m3;
-        L.a[5][x][jl + 1][kl] = SA.hzn_m4;
-        L.b[0][x][jl + 1][kl] = bEZ;
-        L.b[1][x][jl + 1][kl] = SB.hxn_m1;
-        L.b[2][x][jl + 1][kl] = SB.ezh_m2;
-        L.b[3][x][jl + 1][kl] = SB.HZm2;
-        L.b[4][x][jl + 1][kl] = SB.exh_m3;
-        L.b[5][x][jl + 1][kl] = SB.hzn_m4;
+        *ex(0, s, 1) = cur.ez;
+        *ex(1, s, 1) = SA.hxn_m1;
+        *ex(2, s, 1) = SA.ezh_m2;
+        *ex(3, s, 1) = SA.HZm2;
+        *ex(4, s, 1) = SA.exh_m3;
+        *ex(5, s, 1) = SA.hzn_m4;
+        *ex(6, s, 1) = bEZ;
+        *ex(7, s, 1) = SB.hxn_m1;
+        *ex(8, s, 1) = SB.ezh_m2;
+        *ex(9, s, 1) = SB.HZm2;
+        *ex(10, s, 1) = SB.exh_m3;
+        *ex(11, s, 1) = SB.hzn_m4;
         __syncthreads();
-        const Nb<R> nA = {L.a[0][x][jl + 2][kl], L.a[1][x][jl][kl], L.a[2][x][jl + 2][kl],
-                          L.a[3][x][jl][kl],     L.a[4][x][jl + 2][kl], L.a[5][x][jl][kl]};
-        const Nb<R> nB = {L.b[0][x][jl + 2][kl], L.b[1][x][jl][kl], L.b[2][x][jl + 2][kl],
-                          L.b[3][x][jl][kl],     L.b[4][x][jl + 2][kl], L.b[5][x][jl][kl]};
+        const Nb<R> nA = {*ex(0, s, 2), *ex(1, s, 0), *ex(2, s, 2), *ex(3, s, 0), *ex(4, s, 2), *ex(5, s, 0)};
+        const Nb<R> nB = {*ex(6, s, 2), *ex(7, s, 0), *ex(8, s, 2), *ex(9, s, 0), *ex(10, s, 2), *ex(11, s, 0)};
         if (NB == 1) __syncthreads();    // all reads done before the next plane's writes
 
         Co<R> fA, fB;
@@ -556,16 +560,18 @@ __device__ __forceinline__ void fused2_tile(const FArgs<R>& A, const Tile& t, LD
             fB = coef(p - 4, ch >> 16);
         }
         // S3 of stage A is at plane p-1 (step n), of stage B at plane p-5 (step n+1)
-        const bool srcA = src_row && p - 1 == A.src.i0;
-        const bool srcB = src_row && p - 5 == A.src.i0;
-        const bool srcBw = LW == 64 ? srcB : src_wave && p - 5 == A.src.i0;   // wave-uniform
+        const bool srcA = SRC && src_row && p - 1 == A.src.i0;
+        const bool srcB = SRC && src_row && p - 5 == A.src.i0;
+        const bool srcBw = LW == 64 ? srcB : SRC && src_wave && p - 5 == A.src.i0;   // wave-uniform
         R kzA = A.kz, kzB = A.kz;
-        if constexpr (CLS) {
+        if constexpr (CLS && SRC) {
             kzA = tab(cbyte(kh0, 1), CLS_KZ);
             kzB = tab(cbyte(kh1, 1), CLS_KZ);
         }
-        R injA, injB;
-        if constexpr (ARR) {      // the arrays hold kappa_z = 0 on PEC edges
+        R injA = 0, injB = 0;
+        if constexpr (!SRC) {
+            (void)kzA, (void)kzB;
+        } else if constexpr (ARR) {      // the arrays hold kappa_z = 0 on PEC edges
             injA = (srcA && src_k) ? inject(A.src.n, hKZ[1]) : R(0);
             injB = (srcB && src_k) ? inject(A.src.n + 1, hKZ[5]) : R(0);
         } else {
@@ -577,13 +583,13 @@ __device__ __forceinline__ void fused2_tile(const FArgs<R>& A, const Tile& t, LD
             if (eo.want & 1)
                 accA += en_terms(In<R>{cur.ex, cur.ey, cur.ez, cur.hx, cur.hy, cur.hz}, SA, nA, c0, ch, p, kh0);
         }
-        const Out<R> oA = stage_plane(SA, In<R>{cur.ex, cur.ey, cur.ez, cur.hx, cur.hy, cur.hz}, nA, fA, injA);
+        const Out<R> oA = stage_plane<SRC>(SA, In<R>{cur.ex, cur.ey, cur.ez, cur.hx, cur.hy, cur.hz}, nA, fA, injA);
         if constexpr (EN) {      // y^{n+1}: stage B's input at plane p-4 (its e_x is stage A's S9 above)
             if (eo.want & 2)
                 accB += en_terms(In<R>{oA.ex14, bEY, bEZ, bHX, bHY, bHZ}, SB, nB, (ch >> 12) & 7u, ch >> 16, p - 4,
                                  kh1);
         }
-        const Out<R> oB = stage_plane(SB, In<R>{oA.ex14, bEY, bEZ, bHX, bHY, bHZ}, nB, fB, injB);
+        const Out<R> oB = stage_plane<SRC>(SB, In<R>{oA.ex14, bEY, bEZ, bHX, bHY, bHZ}, nB, fB, injB);
 
         if (srcA) ezA = oA.ezold1;
         if constexpr (WIT) {
@@ -612,24 +618,15 @@ __device__ __forceinline__ void fused2_tile(const FArgs<R>& A, const Tile& t, LD
             }
         }
 
-        if (owned) {
-            const int q1 = p - 5;
-            const uint32_t o1 = in_ld + (uint32_t)(q1 - xs) * plane_bytes;
-            const uint32_t o2 = o1 - plane_bytes, o3 = o2 - plane_bytes, o4 = o3 - plane_bytes;
-            if (xown(q1)) gstore(gEZ, o1, oB.ezh1);
-            if (xown(q1 - 1)) {
-                gstore(gHX, o2, oB.hxh2);
-                gstore(gHY, o2, oB.hyh2);
-            }
-            if (xown(q1 - 2)) {
-                gstore(gHZ, o3, oB.hzn3);
-                gstore(gEY, o3, oB.ey13);
-            }
-            if (xown(q1 - 3)) gstore(gEX, o4, oB.ex14);
-        }
+        st(A.ez1, p - 5, oB.ezh1);
+        st(A.hx1, p - 6, oB.hxh2);
+        st(A.hy1, p - 6, oB.hyh2);
+        st(A.hz1, p - 7, oB.hzn3);
+        st(A.ey1, p - 7, oB.ey13);
+        st(A.ex1, p - 8, oB.ex14);
 
-        L.d[1][s][tid] = oA.hxh2;
-        L.d[2][s][tid] = oA.hyh2;
+        *dl(1, s) = oA.hxh2;
+        *dl(2, s) = oA.hyh2;
         d_ey4 = oA.ey13;
         ch = (ch << 4) | c0;
         if constexpr (ARR) {      // histories one plane older
@@ -644,11 +641,24 @@ __device__ __forceinline__ void fused2_tile(const FArgs<R>& A, const Tile& t, LD
         }
     };
 
-    // trip count rounded up to a multiple of PD+1, as in the single-step kernel
-    for (int p = xs - 4; p <= pend; p += PD + 1) {
+    // The march: unrolled so that the prefetch buffers, the LDS parity and most
+    // of the carried state keep their registers.  A workgroup whose tile does not
+    // hold the source row takes the march without the source.
+    constexpr int U = PD == 2 ? 6 : EN ? 2 : 4;
+    static_assert(U % 2 == 0 && U % (PD + 1) == 0, "whole turns of the parity and of the prefetch buffers");
+    auto march = [&](auto src_tile) {
+        int p = xs - 4;
+        for (;;) {
 #pragma unroll
-        for (int u = 0; u <= PD; ++u) body(p + u, buf[u], buf[(u + PD) % (PD + 1)]);
-    }
+            for (int u = 0; u < U; ++u) {
+                body(src_tile, p, u & 1, buf[u % (PD + 1)], buf[(u + PD) % (PD + 1)]);
+                if (p++ == pend) return;
+            }
+        }
+    };
+    const int srow = A.src.j0 - (t.ty * TY - 3);
+    if (A.src.on && srow >= 0 && srow < TYH) march(std::true_type{});
+    else march(std::false_type{});
     if constexpr (EN) {
         // the workgroup's two sums: waves by shuffles, then the waves in order
         constexpr int NW = TYH * LW / 64;
@@ -909,7 +919,7 @@ bool fused2_setup(FArgs<R>& A, int rows, int xchunk, int order, int lanes, bool 
     const int64_t xmax = ((int64_t(1) << 31) - 1) / plane_bytes - 8;
     if (xmax < 1) return false;
     // planes xs-4 .. xe+7, of which the first and the last few are cheaper
-    set_chunks(A, xchunk, order, xmax, 10, KT2 == 28 ? 3 : 2, member);
+    set_chunks(A, xchunk, order, xmax, 10, 1, member);
     return true;
 }
 

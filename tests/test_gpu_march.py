@@ -1,0 +1,47 @@
+"""The two-step kernel's march along x: chunk lengths that end it at every place
+of its unrolled loop, tiles with and without the source row, against the
+single-step kernel (materials by class: against one chunk), bitwise."""
+import numpy as np
+import pytest
+
+from paper_0901_1053_amd import inputs, tete
+
+pytestmark = pytest.mark.gpu
+
+DZ = 1e-3
+SHAPE = (25, 40, 70)
+
+
+def _fields(orc, precision, kernel, xchunk, rows, bunch_row, classes):
+    nx, ny, nz = SHAPE
+    cells = inputs.random_cells(nx, ny, nz, 61)
+    G = tete.Grid(nx, ny, nz, 2 * DZ, 2 * DZ, DZ, DZ, precision=precision, materials=classes)
+    G.set_pec_cells(cells)
+    if classes:
+        g = orc.Geom(nx, ny, nz, 2 * DZ, 2 * DZ, DZ, DZ)
+        vac = orc.vacuum_materials(g, cells)
+        rng = np.random.default_rng(62)
+        table = np.array([[vac[k].max() for k in inputs.KEYS]] * 4) * rng.uniform(0.6, 1.0, size=(4, 6))
+        G.set_material_classes(rng.integers(0, 4, size=g.shape).astype(np.uint8), table)
+    G.set_fields(inputs.random_fields(G.shape, 63))
+    G.set_bunch(1e-9, 2.0 * DZ, nx // 2, bunch_row, 12, -90, 120)
+    G.set_tuning(kernel, rows, xchunk, 0, 0)
+    G.step(4)
+    out = G.get_fields()
+    out["wake"] = G.wake()
+    G.close()
+    return out
+
+
+@pytest.mark.parametrize("precision,rows,classes", [("fp32", 16, False), ("fp32", 24, False), ("fp32", 32, False),
+                                                    ("fp32", 0, True), ("fp64", 16, False), ("fp64", 0, True)])
+def test_every_end_of_the_march(orc, precision, rows, classes):
+    # bunch in the first rows, at the edge of two 16-row tiles, in a later tile
+    for bunch_row in (2, 9, 33):
+        base = _fields(orc, precision, "fused2" if classes else "fused", 10 ** 6, 0, bunch_row, classes)
+        for xchunk in (1, 2, 3, 4, 5, 6, 13, 26):
+            print("march", precision, rows, bunch_row, xchunk, flush=True)
+            got = _fields(orc, precision, "fused2", xchunk, rows, bunch_row, classes)
+            for k in base:
+                assert np.array_equal(got[k], base[k]), (bunch_row, xchunk, k)
+        assert np.any(base["wake"] != 0)
