@@ -366,7 +366,7 @@ tete_status do_steps(tete_grid* g, int64_t nsteps)
     // launches of at most EN_PARTS workgroups
     int64_t en_blocks = 0;
     const bool en_fuse = two && g->diag_every > 0 && (!g->mat_set || g->mat_cls) && !g->skip &&
-                         (en_blocks = fused2_blocks<R>(g->geo, fused_xchunk(g), g->tune.order)) > 0 &&
+                         (en_blocks = fused2_blocks<R>(g->geo, fused_xchunk(g), g->tune.order, g->mat_cls != 0)) > 0 &&
                          en_blocks <= EN_PARTS;
     for (int64_t s = 0; s < nsteps; ++s) {
         const bool at_n = g->diag_every > 0 && g->n % g->diag_every == 0;

@@ -185,6 +185,14 @@ struct Shape2 {
 template <typename R> struct Default2;
 template <> struct Default2<float> { static constexpr int rows = 16, lw = 64, pd = 1; };
 template <> struct Default2<double> { static constexpr int rows = 16, lw = 32, pd = 2; };
+// Rows (of 32 lanes) of the instance that takes energy samples.  The sums'
+// operands do not fit 128 VGPRs; in FP32 with vacuum coefficients they fit the
+// 168 of 24 rows, two planes ahead (with witness lines 4 spill; one plane ahead
+// took 571 us per step).  Three waves per SIMD and 504 owned of 768 entries
+// against two and 280 of 512 with 16 rows: 657 -> 544 us per step on 256 x 256 x
+// 1024 with a sample every second step.  Materials by class need 201, FP64 231.
+constexpr int kEnRows32 = 24;
+inline int en_rows(int real_bytes, bool cls) { return real_bytes == 4 && !cls ? kEnRows32 : 16; }
 inline int lanes2(int real_bytes, int rows) { return real_bytes == 8 || rows == 24 || rows == 32 ? 32 : 64; }
 
 // Two steps of one work item (tile and x-chunk).  Every thread of the
@@ -711,8 +719,8 @@ __global__ __launch_bounds__(TYH * LW) void k_fused2(FArgs<R> A, const int* act)
 }
 
 // The two-step kernel that also sums the energy of its input and of the
-// state between its two steps (16 rows of 32 lanes, vacuum coefficients, the
-// full tiling: one pair of partial sums per workgroup, zero for the padding
+// state between its two steps (vacuum coefficients, the shape en_rows, the full
+// tiling: one pair of partial sums per workgroup, zero for the padding
 // workgroups of the blocked tile orders).
 template <typename R, int TYH, int LW, int PD>
 __global__ __launch_bounds__(TYH * LW) void k_fused2_en(FArgs<R> A, EnOut eo)
@@ -985,12 +993,12 @@ void run_fused2(const FArgs<R>& A, const int* act, int nact, hipStream_t s)
 }
 
 template <typename R>
-int64_t fused2_blocks(Geo g, int xchunk, int order)
+int64_t fused2_blocks(Geo g, int xchunk, int order, bool cls)
 {
     Fields<R> none = {};
     Mat<R> M = {};
     FArgs<R> A = fused_args<R>(none, none, M, g, R(0), Src{});
-    if (!fused2_setup<R>(A, 16, xchunk, order, 32)) return -1;
+    if (!fused2_setup<R>(A, en_rows(sizeof(R), cls), xchunk, order, 32)) return -1;
     return A.nblk;
 }
 
@@ -1000,26 +1008,25 @@ hipError_t launch_step_fused2(Fields<R> o, Fields<R> nf, Mat<R> M, Geo g, R alph
                               const int* act, int nact, const EnergyPair* en)
 {
     if (en && en->want) {
-        // energy samples: the default shape over the full tiling, vacuum
+        // energy samples: the shape en_rows over the full tiling
         FArgs<R> A = fused_args<R>(o, nf, M, g, alpha, src);
-        // 16 rows of 32 lanes: 512 threads, whose VGPRs hold the sums'
-        // operands (FP32 two planes ahead, FP64 one)
         // (materials by class: their energy coefficients from en->craw; witness
         // lines on vacuum grids only)
-        if (act || (M.arr[0] && !A.cls) || (A.cls && (!en->craw || wm)) || !fused2_setup<R>(A, 16, xchunk, order, 32))
+        if (act || (M.arr[0] && !A.cls) || (A.cls && (!en->craw || wm)) ||
+            !fused2_setup<R>(A, en_rows(sizeof(R), A.cls), xchunk, order, 32))
             return hipErrorInvalidValue;
         if (wm && (wm->iw < 1 || wm->iw > g.nx - 1 || wm->jw < 1 || wm->jw > g.ny - 1)) return hipErrorInvalidValue;
         if (A.nblk > en->cap) return hipErrorInvalidValue;
         hipError_t e;
         if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return e;
-        constexpr int EPD = sizeof(R) == 4 ? 2 : 1;   // FP64: one plane ahead fits the VGPRs
+        constexpr int ER = sizeof(R) == 4 ? kEnRows32 : 16;
         const EnOut eo = {en->part, en->want, en->alpha, en->craw, nullptr};
         if (A.cls) {
-            k_fused2_en_cls<R, 16, 32, EPD><<<A.nblk, 16 * 32, 0, s>>>(A, eo);
+            k_fused2_en_cls<R, 16, 32, sizeof(R) == 4 ? 2 : 1><<<A.nblk, 16 * 32, 0, s>>>(A, eo);
         } else if (wm) {
-            k_fused2_en_wit<R, 16, 32, EPD><<<A.nblk, 16 * 32, 0, s>>>(A, eo, *wm);
+            k_fused2_en_wit<R, ER, 32, sizeof(R) == 4 ? 2 : 1><<<A.nblk, ER * 32, 0, s>>>(A, eo, *wm);
         } else {
-            k_fused2_en<R, 16, 32, EPD><<<A.nblk, 16 * 32, 0, s>>>(A, eo);
+            k_fused2_en<R, ER, 32, sizeof(R) == 4 ? 2 : 1><<<A.nblk, ER * 32, 0, s>>>(A, eo);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return e;
@@ -1108,7 +1115,7 @@ hipError_t launch_step_fused2(Fields<R> o, Fields<R> nf, Mat<R> M, Geo g, R alph
     template hipError_t launch_step_fused2<R>(Fields<R>, Fields<R>, Mat<R>, Geo, R, Src, const WitMid<R>*, int, \
                                               int, int, int, hipStream_t, hipEvent_t*, const int*, int,      \
                                               const EnergyPair*);                                            \
-    template int64_t fused2_blocks<R>(Geo, int, int);                                                         \
+    template int64_t fused2_blocks<R>(Geo, int, int, bool);                                                         \
     template hipError_t fused2_static_tiles<R>(const uint8_t*, Geo, int, int, int, uint8_t*, int*, int64_t,    \
                                                int64_t*, int*, hipStream_t);
 TETE_FUSED2_INST(float)

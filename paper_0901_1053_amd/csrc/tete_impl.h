@@ -203,7 +203,7 @@ hipError_t launch_step_fused2(Fields<R> oldf, Fields<R> newf, Mat<R> mat, Geo g,
                               hipEvent_t* ev, const int* act, int nact, const EnergyPair* en = nullptr);
 // workgroups of a two-step launch that takes energy samples
 template <typename R>
-int64_t fused2_blocks(Geo g, int xchunk, int order);
+int64_t fused2_blocks(Geo g, int xchunk, int order, bool cls);
 // out[0] = sum of part[t * stride], t < n, in a fixed order (FP64)
 hipError_t launch_sum(const double* part, int n, int stride, double* out, hipStream_t s);
 // One byte per tile of the two-step kernel's tiling (rows, xchunk) in tab: 1

@@ -45,3 +45,26 @@ def test_every_end_of_the_march(orc, precision, rows, classes):
             for k in base:
                 assert np.array_equal(got[k], base[k]), (bunch_row, xchunk, k)
         assert np.any(base["wake"] != 0)
+
+
+# one tile of 18 owned rows by 28 entries exactly, one more, two tiles; with and
+# without the second state's sample
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("ny,nz,every", [(17, 27, 1), (18, 28, 2), (35, 55, 1), (36, 56, 2), (9, 83, 3)])
+def test_energy_samples_at_tile_edges(precision, ny, nz, every):
+    nx = 9
+    print("energy tiles", precision, ny, nz, every, flush=True)
+    out = []
+    for kernel in ("fused2", "fused"):
+        G = tete.Grid(nx, ny, nz, 2 * DZ, 2 * DZ, DZ, DZ, precision=precision, max_series=32)
+        G.set_pec_cells(inputs.random_cells(nx, ny, nz, 64))
+        G.set_fields(inputs.random_fields(G.shape, 65))
+        G.set_tuning(kernel, 0, 0, 0, 0)
+        G.set_diagnostics(every)
+        G.step(9)
+        out.append((G.energy_series(), G.get_fields()))
+        G.close()
+    a, b = out[0][0], out[1][0]
+    assert len(a) == len(b) and np.max(np.abs(a - b)) <= 1e-13 * np.max(np.abs(b))   # FP64 sums of the same terms
+    for k in out[0][1]:
+        assert np.array_equal(out[0][1][k], out[1][1][k]), k
