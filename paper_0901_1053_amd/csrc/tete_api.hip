@@ -139,6 +139,7 @@ struct tete_grid {
     int* skip_act[2];
     int skip_rows[2], skip_xc[2], skip_order[2], skip_nact[2];
     int64_t skip_nt[2];
+    int skip_used;     // planes per chunk of the two-step kernel's list
     int skip_live;
     // sticky error state: TETE_ERR_NONFINITE once a read-out found NaN or
     // Inf, until tete_set_fields; tete_step refuses to run meanwhile
@@ -291,9 +292,10 @@ int fused2_rows(const tete_grid* g)
     return r == 16 || ((r == 24 || r == 32) && g->fp32) ? r : 0;
 }
 
-// X-chunk of the fused kernels: the tuning's, else for grids that skip
+// X-chunk of the fused single step: the tuning's, else for grids that skip
 // static tiles chunks of 32 planes (short chunks find more tiles wholly in
 // the metal, at seven halo planes per chunk), else the library's choice (0).
+// The two-step kernel's own choice counts the active tiles.
 int fused_xchunk(const tete_grid* g)
 {
     return g->tune.xchunk != 0 ? g->tune.xchunk : g->skip ? 32 : 0;
@@ -330,7 +332,7 @@ tete_status static_table(tete_grid* g, bool wit, bool single)
         xc = fused_xchunk(g);
     } else {        // the instance that keeps witness lines has the default rows only
         rows = wit ? 0 : fused2_rows(g);
-        xc = fused_xchunk(g);
+        xc = g->tune.xchunk;
     }
     if (g->skip_rows[kind] == rows && g->skip_xc[kind] == xc && g->skip_order[kind] == order) return TETE_OK;
     if (single) {
@@ -339,7 +341,7 @@ tete_status static_table(tete_grid* g, bool wit, bool single)
                                      g->skip_act[1], skip_cap(g->geo), &g->skip_nt[1], &g->skip_nact[1], g->stream));
     } else {
         HIPCHK(fused2_static_tiles<R>(g->code, g->geo, rows, xc, order, g->skip_tab[0], g->skip_act[0],
-                                      skip_cap(g->geo), &g->skip_nt[0], &g->skip_nact[0], g->stream));
+                                      skip_cap(g->geo), &g->skip_nt[0], &g->skip_nact[0], &g->skip_used, g->stream));
     }
     g->skip_rows[kind] = rows;
     g->skip_xc[kind] = xc;
@@ -366,7 +368,7 @@ tete_status do_steps(tete_grid* g, int64_t nsteps)
     // launches of at most EN_PARTS workgroups
     int64_t en_blocks = 0;
     const bool en_fuse = two && g->diag_every > 0 && (!g->mat_set || g->mat_cls) && !g->skip &&
-                         (en_blocks = fused2_blocks<R>(g->geo, fused_xchunk(g), g->tune.order, g->mat_cls != 0)) > 0 &&
+                         (en_blocks = fused2_blocks<R>(g->geo, g->tune.xchunk, g->tune.order, g->mat_cls != 0)) > 0 &&
                          en_blocks <= EN_PARTS;
     for (int64_t s = 0; s < nsteps; ++s) {
         const bool at_n = g->diag_every > 0 && g->n % g->diag_every == 0;
@@ -415,7 +417,8 @@ tete_status do_steps(tete_grid* g, int64_t nsteps)
                              g->mat_cls ? g->craw : nullptr};
             HIPCHK(launch_step_fused2<R>(fields<R>(g, g->cur), fields<R>(g, 1 - g->cur), M, g->geo, (R)g->alpha,
                                          source(g, g->n), wit ? &wm : nullptr, fused2_rows(g), g->tune.depth,
-                                         fused_xchunk(g), g->tune.order, g->stream, ev, act, g->skip_nact[0],
+                                         act ? g->skip_used : g->tune.xchunk, g->tune.order, g->stream, ev, act,
+                                         g->skip_nact[0],
                                          en_pair ? &en : nullptr));
             if (en_pair) g->ecount += (at_n ? 1 : 0) + (at_n1 ? 1 : 0);
             g->skip_live = 1;

@@ -818,31 +818,25 @@ __global__ __launch_bounds__(TYH * LW) void k_fused2_cls(FArgs<R> A, const int* 
 // and lanes with their halos, over planes max(0, xs-4) .. min(xe+3, nx)) has
 // all three e edges PEC or absent (code 7), entries outside the grid counting
 // as PEC: then e stays zero and h constant there, and both steps leave every
-// entry the tile owns bitwise unchanged.  One workgroup per tile.
-__global__ __launch_bounds__(256) void k_static2(const uint8_t* code, Geo g, int TYH, int LW, int TY, int KT2,
-                                                 int xchunk, int nyt, int nzt, uint8_t* out)
+// entry the tile owns bitwise unchanged.  Here per plane, from which the host
+// takes tiles of any chunk length: out[q tiles + t] is 1 where an entry that
+// tile t loads on plane q has another code.  One wave per tile and plane.
+__global__ __launch_bounds__(256) void k_static2(const uint8_t* code, Geo g, int TYH, int LW, int nyt, int nzt,
+                                                 uint8_t* out)
 {
-    __shared__ int active;
-    const int t = blockIdx.x;
-    const int tz = t % nzt, ty = (t / nzt) % nyt, cx = t / (nzt * nyt);
-    if (threadIdx.x == 0) active = 0;
-    __syncthreads();
-    const int xs = cx * xchunk, xe = min(xs + xchunk, g.nx + 1);
-    const int pb = max(0, xs - 4), pe = min(xe + 3, g.nx);
-    const int rows = TYH, lanes = LW;
-    const int64_t per_plane = (int64_t)rows * lanes;
-    const int64_t n = (int64_t)(pe - pb + 1) * per_plane;
+    const int tiles = nyt * nzt;
+    const int64_t w = (int64_t)blockIdx.x * 4 + threadIdx.x / 64;
+    if (w >= (int64_t)(g.nx + 1) * tiles) return;
+    const int q = (int)(w / tiles), t = (int)(w % tiles);
+    const int j0 = t / nzt * (TYH - 6) - 3, k0 = t % nzt * (LW - 4) - 2;
+    const uint8_t* c = code + (int64_t)q * g.sp;
     bool found = false;
-    for (int64_t e = threadIdx.x; e < n && !found; e += blockDim.x) {
-        const int q = pb + (int)(e / per_plane);
-        const int r = (int)(e % per_plane);
-        const int j = ty * TY - 3 + r / lanes, k = tz * KT2 - 2 + r % lanes;
-        if (j < 0 || j > g.ny || k < 0 || k > g.nz) continue;
-        if ((code[(int64_t)q * g.sp + (int64_t)j * g.sz + k] & 7u) != 7u) found = true;
+    for (int r = threadIdx.x % 64; r < TYH * LW; r += 64) {
+        const int j = j0 + r / LW, k = k0 + r % LW;
+        if ((unsigned)j <= (unsigned)g.ny && (unsigned)k <= (unsigned)g.nz && (c[j * g.sz + k] & 7u) != 7u) found = true;
     }
-    if (found) atomicOr(&active, 1);
-    __syncthreads();
-    if (threadIdx.x == 0) out[t] = active ? 0 : 1;
+    const bool any = __ballot(found) != 0;
+    if (threadIdx.x % 64 == 0) out[w] = any;
 }
 
 // The two-step kernel that also keeps e_z^{n+1/2} of the witness lines
@@ -990,34 +984,66 @@ int64_t fused2_tile_cap(Geo g)
     return (int64_t)(g.nx + 1) * ((g.ny + 1 + 9) / 10) * ((g.nz + 1 + 27) / 28);
 }
 
+// Chunk length of the active tiles where the tuning gives none: the launch runs
+// them in rounds of kRound, each as long as a chunk and ten planes; equal chunks,
+// as many as make that shortest (a quarter of the work over all CUs added, as in
+// plan_chunks).  Chunks of 32 planes whatever the grid took 72.6 us per launch on
+// the 96 x 96 x 512 open pipe FP32, this rule 64.2.
 template <typename R>
 hipError_t fused2_static_tiles(const uint8_t* code, Geo g, int rows, int xchunk, int order, uint8_t* tab, int* act,
-                               int64_t cap, int64_t* ntiles, int* nact, hipStream_t s)
+                               int64_t cap, int64_t* ntiles, int* nact, int* used, hipStream_t s)
 {
     Fields<R> none = {};
     Mat<R> M = {};
     M.code = code;
     FArgs<R> A = fused_args<R>(none, none, M, g, R(0), Src{});
     if (!fused2_setup<R>(A, rows, xchunk, order)) return hipErrorInvalidValue;
-    const int64_t nt = (int64_t)A.nyt * A.nzt * A.nxc;
-    if (nt > cap || nt > 0x7fffffff) return hipErrorInvalidValue;
+    const int tiles = A.nyt * A.nzt, planes = g.nx + 1;
+    const int64_t n = (int64_t)tiles * planes;
+    if (n > cap || n > 0x7fffffff) return hipErrorInvalidValue;
     const int r = rows == 0 ? Default2<R>::rows : rows;
-    const int lw = lanes2(sizeof(R), r);
-    k_static2<<<(int)nt, 256, 0, s>>>(code, g, r, lw, r - 6, lw - 4, A.xchunk, A.nyt, A.nzt, tab);
+    k_static2<<<(int)((n + 3) / 4), 256, 0, s>>>(code, g, r, lanes2(sizeof(R), r), A.nyt, A.nzt, tab);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    std::vector<uint8_t> h((size_t)nt);
-    if ((e = hipMemcpyAsync(h.data(), tab, (size_t)nt, hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
+    std::vector<uint8_t> h((size_t)n);
+    if ((e = hipMemcpyAsync(h.data(), tab, (size_t)n, hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
+    // next[q tiles + t]: the first plane from q on that is not static in tile t
+    std::vector<int> next((size_t)n + tiles, planes);
+    for (int64_t i = n; i-- > 0;) next[(size_t)i] = h[(size_t)i] ? (int)(i / tiles) : next[(size_t)(i + tiles)];
+    auto active = [&](int t, int cx, int xc) {
+        const int xs = cx * xc, xe = std::min(xs + xc, planes);
+        return next[(size_t)std::max(0, xs - 4) * tiles + t] <= std::min(xe + 3, g.nx);
+    };
+    if (xchunk == 0) {
+        const int64_t plane_bytes = (int64_t)g.sp * sizeof(R);
+        const int xmax = (int)std::min<int64_t>(planes, ((int64_t(1) << 31) - 1) / plane_bytes - 8);
+        double best = 0.0;
+        for (int c = (planes + xmax - 1) / xmax; c <= planes; ++c) {
+            const int xc = (planes + c - 1) / c;
+            if ((planes + xc - 1) / xc != c) continue;
+            int64_t items = 0;
+            for (int cx = 0; cx < c; ++cx)
+                for (int t = 0; t < tiles; ++t) items += active(t, cx, xc);
+            const double cost =
+                ((double)((items + kRound - 1) / kRound) + 0.25 * (double)items / kRound) * (double)(xc + 10);
+            if (best == 0.0 || cost < best) {
+                best = cost;
+                xchunk = xc;
+            }
+            if (items > 8 * (int64_t)kRound) break;   // more chunks only add lead-in planes
+        }
+        if (!fused2_setup<R>(A, rows, xchunk, order)) return hipErrorInvalidValue;
+    }
     // the active tiles in the order the full launch takes them
     std::vector<int> list;
-    list.reserve((size_t)nt);
+    list.reserve((size_t)tiles * A.nxc);
     const int nlb = launch_tiles(A.order, A.nyt, A.nzt, A.nxc);
     for (int lb = 0; lb < nlb; ++lb) {
         int ty, tz, cx;
         if (!tile_of(lb, A.order, A.nyt, A.nzt, ty, tz, cx)) continue;
-        const int t = (cx * A.nyt + ty) * A.nzt + tz;
-        if (!h[(size_t)t]) list.push_back(t);
+        const int t = ty * A.nzt + tz;
+        if (active(t, cx, A.xchunk)) list.push_back(cx * tiles + t);
     }
     if (!list.empty()) {
         if ((e = hipMemcpyAsync(act, list.data(), sizeof(int) * list.size(), hipMemcpyHostToDevice, s)) !=
@@ -1025,8 +1051,9 @@ hipError_t fused2_static_tiles(const uint8_t* code, Geo g, int rows, int xchunk,
             return e;
         if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;   // list is a host temporary
     }
-    *ntiles = nt;
+    *ntiles = (int64_t)tiles * A.nxc;
     *nact = (int)list.size();
+    *used = A.xchunk;
     return hipSuccess;
 }
 
@@ -1164,7 +1191,7 @@ hipError_t launch_step_fused2(Fields<R> o, Fields<R> nf, Mat<R> M, Geo g, R alph
                                               const EnergyPair*);                                            \
     template int64_t fused2_blocks<R>(Geo, int, int, bool);                                                         \
     template hipError_t fused2_static_tiles<R>(const uint8_t*, Geo, int, int, int, uint8_t*, int*, int64_t,    \
-                                               int64_t*, int*, hipStream_t);
+                                               int64_t*, int*, int*, hipStream_t);
 TETE_FUSED2_INST(float)
 TETE_FUSED2_INST(double)
 

@@ -207,16 +207,16 @@ template <typename R>
 int64_t fused2_blocks(Geo g, int xchunk, int order, bool cls);
 // out[0] = sum of part[t * stride], t < n, in a fixed order (FP64)
 hipError_t launch_sum(const double* part, int n, int stride, double* out, hipStream_t s);
-// One byte per tile of the two-step kernel's tiling (rows, xchunk) in tab: 1
-// where every entry the tile loads has its three e edges PEC, so that a step
-// leaves the tile's entries unchanged; and in act the *nact other tiles in the
-// launch order of the tile order `order`.  *ntiles = tiles (at most cap; act
-// holds cap ints).  Synchronises the stream.
+// The tiles of the two-step kernel's tiling (rows, xchunk; 0: chosen for the
+// active tiles, *used) on which not every entry loaded has its three e edges
+// PEC, so that a step may change them: *nact tiles in act, in the launch order
+// of the tile order `order`.  *ntiles = all tiles; tab holds a byte per tile and
+// plane (at most cap; act holds cap ints).  Synchronises the stream.
 // Bytes a static-tile table needs at most, over every tiling.
 int64_t fused2_tile_cap(Geo g);
 template <typename R>
 hipError_t fused2_static_tiles(const uint8_t* code, Geo g, int rows, int xchunk, int order, uint8_t* tab, int* act,
-                               int64_t cap, int64_t* ntiles, int* nact, hipStream_t s);
+                               int64_t cap, int64_t* ntiles, int* nact, int* used, hipStream_t s);
 // One step of Yee's scheme (7) (tete_yee.hip): state (e^{n-1/2}, h^n),
 // dtau = 2 alpha; xchunk and order as for the fused step.
 bool yee_fits(Geo g, int real_bytes);
