@@ -1012,7 +1012,7 @@ tete_status tete_set_open_pipes(tete_grid* g, int64_t start_step, int32_t kend, 
     }
     // |r|^2 <= 1e-32 |b|^2 (b = delta): the residual at the rounding level
     HIPCHK(launch_cg_init(W, P, src, 1e-32, g->stream));
-    const int cap = 20 * (g->d.nx + g->d.ny) + 1000, chunk = 32;
+    const int cap = (20 * (g->d.nx + g->d.ny) + 1000 + 31) / 32 * 32, chunk = cg_one_block(P) ? cap : 32;
     double hs[8] = {0};
     int done = 0;
     for (int it = 0; it < cap && !done; it += chunk) {

@@ -359,6 +359,8 @@ hipError_t launch_cg_init(CgWork W, CgPlane P, int64_t src, double tol, hipStrea
 // iters iterations (a converged iteration leaves x unchanged); sc[0] = |r|^2,
 // sc[3] = 1 once converged, sc[5] = the iterations taken
 hipError_t launch_cg_iterations(CgWork W, CgPlane P, int iters, hipStream_t s);
+// one workgroup takes all the iterations of such a plane in one launch
+bool cg_one_block(CgPlane P);
 // profile table F[p + 2M + 1], p = -2M-1 .. 1, of the bunch current lam
 hipError_t launch_pipe_profile(double* F, const double* lam, int M, double dtau, hipStream_t s);
 // the state y^{n0} of the bunch's field in the pipe into f

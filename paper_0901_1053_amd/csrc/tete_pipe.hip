@@ -152,6 +152,157 @@ __global__ void k_cg_dir(double* p, const double* r, const double* sc, CgPlane P
         p[t] = r[t] + b * p[t];
 }
 
+// The iterations of a plane that one workgroup holds: r, q and x of node
+// t = 1024 m + thread in registers (m < M), p in LDS with zeros around it.  A
+// launch per sub-step took 18.3 us per iteration whatever the plane, five launches
+// as long as a launch takes; here the sub-steps are three barriers apart: 2.5 us on
+// 64 x 64 nodes, 4.0 on 97 x 97, 6.7 on 112 x 128, most of it LDS reads of the
+// five-point stencil and the sums.  17 nodes per thread fill the LDS; a larger
+// plane takes the launches.  The sums are
+// those of the kernels above in the same order (waves of 64 nodes by the shuffle
+// tree, four waves, then the blocks of 256 nodes by the same rule), so the
+// iterates and their number are bitwise the same.
+constexpr int CGT = 1024;        // threads
+constexpr int CGP = 512;         // most zeros before and after p: row length + 1
+
+__device__ __forceinline__ double cg_pair(uint32_t al, uint32_t ah) { return __hiloint2double((int)ah, (int)al); }
+// One level of the shuffle tree for two values at a time: lanes below 32 (even
+// rows of 16) of the result hold a's sums, the others b's.
+__device__ __forceinline__ double cg_fold32(double a, double b)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)__double2loint(a), (uint32_t)__double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)__double2hiint(a), (uint32_t)__double2hiint(b), false, false);
+    return cg_pair(lo[0], hi[0]) + cg_pair(lo[1], hi[1]);
+}
+__device__ __forceinline__ double cg_fold16(double a, double b)
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)__double2loint(a), (uint32_t)__double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)__double2hiint(a), (uint32_t)__double2hiint(b), false, false);
+    return cg_pair(lo[0], hi[0]) + cg_pair(lo[1], hi[1]);
+}
+template <int N>
+__device__ __forceinline__ double cg_row(double v)      // v of lane + N within a row of 16
+{
+    return cg_pair((uint32_t)__builtin_amdgcn_mov_dpp(__double2loint(v), 0x100 + N, 0xf, 0xf, true),
+                   (uint32_t)__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x100 + N, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double cg_rows(double v)
+{
+    v += cg_row<8>(v);
+    v += cg_row<4>(v);
+    v += cg_row<2>(v);
+    v += cg_row<1>(v);
+    return v;
+}
+
+// Sums of the M values per thread over the workgroup, as k_cg_apply and
+// k_cg_alpha (k_cg_update and k_cg_beta) form them; ws: 16 M doubles.  Every
+// thread returns the sum.
+template <int M>
+__device__ __forceinline__ double cg_sum(const double (&v)[M], double* ws)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int m = 0; m < M; m += 4) {
+        // row 0 of the result holds v[m], row 1 v[m+2], row 2 v[m+1], row 3 v[m+3]
+        const double a = cg_fold32(v[m], m + 1 < M ? v[m + 1] : 0.0);
+        const double b = cg_fold32(m + 2 < M ? v[m + 2] : 0.0, m + 3 < M ? v[m + 3] : 0.0);
+        const double s = cg_rows(cg_fold16(a, b));
+        const int row = lane >> 4, mm = m + (row >> 1) + (row & 1) * 2;
+        if ((lane & 15) == 0 && mm < M) ws[mm * 16 + wave] = s;
+    }
+    __syncthreads();
+    // block b of 256 nodes: its four waves in order; blocks by the tree of 64
+    double part[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int b = 64 * h + lane;
+        part[h] = 0.0;
+        if (b < 4 * M) part[h] += ((ws[4 * b] + ws[4 * b + 1]) + ws[4 * b + 2]) + ws[4 * b + 3];
+    }
+    const double s = cg_fold32(part[0], part[1]);
+    const double t = cg_rows(cg_fold16(s, s));
+    const double r0 = cg_pair((uint32_t)__builtin_amdgcn_readlane(__double2loint(t), 0),
+                              (uint32_t)__builtin_amdgcn_readlane(__double2hiint(t), 0));
+    const double r1 = cg_pair((uint32_t)__builtin_amdgcn_readlane(__double2loint(t), 32),
+                              (uint32_t)__builtin_amdgcn_readlane(__double2hiint(t), 32));
+    return r0 + r1;
+}
+
+template <int M>
+__global__ __launch_bounds__(CGT) void k_cg_block(CgWork W, CgPlane P, int iters)
+{
+    __shared__ double pl[M * CGT + 2 * CGP];
+    __shared__ double ws[2][16 * M];
+    const int tid = threadIdx.x, n = (int)P.n, sy = P.ny + 1;
+    double* const p = pl + CGP;
+    double x[M], r[M];
+    uint32_t freem = 0;
+    for (int t = tid; t < M * CGT + 2 * CGP; t += CGT) pl[t] = 0.0;
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const int t = m * CGT + tid;
+        x[m] = r[m] = 0.0;
+        if (t < n) {
+            x[m] = W.x[t];
+            r[m] = W.r[t];
+            p[t] = W.p[t];
+            if (W.w[t] != 0.0) freem |= 1u << m;
+        }
+    }
+    double rr = W.sc[CG_RR], alpha = W.sc[CG_ALPHA], beta = W.sc[CG_BETA], it = W.sc[CG_ITER];
+    const double tol = W.sc[CG_TOL];
+    bool done = W.sc[CG_DONE] != 0.0;
+    __syncthreads();
+    for (int k = 0; k < iters && !done && rr == rr; ++k) {
+        double q[M], s[M];
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const int t = m * CGT + tid;
+            double v = 0.0;
+            const double c = p[t];
+            // free nodes lie strictly inside the plane; the zeros around p keep
+            // the others' reads in bounds
+            if (freem >> m & 1) v = P.wx * ((c - p[t + sy]) + (c - p[t - sy])) + P.wy * ((c - p[t + 1]) + (c - p[t - 1]));
+            q[m] = v;
+            s[m] = c * v;
+        }
+        const double pq = cg_sum<M>(s, ws[0]);
+        alpha = pq == 0.0 ? 0.0 : rr / pq;
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            x[m] += alpha * p[m * CGT + tid];
+            r[m] = r[m] - alpha * q[m];
+            s[m] = r[m] * r[m];
+        }
+        const double rn = cg_sum<M>(s, ws[1]);     // its barrier: every read of p above is done
+        beta = rr != 0.0 ? rn / rr : 0.0;
+        rr = rn;
+        it += 1.0;
+        done = rn <= tol;
+#pragma unroll
+        for (int m = 0; m < M; ++m) p[m * CGT + tid] = r[m] + beta * p[m * CGT + tid];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const int t = m * CGT + tid;
+        if (t < n) {
+            W.x[t] = x[m];
+            W.r[t] = r[m];
+            W.p[t] = p[t];
+        }
+    }
+    if (tid == 0) {
+        W.sc[CG_RR] = rr;
+        W.sc[CG_ALPHA] = alpha;
+        W.sc[CG_BETA] = beta;
+        W.sc[CG_DONE] = done ? 1.0 : 0.0;
+        W.sc[CG_ITER] = it;
+    }
+}
+
 // x = 0, r = p = delta at the bunch node; sc as for a fresh iteration.
 __global__ void k_cg_init(double* x, double* r, double* p, CgPlane P, int64_t src, double tol, double* sc)
 {
@@ -235,8 +386,18 @@ hipError_t launch_cg_init(CgWork W, CgPlane P, int64_t src, double tol, hipStrea
     return hipGetLastError();
 }
 
+bool cg_one_block(CgPlane P) { return P.n <= 17 * CGT && P.ny + 2 <= CGP; }
+
 hipError_t launch_cg_iterations(CgWork W, CgPlane P, int iters, hipStream_t s)
 {
+    if (cg_one_block(P)) {
+        if (P.n <= 4 * CGT) k_cg_block<4><<<1, CGT, 0, s>>>(W, P, iters);
+        else if (P.n <= 7 * CGT) k_cg_block<7><<<1, CGT, 0, s>>>(W, P, iters);
+        else if (P.n <= 10 * CGT) k_cg_block<10><<<1, CGT, 0, s>>>(W, P, iters);
+        else if (P.n <= 14 * CGT) k_cg_block<14><<<1, CGT, 0, s>>>(W, P, iters);
+        else k_cg_block<17><<<1, CGT, 0, s>>>(W, P, iters);
+        return hipGetLastError();
+    }
     const int nb = pblocks(P.n);
     for (int it = 0; it < iters; ++it) {
         k_cg_apply<<<nb, PT, 0, s>>>(W.q, W.p, W.w, P, W.partial);
