@@ -171,7 +171,7 @@ FArgs<R> fused_args(Fields<R> oldf, Fields<R> newf, Mat<R> mat, Geo g, R alpha, 
 // Fills the tiling of A for a launch shape; false if the shape is invalid or
 // the grid's planes are too large for the fused kernel.
 template <typename R>
-bool fused_setup(FArgs<R>& A, int rows, int xchunk, int order, bool member = false);
+bool fused_setup(FArgs<R>& A, int rows, int xchunk, int order, bool member = false, bool mat = false);
 int fused_default_rows(int real_bytes);
 // Two steps in one launch (tete_fused2.hip): the fused step temporally
 // blocked; xchunk and order as for the single step.

@@ -68,3 +68,42 @@ def test_energy_samples_at_tile_edges(precision, ny, nz, every):
     assert len(a) == len(b) and np.max(np.abs(a - b)) <= 1e-13 * np.max(np.abs(b))   # FP64 sums of the same terms
     for k in out[0][1]:
         assert np.array_equal(out[0][1][k], out[1][1][k]), k
+
+
+def _single(orc, precision, xchunk, bunch_row, arrays, shape):
+    nx, ny, nz = shape
+    cells = inputs.random_cells(nx, ny, nz, 66)
+    G = tete.Grid(nx, ny, nz, 2 * DZ, 2 * DZ, DZ, DZ, precision=precision, materials=arrays)
+    G.set_pec_cells(cells)
+    if arrays:
+        g = orc.Geom(nx, ny, nz, 2 * DZ, 2 * DZ, DZ, DZ)
+        vac = orc.vacuum_materials(g, cells)
+        rng = np.random.default_rng(67)
+        G.set_materials({k: v * rng.uniform(0.6, 1.0, size=v.shape) for k, v in vac.items()})
+    G.set_fields(inputs.random_fields(G.shape, 68))
+    G.set_bunch(1e-9, 2.0 * DZ, nx // 2, bunch_row, 12, -90, 120)
+    G.set_tuning("split" if xchunk < 0 else "fused", 0, max(xchunk, 0), 0, 0)
+    G.step(3)
+    out = G.get_fields()
+    out["wake"] = G.wake()
+    G.close()
+    return out
+
+
+# the single step: every end of its march, tiles of 8, 12 and 20 owned rows by 62
+# and 30 entries; against the two-kernel step within 1e-12 / 2e-5, and bitwise
+# between chunk lengths
+@pytest.mark.parametrize("precision,arrays", [("fp32", False), ("fp64", False), ("fp32", True), ("fp64", True)])
+@pytest.mark.parametrize("shape", [(25, 40, 70), (9, 19, 29), (9, 20, 61), (4, 41, 62)])
+def test_every_end_of_the_single_step(orc, precision, arrays, shape):
+    tol = 1e-12 if precision == "fp64" else 2e-5
+    for bunch_row in (2, shape[1] // 2, shape[1] - 1):
+        print("single march", precision, arrays, shape, bunch_row, flush=True)
+        ref = _single(orc, precision, -1, bunch_row, arrays, shape)
+        base = _single(orc, precision, 10 ** 6, bunch_row, arrays, shape)
+        for k in ref:
+            assert np.max(np.abs(base[k] - ref[k])) <= tol * max(np.max(np.abs(ref[k])), 1e-300), k
+        for xchunk in (1, 2, 3, 4, 5, 6):
+            got = _single(orc, precision, xchunk, bunch_row, arrays, shape)
+            for k in base:
+                assert np.array_equal(got[k], base[k]), (bunch_row, xchunk, k)
