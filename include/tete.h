@@ -204,7 +204,7 @@ tete_status tete_set_pec_cells(tete_grid* g, const uint8_t* cell_is_pec);
  * runs as after tete_set_material_classes with those tuples: paired steps
  * take the two-step kernel's class instance, with the same results as the
  * materials step over the arrays.  Otherwise, with FP32 fields, paired steps
- * take the two-step kernel's arrays instance (16 rows of 32 lanes, the six
+ * take the two-step kernel's arrays instance (16 or 24 rows of 32 lanes, the six
  * arrays read with the fields once per two steps; not with witness lines or
  * TETE_F_SKIP_STATIC), with the same results as single materials steps; every
  * other step (and every step with FP64 fields) is the materials step.

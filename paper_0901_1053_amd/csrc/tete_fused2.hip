@@ -89,14 +89,6 @@ struct Shape2 {
 template <typename R> struct Default2;
 template <> struct Default2<float> { static constexpr int rows = 16, lw = 64, pd = 1; };
 template <> struct Default2<double> { static constexpr int rows = 16, lw = 32, pd = 2; };
-// Rows (of 32 lanes) of the instance that takes energy samples.  The sums'
-// operands do not fit 128 VGPRs; in FP32 with vacuum coefficients they fit the
-// 168 of 24 rows, two planes ahead (with witness lines 4 spill; one plane ahead
-// took 571 us per step).  Three waves per SIMD and 504 owned of 768 entries
-// against two and 280 of 512 with 16 rows: 657 -> 544 us per step on 256 x 256 x
-// 1024 with a sample every second step.  Materials by class need 201, FP64 231.
-constexpr int kEnRows32 = 24;
-inline int en_rows(int real_bytes, bool cls) { return real_bytes == 4 && !cls ? kEnRows32 : 16; }
 inline int lanes2(int real_bytes, int rows) { return real_bytes == 8 || rows == 24 || rows == 32 ? 32 : 64; }
 
 // Two steps of one work item (tile and x-chunk).  Every thread of the
@@ -544,7 +536,7 @@ __device__ __forceinline__ void fused2_tile(const FArgs<R>& A, const Tile& t, LD
     // The march: unrolled so that the prefetch buffers, the LDS parity and most
     // of the carried state keep their registers.  A workgroup whose tile does not
     // hold the source row takes the march without the source.
-    constexpr int U = PD == 2 ? 6 : EN ? 2 : 4;
+    constexpr int U = PD == 2 ? 6 : EN || ARR ? 2 : 4;   // 4 spills with EN or ARR
     static_assert(U % 2 == 0 && U % (PD + 1) == 0, "whole turns of the parity and of the prefetch buffers");
     auto march = [&](auto src_tile) {
         int p = xs - 4;
@@ -611,7 +603,7 @@ __global__ __launch_bounds__(TYH * LW) void k_fused2(FArgs<R> A, const int* act)
 }
 
 // The two-step kernel that also sums the energy of its input and of the
-// state between its two steps (vacuum coefficients, the shape en_rows, the full
+// state between its two steps (vacuum coefficients, the full
 // tiling: one pair of partial sums per workgroup, zero for the padding
 // workgroups of the blocked tile orders).
 template <typename R, int TYH, int LW, int PD>
@@ -683,8 +675,8 @@ __global__ __launch_bounds__(TYH * LW) void k_fused2_en_cls(FArgs<R> A, EnOut eo
                                                                             eo);
 }
 
-// The two-step kernel with per-entry materials (FP32: 16 rows of 32 lanes,
-// 512 threads, two planes loaded ahead).
+// The two-step kernel with per-entry materials (FP32: 16 rows of 32 lanes, two
+// planes loaded ahead, or 24 rows, one).
 template <typename R, int TYH, int LW, int PD>
 __global__ __launch_bounds__(TYH * LW) void k_fused2_arr(FArgs<R> A, Arr6<R> MA, const int* act)
 {
@@ -958,13 +950,45 @@ void run_fused2(const FArgs<R>& A, const int* act, int nact, hipStream_t s)
     else if (nact > 0) k_fused2<R, TYH, LW, PD><<<nact, TYH * LW, 0, s>>>(A, act);
 }
 
+// Shape of the FP32 instances whose operands do not fit 128 VGPRs, energy samples
+// with vacuum coefficients (two planes ahead) and per-entry materials (one):
+// 24 rows of 32 lanes, three waves per SIMD and 504 of 768 entries owned, or 16
+// rows, two waves per SIMD and 280 of 512 owned but a plane taken in less time.
+// Of the two the one whose rounds of workgroups take less: planes of the longest
+// chain of chunks, a plane of 24 rows `per24` planes of 16.  That is 1.32 with
+// samples (us per step with a sample every second step, 16 and 24 rows: 24 x 24 x
+// 48 10.5, 12.5; 48 x 48 x 256 17.3, 18.6; 64 x 64 x 256 24.8, 22.1; 128 x 128 x
+// 1024 176, 152; 256 x 256 x 1024 657, 544) and 1.46 with materials (48 x 48 x 256
+// 14.2, 16.7; 91 x 77 x 513 43.0, 47.9; 120 x 130 x 300 62.6, 60.1; 256 x 256 x 512
+// 348, 327).  Witness lines spill 4 registers with 24 rows; materials by class
+// need 201 VGPRs, FP64 231: 16 rows.
+template <typename R>
+bool setup_16_or_24(FArgs<R>& A, bool rows24, double per24, int xchunk, int order, int& rows)
+{
+    rows = 16;
+    if (!fused2_setup<R>(A, 16, xchunk, order, 32)) return false;
+    if (!rows24 || sizeof(R) == 8) return true;
+    FArgs<R> B = A;
+    if (!fused2_setup<R>(B, 24, xchunk, order, 32)) return false;
+    auto planes = [](const FArgs<R>& X) {
+        return (double)((X.nfull + kRound - 1) / kRound) * (X.xchunk + 10) + (X.nblk > X.nfull ? X.tchunk + 10 : 0);
+    };
+    if (per24 * planes(B) < planes(A)) {
+        A = B;
+        rows = 24;
+    }
+    return true;
+}
+constexpr double kEnPer24 = 1.32, kArrPer24 = 1.46;
+
 template <typename R>
 int64_t fused2_blocks(Geo g, int xchunk, int order, bool cls)
 {
     Fields<R> none = {};
     Mat<R> M = {};
     FArgs<R> A = fused_args<R>(none, none, M, g, R(0), Src{});
-    if (!fused2_setup<R>(A, en_rows(sizeof(R), cls), xchunk, order, 32)) return -1;
+    int rows;
+    if (!setup_16_or_24<R>(A, !cls, kEnPer24, xchunk, order, rows)) return -1;
     return A.nblk;
 }
 
@@ -974,25 +998,28 @@ hipError_t launch_step_fused2(Fields<R> o, Fields<R> nf, Mat<R> M, Geo g, R alph
                               const int* act, int nact, const EnergyPair* en)
 {
     if (en && en->want) {
-        // energy samples: the shape en_rows over the full tiling
+        // energy samples: their own shape over the full tiling
         FArgs<R> A = fused_args<R>(o, nf, M, g, alpha, src);
         // (materials by class: their energy coefficients from en->craw; witness
         // lines on vacuum grids only)
+        int er;
         if (act || (M.arr[0] && !A.cls) || (A.cls && (!en->craw || wm)) ||
-            !fused2_setup<R>(A, en_rows(sizeof(R), A.cls), xchunk, order, 32))
+            !setup_16_or_24<R>(A, !A.cls, kEnPer24, xchunk, order, er))
             return hipErrorInvalidValue;
         if (wm && (wm->iw < 1 || wm->iw > g.nx - 1 || wm->jw < 1 || wm->jw > g.ny - 1)) return hipErrorInvalidValue;
         if (A.nblk > en->cap) return hipErrorInvalidValue;
         hipError_t e;
         if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return e;
-        constexpr int ER = sizeof(R) == 4 ? kEnRows32 : 16;
         const EnOut eo = {en->part, en->want, en->alpha, en->craw, nullptr};
+        constexpr int EPD = sizeof(R) == 4 ? 2 : 1;   // FP64: one plane ahead fits the VGPRs
         if (A.cls) {
-            k_fused2_en_cls<R, 16, 32, sizeof(R) == 4 ? 2 : 1><<<A.nblk, 16 * 32, 0, s>>>(A, eo);
-        } else if (wm) {
-            k_fused2_en_wit<R, ER, 32, sizeof(R) == 4 ? 2 : 1><<<A.nblk, ER * 32, 0, s>>>(A, eo, *wm);
-        } else {
-            k_fused2_en<R, ER, 32, sizeof(R) == 4 ? 2 : 1><<<A.nblk, ER * 32, 0, s>>>(A, eo);
+            k_fused2_en_cls<R, 16, 32, EPD><<<A.nblk, 16 * 32, 0, s>>>(A, eo);
+        } else if (er == 16) {
+            if (wm) k_fused2_en_wit<R, 16, 32, EPD><<<A.nblk, 16 * 32, 0, s>>>(A, eo, *wm);
+            else k_fused2_en<R, 16, 32, EPD><<<A.nblk, 16 * 32, 0, s>>>(A, eo);
+        } else if constexpr (sizeof(R) == 4) {
+            if (wm) k_fused2_en_wit<R, 24, 32, 2><<<A.nblk, 24 * 32, 0, s>>>(A, eo, *wm);
+            else k_fused2_en<R, 24, 32, 2><<<A.nblk, 24 * 32, 0, s>>>(A, eo);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return e;
@@ -1009,21 +1036,19 @@ hipError_t launch_step_fused2(Fields<R> o, Fields<R> nf, Mat<R> M, Geo g, R alph
         if (wm) return hipErrorInvalidValue;
         rows = sizeof(R) == 4 ? 24 : 16;
     }
-    // per-entry materials (FP32 only): one shape, 16 rows of 32 lanes; no
-    // witness lines, no static-tile list
+    // per-entry materials (FP32 only): their own shape; no witness lines, no
+    // static-tile list
     const bool arr = !A.cls && M.arr[0] != nullptr;
-    int lanes = 0;
     if (arr) {
         if (sizeof(R) != 4 || wm || act) return hipErrorInvalidValue;
         for (int c = 0; c < 6; ++c)
             if (!M.arr[c]) return hipErrorInvalidValue;
-        rows = 16;
-        lanes = 32;
     }
     // with a list of active tiles, one workgroup per entry (none: every tile is
     // static and the new set already holds the result)
     const int grid = act ? nact : 0;
-    if (!fused2_setup<R>(A, rows, xchunk, order, lanes)) return hipErrorInvalidValue;
+    if (!(arr ? setup_16_or_24<R>(A, true, kArrPer24, xchunk, order, rows) : fused2_setup<R>(A, rows, xchunk, order)))
+        return hipErrorInvalidValue;
     hipError_t e;
     if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return e;
     bool done = false;
@@ -1031,7 +1056,8 @@ hipError_t launch_step_fused2(Fields<R> o, Fields<R> nf, Mat<R> M, Geo g, R alph
         if (arr) {
             Arr6<R> MA;
             for (int c = 0; c < 6; ++c) MA.m[c] = M.arr[c];
-            k_fused2_arr<R, 16, 32, 2><<<A.nblk, 16 * 32, 0, s>>>(A, MA, nullptr);
+            if (rows == 16) k_fused2_arr<R, 16, 32, 2><<<A.nblk, 16 * 32, 0, s>>>(A, MA, nullptr);
+            else k_fused2_arr<R, 24, 32, 1><<<A.nblk, 24 * 32, 0, s>>>(A, MA, nullptr);
             done = true;
         }
     }

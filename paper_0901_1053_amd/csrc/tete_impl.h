@@ -195,7 +195,7 @@ struct EnergyPair {
 // rows (0 with wm), xchunk and order; the launch takes only these (none if
 // nact is 0), and with wm stores witness values only in them; en (or
 // nullptr, or want 0): energy samples, with vacuum coefficients only, in
-// their own shape (16 rows of 32 lanes; the rows and depth asked for do not
+// their own shape (16 or 24 rows of 32 lanes; the rows and depth asked for do not
 // apply; hipErrorInvalidValue otherwise, or when the launch has more
 // workgroups than en->cap)
 template <typename R>

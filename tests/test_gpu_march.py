@@ -107,3 +107,34 @@ def test_every_end_of_the_single_step(orc, precision, arrays, shape):
             got = _single(orc, precision, xchunk, bunch_row, arrays, shape)
             for k in base:
                 assert np.array_equal(got[k], base[k]), (bunch_row, xchunk, k)
+
+
+# 270 tiles of 16 rows are two rounds of workgroups, 162 of 24 rows one; 54 and 36
+# tiles one round either way: the FP32 instances with 24 and with 16 rows
+@pytest.mark.parametrize("shape", [(6, 95, 735), (6, 95, 150)])
+@pytest.mark.parametrize("kind", ["energy", "arrays"])
+def test_rows_of_the_larger_instances(orc, kind, shape):
+    nx, ny, nz = shape
+    print("16 or 24 rows", kind, shape, flush=True)
+    cells = inputs.random_cells(nx, ny, nz, 81)
+    out = []
+    for kernel in ("fused2", "fused"):
+        G = tete.Grid(nx, ny, nz, 2 * DZ, 2 * DZ, DZ, DZ, precision="fp32", materials=kind == "arrays", max_series=32)
+        G.set_pec_cells(cells)
+        if kind == "arrays":
+            vac = orc.vacuum_materials(orc.Geom(nx, ny, nz, 2 * DZ, 2 * DZ, DZ, DZ), cells)
+            rng = np.random.default_rng(82)
+            G.set_materials({k: v * rng.uniform(0.6, 1.0, size=v.shape) for k, v in vac.items()})
+        else:
+            G.set_diagnostics(1)
+        G.set_fields(inputs.random_fields(G.shape, 83))
+        G.set_bunch(1e-9, 2.0 * DZ, nx // 2, 41, 12, -90, 120)
+        G.set_tuning(kernel, 0, 10 ** 6, 0, 0)
+        G.step(5)
+        out.append((G.get_fields(), G.wake(), G.energy_series() if kind == "energy" else np.ones(1)))
+        G.close()
+    for k in out[0][0]:
+        assert np.array_equal(out[0][0][k], out[1][0][k]), k
+    assert np.array_equal(out[0][1], out[1][1])
+    a, b = out[0][2], out[1][2]
+    assert len(a) == len(b) and np.max(np.abs(a - b)) <= 1e-13 * np.max(np.abs(b))   # FP64 sums of the same terms
