@@ -1328,17 +1328,20 @@ size_t batch_table_bytes() { return up(sizeof(BatchTable<R>)); }
 // the items of many grids share the persistent workgroups).
 int batch_order(const tete_grid* g) { return g->tune.order != 0 ? g->tune.order : 2; }
 
-// Two-step arguments of one member for both parities, in chunks of xc planes.
+// Two-step arguments of one member for both parities.
 template <typename R>
-bool batch_two_args(tete_grid* g, BatchItem<R>& it, int phase, int xc)
+bool batch_two_args(tete_grid* g, BatchItem<R>& it, int phase, int& total2)
 {
     FArgs<R> f2 = fused_args<R>(fields<R>(g, g->cur), fields<R>(g, 1 - g->cur), mats<R>(g), g->geo, (R)g->alpha,
                                 source(g, g->n));
     FArgs<R> b2 = fused_args<R>(fields<R>(g, 1 - g->cur), fields<R>(g, g->cur), mats<R>(g), g->geo, (R)g->alpha,
                                 source(g, g->n));
-    if (!fused2_setup<R>(f2, 0, xc, batch_order(g)) || !fused2_setup<R>(b2, 0, xc, batch_order(g))) return false;
+    const int xc = g->tune.kernel == TETE_KERNEL_FUSED2 ? g->tune.xchunk : 0;
+    if (!fused2_setup<R>(f2, 0, xc, batch_order(g), 0, true) || !fused2_setup<R>(b2, 0, xc, batch_order(g), 0, true))
+        return false;
     it.a2[phase] = f2;
     it.a2[1 - phase] = b2;
+    total2 += f2.nblk;
     return true;
 }
 
@@ -1357,18 +1360,6 @@ tete_status batch_build(tete_batch* b)
         batch_drop_graph(b);   // the captured block launches the other kernel
         b->two = two;
     }
-    BatchMember mem[TETE_MAX_BATCH];
-    int nmem = 0;
-    for (int s = 0; s < TETE_MAX_BATCH && two; ++s) {
-        tete_grid* g = b->slot[s];
-        if (!g) continue;
-        FArgs<R> f2 = fused_args<R>(fields<R>(g, g->cur), fields<R>(g, 1 - g->cur), mats<R>(g), g->geo, (R)g->alpha,
-                                    source(g, g->n));
-        if (!fused2_setup<R>(f2, 0, 1, batch_order(g))) return TETE_ERR_ARG;
-        const int planes = g->geo.nx + 1;
-        mem[nmem++] = {f2.nblk / planes, planes, g->tune.kernel == TETE_KERNEL_FUSED2 ? g->tune.xchunk : 0};
-    }
-    const int c2 = batch_chunk(mem, nmem, b->grid);
     int total = 0, total2 = 0;
     for (int s = 0; s < TETE_MAX_BATCH; ++s) {
         tete_grid* g = b->slot[s];
@@ -1385,22 +1376,14 @@ tete_status batch_build(tete_batch* b)
         H->item[i].a[b->phase] = fwd;
         H->item[i].a[1 - b->phase] = bwd;
         H->offset[i] = total;
-        H->inst2[i] = i;
-        if (two && !batch_two_args<R>(g, H->item[i], b->phase, mem[i].chunk(c2))) return TETE_ERR_ARG;
+        H->offset2[i] = total2;
+        if (two && !batch_two_args<R>(g, H->item[i], b->phase, total2)) return TETE_ERR_ARG;
         H->step[i] = g->n;
         total += fwd.nblk;
         b->seen_n[s] = g->n;
         b->seen_cur[s] = g->cur;
     }
     H->offset[H->ninst] = total;
-    std::sort(H->inst2, H->inst2 + H->ninst, [&](int x, int y) {
-        const int cx = H->item[x].a2[0].xchunk, cy = H->item[y].a2[0].xchunk;
-        return cx != cy ? cx > cy : x < y;
-    });
-    for (int p = 0; p < H->ninst; ++p) {
-        H->offset2[p] = total2;
-        total2 += H->item[H->inst2[p]].a2[0].nblk;
-    }
     H->offset2[H->ninst] = total2;
     H->total = total;
     H->total2 = total2;

@@ -65,14 +65,11 @@ __device__ __forceinline__ double lane_next(double v)
     return __builtin_bit_cast(double, w);
 }
 
-// Place of workgroup b of n in a round of a persistent two-step batch launch.
-__host__ __device__ __forceinline__ int batch_pos(int b, int n, int round) { return round & 1 ? n - 1 - b : b; }
-
 // Logical tile of a workgroup.  Consecutive hardware workgroups are spread
 // round-robin over the eight XCDs; the remap gives each XCD a contiguous range
 // of logical tiles so that neighbouring j-tiles (which share halo rows) run on
 // the same XCD and share its L2.
-__host__ __device__ __forceinline__ int xcd_remap(int b, int n)
+__device__ __forceinline__ int xcd_remap(int b, int n)
 {
     const int nx = 8;
     int x = b % nx, r = b / nx;
@@ -230,8 +227,8 @@ inline ChunkPlan plan_chunks(int64_t tiles, int nplanes, int64_t xmax, int fill,
 }
 
 // Fills the tiling of A: the x-chunk asked for (clipped to xmax planes), or
-// where xchunk is 0 the plan above.  A member of a batch stepped one step at a
-// time shares the rounds with other members' items: as few chunks as possible, but at least 128 items,
+// where xchunk is 0 the plan above.  A member of a batch shares the rounds with
+// other members' items: as few chunks as possible, but at least 128 items,
 // chunks of at least 16 planes, and each within xmax.
 template <typename R>
 inline void set_chunks(FArgs<R>& A, int xchunk, int order, int64_t xmax, int fill, int unroll, bool member)

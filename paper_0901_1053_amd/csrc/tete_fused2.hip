@@ -737,11 +737,10 @@ __global__ __launch_bounds__(TYH * LW) void k_fused2_wit(FArgs<R> A, WitMid<R> w
 }
 
 // Two steps of every active instance of a batch, by a persistent grid, as the
-// single-step batch kernel does it: round w / gridDim.x takes work item w
-// (instance, tile, x-chunk), remapped over the XCDs within the round.  The items
-// come by falling length, so the workgroups take every other round in reverse:
-// who had the longer item gets the shorter one next.  The launch follows `flips`
-// launches and `steps` steps of the current block.
+// single-step batch kernel does it: work item w (instance, tile, x-chunk) is
+// taken by workgroup w mod gridDim.x in round w / gridDim.x, remapped over
+// the XCDs within a round; the launch follows `flips` launches and `steps`
+// steps of the current block.
 template <typename R>
 __global__ __launch_bounds__(Default2<R>::rows * Default2<R>::lw) void k_fused2_batch(const BatchTable<R>* Tg,
                                                                                      int flips, int steps)
@@ -760,16 +759,15 @@ __global__ __launch_bounds__(Default2<R>::rows * Default2<R>::lw) void k_fused2_
     for (int round = 0; round * (int)gridDim.x < total; ++round) {
         const int base = round * (int)gridDim.x;
         const int span = min((int)gridDim.x, total - base);
-        const int pos = batch_pos(blockIdx.x, gridDim.x, round);
-        if (pos >= span) break;
-        const int w = __builtin_amdgcn_readfirstlane(base + xcd_remap(pos, span));
-        int lo = 0, hi = ninst - 1;               // last place whose first item is <= w
+        if ((int)blockIdx.x >= span) break;
+        const int w = __builtin_amdgcn_readfirstlane(base + xcd_remap(blockIdx.x, span));
+        int lo = 0, hi = ninst - 1;               // last instance whose first item is <= w
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
             if (T->offset2[mid] <= w) lo = mid;
             else hi = mid - 1;
         }
-        const int inst = __builtin_amdgcn_readfirstlane(T->inst2[lo]);
+        const int inst = __builtin_amdgcn_readfirstlane(lo);
         FArgs<R> A;
         {
             const CWords src = (CWords)&T->item[inst].a2[parity];
@@ -779,57 +777,12 @@ __global__ __launch_bounds__(Default2<R>::rows * Default2<R>::lw) void k_fused2_
         }
         A.src.n = T->step[inst] + steps;
         Tile t;
-        if (tile_at(A, w - T->offset2[lo], t)) fused2_tile<R, S::rows, S::nb, S::lw, Default2<R>::pd>(A, t, L);
+        if (tile_at(A, w - T->offset2[inst], t)) fused2_tile<R, S::rows, S::nb, S::lw, Default2<R>::pd>(A, t, L);
         __syncthreads();   // the LDS is reused by the next item
     }
 }
 
 }  // namespace
-
-// Longest chunk of a batch's two-step items: of the lengths that cut the longest
-// member into equal chunks, the one with which the busiest of `grid` workgroups
-// has the fewest planes, each item counting its planes and ten of lead-in and
-// drain; the items by falling length, dealt in rounds as k_fused2_batch takes
-// them.  Chunks chosen per member (at least 128 items each) left the busiest
-// workgroup 657 planes on 8 members of 73 x 67 x 219 to 155 x 149 x 910, this rule
-// 554, where the mean is 478.
-int batch_chunk(const BatchMember* m, int nmem, int grid)
-{
-    constexpr int kMax = 1024;
-    int64_t load[kMax], best_cost = 0;
-    int by[TETE_MAX_BATCH], pmax = 1, best = 0;
-    const int n = std::min(grid, kMax);
-    for (int i = 0; i < nmem; ++i) {
-        by[i] = i;
-        pmax = std::max(pmax, m[i].planes);
-    }
-    for (int cut = 1; cut <= pmax; ++cut) {
-        const int c = (pmax + cut - 1) / cut;
-        if (cut > 1 && c == (pmax + cut - 2) / (cut - 1)) continue;
-        std::sort(by, by + nmem, [&](int x, int y) {
-            const int cx = m[x].chunk(c), cy = m[y].chunk(c);
-            return cx != cy ? cx > cy : x < y;
-        });
-        std::fill(load, load + n, 0);
-        int64_t items = 0;
-        for (int i = 0; i < nmem; ++i) {
-            const BatchMember& x = m[by[i]];
-            const int xc = x.chunk(c);
-            for (int p = 0; p < x.planes; p += xc) {
-                const int cost = std::min(xc, x.planes - p) + 10;
-                for (int t = 0; t < x.tiles; ++t, ++items)
-                    load[batch_pos((int)(items % n), n, (int)(items / n & 1))] += cost;
-            }
-        }
-        if (best > 0 && items > 16 * (int64_t)n) break;   // more chunks only add lead-in planes
-        const int64_t cost = *std::max_element(load, load + n);
-        if (best == 0 || cost < best_cost) {
-            best = c;
-            best_cost = cost;
-        }
-    }
-    return best;
-}
 
 template <typename R>
 hipError_t launch_batch_step2(BatchTable<R>* T, int grid, int flips, int steps, hipStream_t s)
@@ -839,7 +792,7 @@ hipError_t launch_batch_step2(BatchTable<R>* T, int grid, int flips, int steps, 
 }
 
 template <typename R>
-bool fused2_setup(FArgs<R>& A, int rows, int xchunk, int order, int lanes)
+bool fused2_setup(FArgs<R>& A, int rows, int xchunk, int order, int lanes, bool member)
 {
     if (rows == 0) rows = Default2<R>::rows;
     if (rows != 16 && !((rows == 24 || rows == 32) && sizeof(R) == 4)) return false;
@@ -852,7 +805,7 @@ bool fused2_setup(FArgs<R>& A, int rows, int xchunk, int order, int lanes)
     const int64_t xmax = ((int64_t(1) << 31) - 1) / plane_bytes - 8;
     if (xmax < 1) return false;
     // planes xs-4 .. xe+7, of which the first and the last few are cheaper
-    set_chunks(A, xchunk, order, xmax, 10, 1, false);
+    set_chunks(A, xchunk, order, xmax, 10, 1, member);
     return true;
 }
 
@@ -1103,7 +1056,7 @@ hipError_t launch_step_fused2(Fields<R> o, Fields<R> nf, Mat<R> M, Geo g, R alph
 
 #define TETE_FUSED2_INST(R)                                                                                    \
     template hipError_t launch_batch_step2<R>(BatchTable<R>*, int, int, int, hipStream_t);                     \
-    template bool fused2_setup<R>(FArgs<R>&, int, int, int, int);                                                 \
+    template bool fused2_setup<R>(FArgs<R>&, int, int, int, int, bool);                                           \
     template hipError_t launch_step_fused2<R>(Fields<R>, Fields<R>, Mat<R>, Geo, R, Src, const WitMid<R>*, int, \
                                               int, int, int, hipStream_t, hipEvent_t*, const int*, int,      \
                                               const EnergyPair*);                                            \

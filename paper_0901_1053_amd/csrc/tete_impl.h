@@ -111,9 +111,7 @@ struct BatchTable {
     int total2;                        // work items of one two-step launch
     int phase;                         // parity of the launches taken so far
     int offset[TETE_MAX_BATCH + 1];    // first work item of each instance (single step)
-    // two-step kernel: instances by falling chunk length, first work item of each
-    int inst2[TETE_MAX_BATCH];
-    int offset2[TETE_MAX_BATCH + 1];
+    int offset2[TETE_MAX_BATCH + 1];   // first work item of each instance (two-step kernel)
     int64_t step[TETE_MAX_BATCH];      // step index n of each instance
     BatchItem<R> item[TETE_MAX_BATCH];
 };
@@ -178,7 +176,8 @@ int fused_default_rows(int real_bytes);
 bool fused2_fits(Geo g, int real_bytes);
 // rows: 0 (default), 16, or 24 or 32 (FP32 only: rows of 32 lanes).
 template <typename R>
-bool fused2_setup(FArgs<R>& A, int rows, int xchunk, int order, int lanes = 0);
+// member: the grid steps as a member of a batch
+bool fused2_setup(FArgs<R>& A, int rows, int xchunk, int order, int lanes = 0, bool member = false);
 // Energy samples taken by a two-step launch: want bit 0 the energy of its
 // input y^n, bit 1 that of y^{n+1}; written to out[0], out[1] (only the ones
 // wanted, in that order); part: cap pairs of FP64 partial sums.
@@ -234,19 +233,6 @@ hipError_t launch_step_yee2(Fields<R> oldf, Fields<R> newf, Mat<R> mat, Geo g, R
 // steps of the current block
 template <typename R>
 hipError_t launch_batch_step(BatchTable<R>* T, int rows, int depth, int grid, int flips, int steps, hipStream_t s);
-// Two-step items of one batch member: tiles, planes, and the chunk length its
-// tuning asks for (or 0).
-struct BatchMember {
-    int tiles, planes, fixed;
-    // planes per chunk where the batch's longest chunk is c: equal chunks
-    int chunk(int c) const
-    {
-        if (fixed > 0) return fixed < planes ? fixed : planes;
-        const int n = (planes + c - 1) / c;
-        return (planes + n - 1) / n;
-    }
-};
-int batch_chunk(const BatchMember* m, int nmem, int grid);
 // Two steps of every instance of a batch (tete_fused2.hip)
 template <typename R>
 hipError_t launch_batch_step2(BatchTable<R>* T, int grid, int flips, int steps, hipStream_t s);
