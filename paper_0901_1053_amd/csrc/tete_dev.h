@@ -228,7 +228,8 @@ inline ChunkPlan plan_chunks(int64_t tiles, int nplanes, int64_t xmax, int fill,
 
 // Fills the tiling of A: the x-chunk asked for (clipped to xmax planes), or
 // where xchunk is 0 the plan above.  A member of a batch shares the rounds with
-// other members' items: as few chunks as possible, but at least 128 items,
+// other members' items: as few chunks of at most xmax planes as possible, but at
+// least 128 items,
 // chunks of at least 16 planes, and each within xmax.
 template <typename R>
 inline void set_chunks(FArgs<R>& A, int xchunk, int order, int64_t xmax, int fill, int unroll, bool member)

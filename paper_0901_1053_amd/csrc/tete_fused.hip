@@ -404,7 +404,7 @@ bool fused_setup(FArgs<R>& A, int rows, int xchunk, int order, bool member, bool
     const int TY = rows - 4, KT = owned_k(mat ? mat_lanes(sizeof(R)) : 64);
     A.nyt = (A.g.ny + 1 + TY - 1) / TY;
     A.nzt = (A.g.nz + 1 + KT - 1) / KT;
-    // every buffer range must stay below 2^31 bytes: (xchunk + 4) planes
+    // chunks of less than 2^31 bytes with their halo; longer ones gain nothing
     const int64_t plane_bytes = (int64_t)A.g.sp * sizeof(R);
     const int64_t xmax = ((int64_t(1) << 31) - 1) / plane_bytes - 4;
     if (xmax < 1) return false;

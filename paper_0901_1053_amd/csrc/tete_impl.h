@@ -175,9 +175,9 @@ int fused_default_rows(int real_bytes);
 // blocked; xchunk and order as for the single step.
 bool fused2_fits(Geo g, int real_bytes);
 // rows: 0 (default), 16, or 24 or 32 (FP32 only: rows of 32 lanes).
+// member: planes per chunk at most as a member of a batch (0: no member).
 template <typename R>
-// member: the grid steps as a member of a batch
-bool fused2_setup(FArgs<R>& A, int rows, int xchunk, int order, int lanes = 0, bool member = false);
+bool fused2_setup(FArgs<R>& A, int rows, int xchunk, int order, int lanes = 0, int member = 0);
 // Energy samples taken by a two-step launch: want bit 0 the energy of its
 // input y^n, bit 1 that of y^{n+1}; written to out[0], out[1] (only the ones
 // wanted, in that order); part: cap pairs of FP64 partial sums.

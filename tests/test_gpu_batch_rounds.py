@@ -1,7 +1,7 @@
-"""Two-step batch launches of several rounds of workgroups, dealt by falling
-chunk length and every other round in reverse: members of uneven length along x,
-a last round that is full, nearly empty or the only one, and a member with its
-own chunk length, each against the member stepped alone, bitwise."""
+"""Two-step batch launches of several rounds of workgroups: members of uneven
+length along x, a last round that is full, nearly empty or the only one, a member
+with its own chunk length, and batches on both sides of the chunk length's rule,
+each against the member stepped alone, bitwise."""
 import numpy as np
 import pytest
 
@@ -30,6 +30,8 @@ def _grid(shape, precision, seed, xchunk):
     ("fp32", 95, 595, (3, 30, 7, 19, 11, 24, 2, 15, 9), 0), ("fp64", 95, 275, (3, 30, 7, 19, 11, 24, 2, 15, 9), 0),
     ("fp32", 95, 595, (17, 5, 12), 4), ("fp32", 79, 959, (8, 8, 8, 8), 0), ("fp32", 9, 257 * 60 - 1, (6,), 0),
     ("fp64", 9, 40, (70, 3), 0),
+    # 2040 and 2060 tiles: chunks of at most 48 and of at most 24 planes
+    ("fp32", 9, 1020 * 60 - 1, (50, 3), 0), ("fp32", 9, 1030 * 60 - 1, (50, 3), 0),
 ])
 def test_rounds_equal_alone(precision, ny, nz, nxs, xchunk):
     print("batch rounds", precision, ny, nz, nxs, flush=True)
