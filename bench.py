@@ -568,7 +568,7 @@ def materials_section(case, precision, explicit_ms_per_step, steps=6):
 def skip_section(case, precision, explicit_ms_per_step, witness_ms=None, steps=8, xchunks=(0, 257, 128, 64, 16)):
     """The two-step kernel leaving out tiles that lie wholly in PEC
     (skip_static) on the large workload, for the default x-chunk of such grids
-    (32 planes), the full step's (257) and a few others (short chunks find
+    (chosen from the active tiles), the full step's (257) and a few others (short chunks find
     more tiles wholly in the metal block around the pipe, each chunk re-reads
     seven halo planes): kernel time per step, tiles left out, and the ratio
     to the full two-step step.  Fields and wake are those
@@ -589,7 +589,7 @@ def skip_section(case, precision, explicit_ms_per_step, witness_ms=None, steps=8
         G.set_timing(0)
         ms = (a + b) / n
         sk, tot = G.static_tiles()
-        rows.append({"xchunk": xc or "default (32)", "tiles": tot, "static_tiles": sk,
+        rows.append({"xchunk": xc or "default", "tiles": tot, "static_tiles": sk,
                      "ms_per_step": round(ms, 3),
                      "speedup_vs_full_step": round(explicit_ms_per_step / ms, 2) if explicit_ms_per_step else None})
     # the same grid with the witness node of the witness timing (32 cells off

@@ -93,7 +93,9 @@ enum {
                                  * Two-step and fused single-step launches take only
                                  * the other tiles (the two-kernel step of
                                  * TETE_KERNEL_SPLIT and batches take all); with tuning
-                                 * x-chunk 0 these launches use chunks of 32 planes.
+                                 * x-chunk 0 two-step launches take the chunk length
+                                 * whose active tiles run in the fewest planes, single
+                                 * steps chunks of 32 planes.
                                  * The tile list is built, and the stream synchronised,
                                  * at the first such launch after the codes or the
                                  * tiling (rows, x-chunk, order; witness set or not)
@@ -449,7 +451,7 @@ tete_status tete_charges(tete_grid* g, double* max_res_e, double* max_abs_h);
  * per workgroup of either fused kernel (0: chosen from the grid size so that the
  * workgroups fill whole rounds of 256, one per CU).
  * depth: x-planes of old data the fused single step prefetches ahead, 1..3
- * (0: 2; the two-step kernel prefetches one).  order: order in which the
+ * (0: 2; FP64 takes 2 for 3; the two-step kernel prefetches one).  order: order in which the
  * fused kernels' tiles are scheduled: 1 (j-tiles first), 2 (k-tiles first),
  * 3, 4, 5 or 6 (blocks of 8 k-tiles by 4 j-tiles, 16 by 2, 4 by 8 or 2 by
  * 16); 0: 2.  tete_set_materials

@@ -1025,7 +1025,7 @@ hipError_t launch_step_fused2(Fields<R> o, Fields<R> nf, Mat<R> M, Geo g, R alph
     }
     if (!done && A.cls) {
         // materials by class: one shape per field type (FP32: 24 rows of 32
-        // lanes, two planes ahead, 167 VGPRs; FP64: 16 rows of 32 lanes, one
+        // lanes, two planes ahead, 165 VGPRs; FP64: 16 rows of 32 lanes, one
         // plane ahead), whatever the tuning asks
         constexpr int CR = sizeof(R) == 4 ? 24 : 16, CP = sizeof(R) == 4 ? 2 : 1;
         if (!act) k_fused2_cls<R, CR, 32, CP><<<A.nblk, CR * 32, 0, s>>>(A, nullptr);
