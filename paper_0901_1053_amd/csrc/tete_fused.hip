@@ -461,9 +461,10 @@ bool fused_fits(Geo g, int real_bytes)
 
 int64_t fused_tile_cap(Geo g)
 {
-    // no more than with 8 rows (12-row tiles) by 30 entries (32 lanes) over tiles
-    // of single planes
-    return (int64_t)(g.nx + 1) * ((g.ny + 1 + 7) / 8) * ((g.nz + 1 + 29) / 30);
+    // the smallest owned shapes, 8 rows (12-row tiles) by 62 entries and 20 rows by
+    // 30 (FP64 materials), over tiles of single planes
+    auto tiles = [&](int ty, int kt) { return (int64_t)((g.ny + ty) / ty) * ((g.nz + kt) / kt); };
+    return (int64_t)(g.nx + 1) * std::max(tiles(8, owned_k(64)), tiles(20, owned_k(32)));
 }
 
 template <typename R>
