@@ -449,7 +449,8 @@ tete_status tete_charges(tete_grid* g, double* max_res_e, double* max_abs_h);
  * FP32, of 32 lanes for FP64, the default) or 32 (FP32: 32 rows of 32
  * lanes); 32 leaves the single step at its default.  xchunk: x-planes
  * per workgroup of either fused kernel (0: chosen from the grid size so that the
- * workgroups fill whole rounds of 256, one per CU).
+ * workgroups fill whole rounds of 256, one per CU; at most 48 or 24 in the
+ * two-step launches of a batch).
  * depth: x-planes of old data the fused single step prefetches ahead, 1..3
  * (0: 2; FP64 takes 2 for 3; the two-step kernel prefetches one).  order: order in which the
  * fused kernels' tiles are scheduled: 1 (j-tiles first), 2 (k-tiles first),

@@ -1334,7 +1334,8 @@ int batch_order(const tete_grid* g) { return g->tune.order != 0 ? g->tune.order 
 // memory again; short chunks keep them together.  ms for 16 steps with chunks of up
 // to 1000, 64, 48, 32, 24 planes: 64 members of 64 x 64 x 256 to 192 x 192 x 1024
 // (25 rounds of tiles) 152, 141, 119, 116, 109; 8 of them 14.2, 13.6, 13.3, 13.7,
-// 13.9; chunks chosen per member alone 145 and 13.6.
+// 13.9; chunks chosen per member alone 145 and 13.6.  A longer chunk that a
+// member's tuning asks for (timed in a smaller batch, say) is cut to that.
 int batch_chunk(int64_t tiles, int grid) { return tiles > 8 * (int64_t)grid ? 24 : 48; }
 
 // Two-step arguments of one member for both parities, chunks of at most cmax planes.
@@ -1345,7 +1346,7 @@ bool batch_two_args(tete_grid* g, BatchItem<R>& it, int phase, int cmax, int& to
                                 source(g, g->n));
     FArgs<R> b2 = fused_args<R>(fields<R>(g, 1 - g->cur), fields<R>(g, g->cur), mats<R>(g), g->geo, (R)g->alpha,
                                 source(g, g->n));
-    const int xc = g->tune.kernel == TETE_KERNEL_FUSED2 ? g->tune.xchunk : 0;
+    const int xc = g->tune.kernel == TETE_KERNEL_FUSED2 ? std::min(g->tune.xchunk, cmax) : 0;
     if (!fused2_setup<R>(f2, 0, xc, batch_order(g), 0, cmax) || !fused2_setup<R>(b2, 0, xc, batch_order(g), 0, cmax))
         return false;
     it.a2[phase] = f2;
