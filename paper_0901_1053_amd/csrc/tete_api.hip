@@ -114,7 +114,7 @@ struct tete_grid {
     int yee;           // Yee's scheme (7) instead of (23)
     int implicit;      // the implicit scheme (16) instead of (23)
     int imp_lists;     // work-item lists built for the current geometry
-    int imp_ne, imp_nh;
+    int imp_ne, imp_nh, imp_xc;
     void* f[2][6];
     int cur;           // f[cur] holds y^n
     uint8_t* code;
@@ -267,6 +267,7 @@ ImpWork<R> imp_work(tete_grid* g)
     w.le = (const int*)(g->ws + g->L.imp_le);
     w.lh = (const int*)(g->ws + g->L.imp_lh);
     w.ne = g->imp_ne;
+    w.xc = g->imp_xc;
     w.nh = g->imp_nh;
     return w;
 }
@@ -438,7 +439,7 @@ tete_status do_steps(tete_grid* g, int64_t nsteps)
         }
         if (g->implicit && !g->imp_lists) {   // once per geometry
             HIPCHK(implicit_build_lists<R>(M, g->geo, (int*)(g->ws + g->L.imp_le), (int*)(g->ws + g->L.imp_lh),
-                                           &g->imp_ne, &g->imp_nh, g->stream));
+                                           &g->imp_ne, &g->imp_nh, &g->imp_xc, g->stream));
             g->imp_lists = 1;
         }
         if (g->implicit)

@@ -310,11 +310,13 @@ struct ImpWork {
     const int* le;   // work items of the solves that hold free e_z edges (ne of them)
     const int* lh;   // work items that hold coupled h_z rows (nh)
     int ne, nh;
+    int xc;          // planes per chunk of the items
 };
 // Work items of the implicit scheme's plane solves that hold unknowns, for the
-// current geometry (le, lh: np ints each).  Synchronises the stream.
+// current geometry (le, lh: np ints each), and their planes per chunk *xc.
+// Synchronises the stream.
 template <typename R>
-hipError_t implicit_build_lists(Mat<R> M, Geo g, int* le, int* lh, int* ne, int* nh, hipStream_t s);
+hipError_t implicit_build_lists(Mat<R> M, Geo g, int* le, int* lh, int* ne, int* nh, int* xc, hipStream_t s);
 // One step of the implicit scheme (16) (tete_implicit.hip); ev[0..2] around
 // the two half steps if not NULL
 template <typename R>
