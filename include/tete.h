@@ -114,8 +114,10 @@ enum {
                                  * bounds [1, 1 + alpha^2 (4/dx^2 + 4/dy^2)] (to 1e-17 in
                                  * FP64, 1e-8 in FP32 relative to the first iterate's
                                  * error), over lists of the work items (tiles of rows
-                                 * over chunks of planes) that hold unknowns, which the
-                                 * first tete_step after tete_set_pec_cells builds
+                                 * over chunks of planes) that hold unknowns or, where
+                                 * these leave the chip idle, lists of the systems'
+                                 * rows; the
+                                 * first tete_step after tete_set_pec_cells builds them
                                  * (that call synchronises the stream; the workspace
                                  * holds two int32 lists of np entries).  Stable for
                                  * cdt <= dz with any transverse

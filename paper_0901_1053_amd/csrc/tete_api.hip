@@ -24,7 +24,7 @@ size_t up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
     size_t lam, wacc, wit, wmid, partial, epart, scal, pidx, eser, pser, code, field[12], mat[6], imp[4], imp_le, imp_lh,
-        skip[2], skip_act[2], cls, ctab, craw, total;
+        imp_cnt, skip[2], skip_act[2], cls, ctab, craw, total;
 };
 
 int64_t series_cap(const tete_grid_desc* d) { return d->max_series > 0 ? d->max_series : 4096; }
@@ -67,10 +67,11 @@ bool make_layout(const tete_grid_desc* d, Layout* L)
         if (d->flags & TETE_F_IMPLICIT) { L->imp[c] = o; o = up(o + rb * (size_t)np); }
         else L->imp[c] = 0;
     }
-    L->imp_le = L->imp_lh = 0;
-    if (d->flags & TETE_F_IMPLICIT) {      // work-item lists of the plane solves
+    L->imp_le = L->imp_lh = L->imp_cnt = 0;
+    if (d->flags & TETE_F_IMPLICIT) {      // work-item or row lists of the plane solves, and their chunk counts
         L->imp_le = o;  o = up(o + sizeof(int) * (size_t)np);
         L->imp_lh = o;  o = up(o + sizeof(int) * (size_t)np);
+        L->imp_cnt = o; o = up(o + sizeof(int) * 2 * (size_t)implicit_list_chunks(np));
     }
     L->skip[0] = L->skip[1] = L->skip_act[0] = L->skip_act[1] = 0;
     if (d->flags & TETE_F_SKIP_STATIC) {   // static-tile table and active-tile list of each tiling kind
@@ -113,7 +114,7 @@ struct tete_grid {
     int fp32;
     int yee;           // Yee's scheme (7) instead of (23)
     int implicit;      // the implicit scheme (16) instead of (23)
-    int imp_lists;     // work-item lists built for the current geometry
+    int imp_lists;     // lists of the plane solves built for the current geometry
     int imp_ne, imp_nh, imp_xc;
     void* f[2][6];
     int cur;           // f[cur] holds y^n
@@ -438,8 +439,10 @@ tete_status do_steps(tete_grid* g, int64_t nsteps)
             continue;
         }
         if (g->implicit && !g->imp_lists) {   // once per geometry
-            HIPCHK(implicit_build_lists<R>(M, g->geo, (int*)(g->ws + g->L.imp_le), (int*)(g->ws + g->L.imp_lh),
-                                           &g->imp_ne, &g->imp_nh, &g->imp_xc, g->stream));
+            const int it = implicit_iters(g->geo, g->d.dx, g->d.dy, (double)(R)g->alpha, g->fp32, nullptr);
+            HIPCHK(implicit_build_lists<R>(M, g->geo, it, imp_work<R>(g), (int*)(g->ws + g->L.imp_cnt),
+                                           (int*)(g->ws + g->L.imp_le), (int*)(g->ws + g->L.imp_lh), &g->imp_ne,
+                                           &g->imp_nh, &g->imp_xc, g->stream));
             g->imp_lists = 1;
         }
         if (g->implicit)

@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 
 #include "tete_impl.h"
+#include "tete_plan.h"
 
 namespace tete {
 namespace {
@@ -83,7 +84,6 @@ __device__ __forceinline__ int xcd_remap(int b, int n)
 // an eighth of it per XCD.  With the range split over the whole launch the
 // eight XCDs worked in eight distant bands: 4.14 against 3.90 ms per step on
 // the 512 x 512 x 2048 grid in FP32 (k-tiles first), 7.44 against 7.00 ms in FP64.
-constexpr int kRound = 256;   // workgroups running at a time: one per CU
 __device__ __forceinline__ int xcd_rounds(int b, int n)
 {
     const int r0 = b / kRound * kRound;

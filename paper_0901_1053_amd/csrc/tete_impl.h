@@ -306,17 +306,21 @@ template <typename R>
 struct ImpWork {
     R* b;        // right-hand side
     R* r;        // residual
-    R* d[2];     // Chebyshev directions
+    R* d[2];     // Chebyshev directions; with lists of rows zero between solves
     const int* le;   // work items of the solves that hold free e_z edges (ne of them)
     const int* lh;   // work items that hold coupled h_z rows (nh)
     int ne, nh;
-    int xc;          // planes per chunk of the items
+    int xc;          // planes per chunk of the items; 0: le and lh list rows, one iteration per launch
 };
-// Work items of the implicit scheme's plane solves that hold unknowns, for the
-// current geometry (le, lh: np ints each), and their planes per chunk *xc.
+// Work items of the implicit scheme's plane solves (iters iterations each) that
+// hold unknowns, for the current geometry (le, lh: np ints each), and their planes
+// per chunk *xc; or, with *xc = 0, ascending array indices of the unknowns (free
+// e_z edges, coupled h_z rows).  cnt holds 2 ints per chunk (implicit_list_chunks).
 // Synchronises the stream.
+int implicit_list_chunks(int64_t np);
 template <typename R>
-hipError_t implicit_build_lists(Mat<R> M, Geo g, int* le, int* lh, int* ne, int* nh, int* xc, hipStream_t s);
+hipError_t implicit_build_lists(Mat<R> M, Geo g, int iters, const ImpWork<R>& wk, int* cnt, int* le, int* lh, int* ne,
+                                int* nh, int* xc, hipStream_t s);
 // One step of the implicit scheme (16) (tete_implicit.hip); ev[0..2] around
 // the two half steps if not NULL
 template <typename R>

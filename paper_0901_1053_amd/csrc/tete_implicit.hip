@@ -12,7 +12,8 @@
 // rate: a fixed number of iterations, no inner products, no reductions, and the
 // same result for any launch shape.  The right-hand sides and the back
 // substitution are grid-stride passes over the entries, z fastest; the solves
-// take several iterations per pass (below).
+// take several iterations per pass over work items, or, where those leave the chip
+// idle, one per launch over lists of rows (implicit_passes).
 
 #include <math.h>
 
@@ -25,6 +26,7 @@ namespace tete {
 namespace {
 
 constexpr int TBI = 256;
+constexpr int kListChunk = 8192;   // entries counted and listed by one block
 
 struct IGeo {
     int nx, ny, nz, sz, sp, np;
@@ -138,6 +140,168 @@ __global__ void k_imp_b_u(Fields<R> w, R* B, const uint8_t* code, IGeo g, ICoef<
         const R kz = kap_z(code, g, c, i, j, k);
         if (kz == (R)0) continue;
         B[idx] += c.a * kz * ((val(rhx, g, i, j - 1, k) - rhx[idx]) - (val(rhy, g, i - 1, j, k) - rhy[idx]));
+    }
+}
+
+// One iteration per launch, over lists of the rows that hold unknowns.
+
+// (A x) of the e_z system at a free entry: x + alpha^2 kappa_z r0 x
+template <typename R>
+__device__ __forceinline__ R apply_e(const R* x, const uint8_t* code, const IGeo& g, const ICoef<R>& c, int i, int j,
+                                     int k, int idx, R kz)
+{
+    const R x0 = x[idx];
+    const R r = mu_x(g, c, i, j - 1, k) * (x0 - val(x, g, i, j - 1, k)) - mu_x(g, c, i, j, k) * (val(x, g, i, j + 1, k) - x0) +
+                mu_y(g, c, i - 1, j, k) * (x0 - val(x, g, i - 1, j, k)) - mu_y(g, c, i, j, k) * (val(x, g, i + 1, j, k) - x0);
+    return x0 + c.a * c.a * kz * r;
+}
+
+// (A x) of the h_z system at an in-range entry: x + alpha^2 mu_z r1 x
+template <typename R>
+__device__ __forceinline__ R apply_h(const R* x, const uint8_t* code, const IGeo& g, const ICoef<R>& c, int i, int j,
+                                     int k, int idx, R mz)
+{
+    const R x0 = x[idx];
+    const R r = kap_x(code, g, c, i, j + 1, k) * (x0 - val(x, g, i, j + 1, k)) -
+                kap_x(code, g, c, i, j, k) * (val(x, g, i, j - 1, k) - x0) +
+                kap_y(code, g, c, i + 1, j, k) * (x0 - val(x, g, i + 1, j, k)) -
+                kap_y(code, g, c, i, j, k) * (val(x, g, i - 1, j, k) - x0);
+    return x0 + c.a * c.a * mz * r;
+}
+
+// An h_z row whose four surrounding e edges are all PEC (inside the metal) is
+// the identity and decoupled from every other unknown: its neighbours reach it
+// only through one of those edges, whose kappa is zero.  Its solution is b.
+template <typename R>
+__device__ __forceinline__ bool h_coupled(const uint8_t* code, const IGeo& g, const ICoef<R>& c, int i, int j, int k)
+{
+    return kap_x(code, g, c, i, j + 1, k) != (R)0 || kap_x(code, g, c, i, j, k) != (R)0 ||
+           kap_y(code, g, c, i + 1, j, k) != (R)0 || kap_y(code, g, c, i, j, k) != (R)0;
+}
+
+// Row lists (built once per geometry, ascending): the free e_z edges and the
+// coupled h_z rows.  Chunk b of `chunk` entries is counted by block b, the
+// host turns the counts into offsets, and block b writes its chunk's rows
+// in order (wave ballots and a scan over the block's waves).
+template <typename R>
+__device__ __forceinline__ void row_flags(const uint8_t* code, const IGeo& g, const ICoef<R>& c, int idx, bool& fe,
+                                          bool& fh)
+{
+    int i, j, k;
+    dec(g, idx, i, j, k);
+    fe = kap_z(code, g, c, i, j, k) != (R)0;
+    fh = mu_z(g, c, i, j, k) != (R)0 && h_coupled(code, g, c, i, j, k);
+}
+
+template <typename R>
+__global__ __launch_bounds__(TBI) void k_list_count(const uint8_t* code, IGeo g, ICoef<R> c, int chunk, int* cnt)
+{
+    __shared__ int se[TBI], sh[TBI];
+    const int lo = blockIdx.x * chunk, hi = min(lo + chunk, g.np);
+    int ne = 0, nh = 0;
+    for (int idx = lo + (int)threadIdx.x; idx < hi; idx += TBI) {
+        bool fe, fh;
+        row_flags(code, g, c, idx, fe, fh);
+        ne += fe;
+        nh += fh;
+    }
+    se[threadIdx.x] = ne;
+    sh[threadIdx.x] = nh;
+    __syncthreads();
+    for (int w = TBI / 2; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) {
+            se[threadIdx.x] += se[threadIdx.x + w];
+            sh[threadIdx.x] += sh[threadIdx.x + w];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        cnt[2 * blockIdx.x] = se[0];
+        cnt[2 * blockIdx.x + 1] = sh[0];
+    }
+}
+
+template <typename R>
+__global__ __launch_bounds__(TBI) void k_list_write(const uint8_t* code, IGeo g, ICoef<R> c, int chunk,
+                                                    const int* off, int* le, int* lh)
+{
+    constexpr int NW = TBI / 64;
+    __shared__ int we[NW], wh[NW];
+    const int lo = blockIdx.x * chunk, hi = min(lo + chunk, g.np);
+    const int wave = threadIdx.x / 64;
+    const unsigned long long below = __lanemask_lt();
+    int oe = off[2 * blockIdx.x], oh = off[2 * blockIdx.x + 1];
+    for (int base = lo; base < hi; base += TBI) {       // same trip count for every thread
+        const int idx = base + (int)threadIdx.x;
+        bool fe = false, fh = false;
+        if (idx < hi) row_flags(code, g, c, idx, fe, fh);
+        const unsigned long long me = __ballot(fe), mh = __ballot(fh);
+        if ((threadIdx.x & 63) == 0) {
+            we[wave] = __popcll(me);
+            wh[wave] = __popcll(mh);
+        }
+        __syncthreads();
+        int pe = oe, ph = oh, te = 0, th = 0;
+        for (int w = 0; w < NW; ++w) {
+            if (w < wave) {
+                pe += we[w];
+                ph += wh[w];
+            }
+            te += we[w];
+            th += wh[w];
+        }
+        if (fe) le[pe + __popcll(me & below)] = idx;
+        if (fh) lh[ph + __popcll(mh & below)] = idx;
+        oe += te;
+        oh += th;
+        __syncthreads();                                 // the counts are rewritten next round
+    }
+}
+
+// Chebyshev start on the rows of the list: r = b - A x, d = r / theta.  Rows
+// outside the list (PEC e_z edges, h_z outside its range or inside the
+// metal) are not unknowns: their x is fixed (0, or h_z^n, which equals b on an
+// identity row) and their directions are zero in both buffers of the
+// ping-pong pair, which the e_z and h_z solves share: every solve zeroes its
+// own rows in both buffers in its last iteration.
+template <typename R, bool H>
+__global__ void k_cheb_init(const R* X, const R* B, R* Rr, R* D, const int* list, int n, const uint8_t* code, IGeo g,
+                            ICoef<R> c, R inv_theta)
+{
+    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
+        const int idx = list[t];
+        int i, j, k;
+        dec(g, idx, i, j, k);
+        const R s = H ? mu_z(g, c, i, j, k) : kap_z(code, g, c, i, j, k);
+        const R ax = H ? apply_h(X, code, g, c, i, j, k, idx, s) : apply_e(X, code, g, c, i, j, k, idx, s);
+        const R r = B[idx] - ax;
+        Rr[idx] = r;
+        D[idx] = r * inv_theta;
+    }
+}
+
+// One Chebyshev step: x += d; unless last: r -= A d, d' = c1 d + c2 r; in the
+// last step both direction buffers are cleared on the list's rows
+template <typename R, bool H>
+__global__ void k_cheb_iter(R* X, R* Rr, R* D, R* Dn, const int* list, int n, const uint8_t* code, IGeo g, ICoef<R> c,
+                            R c1, R c2, int last)
+{
+    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
+        const int idx = list[t];
+        int i, j, k;
+        dec(g, idx, i, j, k);
+        const R s = H ? mu_z(g, c, i, j, k) : kap_z(code, g, c, i, j, k);
+        const R d = D[idx];
+        X[idx] += d;
+        if (last) {   // no thread reads the directions any more
+            D[idx] = (R)0;
+            Dn[idx] = (R)0;
+            continue;
+        }
+        const R ad = H ? apply_h(D, code, g, c, i, j, k, idx, s) : apply_e(D, code, g, c, i, j, k, idx, s);
+        const R r = Rr[idx] - ad;
+        Rr[idx] = r;
+        Dn[idx] = c1 * d + c2 * r;
     }
 }
 
@@ -371,30 +535,34 @@ __global__ __launch_bounds__(64 * kChebWaves) void k_cheb_pass(ChebArgs<R> A)
     for (int p = pa; p <= pe; ++p) plane(p);
 }
 
-// Which work items hold unknowns: act[2 it] for the e_z system, act[2 it + 1]
-// for h_z (whose unknowns touch a free e_x or e_y edge).  One workgroup per item.
+// Work items: act[2 it] counts the unknowns of the e_z system, act[2 it + 1] is 1
+// where the item holds some of h_z (which touch a free e_x or e_y edge), else 0.
+// One workgroup per item.
 __global__ __launch_bounds__(TBI) void k_cheb_active(const uint8_t* code, IGeo g, ChebTiles T, int own, int* act)
 {
-    __shared__ int any[2];
+    __shared__ int ne, nh;
     const int it = blockIdx.x;
     const int tz = it % T.nzt, ty = it / T.nzt % T.nyt, cx = it / (T.nzt * T.nyt);
-    if (threadIdx.x < 2) any[threadIdx.x] = 0;
+    if (threadIdx.x == 0) ne = nh = 0;
     __syncthreads();
     const int k0 = tz * T.kt, nk = min(T.kt, g.nz + 1 - k0);
     // an h_z row's e edges reach one row and one plane further
     const int ja = ty * own, nj = min(own + 1, g.ny + 1 - ja), xs = cx * T.xc, nx = min(T.xc + 1, g.nx + 1 - xs);
-    uint32_t f = 0;
+    int fe = 0, fh = 0;
     for (int jx = threadIdx.x / 64; jx < nj * nx; jx += TBI / 64) {
         const int j = jx % nj, i = jx / nj, kk = threadIdx.x & 63;
         if (kk >= nk) continue;
         const uint32_t free = ~(uint32_t)code[k0 + kk + g.sz * (ja + j) + g.sp * (xs + i)];
-        if ((free & 4u) && j < own && i < T.xc) f |= 1u;
-        if (free & 3u) f |= 2u;
+        if ((free & 4u) && j < own && i < T.xc) ++fe;
+        if (free & 3u) fh = 1;
     }
-    if (f & 1u) any[0] = 1;
-    if (f & 2u) any[1] = 1;
+    if (fe) atomicAdd(&ne, fe);
+    if (fh) atomicOr(&nh, 1);
     __syncthreads();
-    if (threadIdx.x < 2) act[2 * it + threadIdx.x] = any[threadIdx.x];
+    if (threadIdx.x == 0) {
+        act[2 * it] = ne;
+        act[2 * it + 1] = nh;
+    }
 }
 
 // h_x = r_hx - alpha mu_x P_y e_z, h_y = r_hy + alpha mu_y P_x e_z (new e_z);
@@ -524,6 +692,26 @@ ChebTiles cheb_tiles(const IGeo& g, int own, int stages, int xc = 0)
     return T;
 }
 
+// x of one system, which holds the iterate to start from, one iteration per launch
+// over the list of its rows.
+template <typename R, bool H>
+hipError_t cheb_solve_rows(R* x, const ImpWork<R>& wk, const uint8_t* code, const IGeo& g, const ICoef<R>& c,
+                           const Cheb& p, int iters, hipStream_t s)
+{
+    const int* list = H ? wk.lh : wk.le;
+    const int n = H ? wk.nh : wk.ne;
+    if (n == 0) return hipSuccess;   // no unknowns: x stays as set
+    const int nb = iblocks(n);
+    k_cheb_init<R, H><<<nb, TBI, 0, s>>>(x, wk.b, wk.r, wk.d[0], list, n, code, g, c, (R)p.inv_theta);
+    for (int t = 0; t < iters; ++t) {
+        const bool last = t == iters - 1;
+        const R c1 = last ? (R)0 : (R)p.c1[t], c2 = last ? (R)0 : (R)p.c2[t];
+        k_cheb_iter<R, H><<<nb, TBI, 0, s>>>(x, wk.r, wk.d[t & 1], wk.d[(t + 1) & 1], list, n, code, g, c, c1, c2,
+                                             last);
+    }
+    return hipGetLastError();
+}
+
 // x of one system: iters iterations from x0 with right-hand side b.  The start
 // (r = b - A x0, d = r / theta) and iters - 1 iterations (x += d, r -= A d, d' =
 // c1 d + c2 r) are the stages, shared evenly among the passes; the last x += d
@@ -534,6 +722,7 @@ template <typename R, bool H>
 hipError_t cheb_solve(const R* x0, R* x, const ImpWork<R>& wk, const uint8_t* code, const IGeo& g, const ICoef<R>& c,
                       const Cheb& p, int iters, hipStream_t s)
 {
+    if (wk.xc == 0) return cheb_solve_rows<R, H>(x, wk, code, g, c, p, iters, s);   // x holds x0
     constexpr int NS = kStages<R>;
     ChebArgs<R> A;
     const int items = H ? wk.nh : wk.ne;
@@ -589,17 +778,55 @@ int implicit_iters(const Geo& g, double dx, double dy, double alpha, int fp32, d
     return std::max(1, std::min(n, 10000));
 }
 
+int implicit_list_chunks(int64_t np) { return (int)((np + kListChunk - 1) / kListChunk); }
+
+// Lists of rows for one iteration per launch: free e_z edges and coupled h_z rows.
+// The directions of all other rows have to be zero, whatever the solves before left.
 template <typename R>
-hipError_t implicit_build_lists(Mat<R> M, Geo geo, int* le, int* lh, int* ne, int* nh, int* xc, hipStream_t s)
+hipError_t build_row_lists(const Mat<R>& M, const IGeo& g, const ImpWork<R>& wk, int* cnt, int* le, int* lh, int* ne,
+                           int* nh, hipStream_t s)
+{
+    const ICoef<R> c{M.k[0], M.k[1], M.k[2], M.m[0], M.m[1], M.m[2], (R)0, (R)0};
+    const int nch = implicit_list_chunks(g.np);
+    hipError_t e;
+    for (int q = 0; q < 2; ++q)
+        if ((e = launch_zero_bytes(wk.d[q], sizeof(R) * (size_t)g.np, s)) != hipSuccess) return e;
+    k_list_count<R><<<nch, TBI, 0, s>>>(M.code, g, c, kListChunk, cnt);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    std::vector<int> h(2 * (size_t)nch);
+    if ((e = hipMemcpyAsync(h.data(), cnt, sizeof(int) * h.size(), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
+    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
+    int64_t te = 0, th = 0;                      // exclusive scan of the chunk counts
+    for (int b = 0; b < nch; ++b) {
+        const int ce = h[2 * b], chh = h[2 * b + 1];
+        h[2 * b] = (int)te;
+        h[2 * b + 1] = (int)th;
+        te += ce;
+        th += chh;
+    }
+    if (te > g.np || th > g.np) return hipErrorInvalidValue;
+    if ((e = hipMemcpyAsync(cnt, h.data(), sizeof(int) * h.size(), hipMemcpyHostToDevice, s)) != hipSuccess) return e;
+    k_list_write<R><<<nch, TBI, 0, s>>>(M.code, g, c, kListChunk, cnt, le, lh);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;   // h is released on return
+    *ne = (int)te;
+    *nh = (int)th;
+    return hipSuccess;
+}
+
+template <typename R>
+hipError_t implicit_build_lists(Mat<R> M, Geo geo, int iters, const ImpWork<R>& wk, int* cnt, int* le, int* lh, int* ne,
+                                int* nh, int* xc, hipStream_t s)
 {
     IGeo g{geo.nx, geo.ny, geo.nz, geo.sz, geo.sp, geo.np};
     // With few active items the march of one item is the pass's time: then
     // shorter chunks, as many as leave a CU for each.  104 x 89 x 758 taper FP32, 12
     // steps with samples: 7.97 ms with the chunks of the full tiling; 461 us per step
-    // with these.  Grids of a few hundred thousand entries stay bound by that march.
+    // with these.
     ChebTiles T = cheb_tiles(g, kOwn<R>, kStages<R>);
     hipError_t e;
     std::vector<int> a[2];
+    int64_t rows = 0;   // free e_z edges
     for (int turn = 0; turn < 2; ++turn) {
         const int64_t items = (int64_t)T.nyt * T.nzt * T.nxc;
         if (2 * items > geo.np) return hipErrorInvalidValue;   // an item covers far more than two entries
@@ -608,6 +835,8 @@ hipError_t implicit_build_lists(Mat<R> M, Geo geo, int* le, int* lh, int* ne, in
         std::vector<int> h(2 * (size_t)items);
         if ((e = hipMemcpyAsync(h.data(), le, sizeof(int) * h.size(), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
         if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
+        rows = 0;
+        for (int64_t t = 0; t < items; ++t) rows += h[2 * t];
         for (int b = 0; b < 2; ++b) {
             a[b].clear();
             for (int64_t t = 0; t < items; ++t)
@@ -618,6 +847,11 @@ hipError_t implicit_build_lists(Mat<R> M, Geo geo, int* le, int* lh, int* ne, in
         const ChebTiles S = cheb_tiles(g, kOwn<R>, kStages<R>, std::max(1, (int)(T.xc * na / kRound)));
         if (2 * (int64_t)S.nyt * S.nzt * S.nxc > geo.np) break;
         T = S;
+    }
+    // the h_z system has about as many rows as e_z
+    if (!implicit_passes(sizeof(R), iters, kStages<R>, 2 * rows, (int64_t)a[0].size(), (int64_t)a[1].size(), T.xc)) {
+        *xc = 0;
+        return build_row_lists<R>(M, g, wk, cnt, le, lh, ne, nh, s);
     }
     *xc = T.xc;
     int* const out[2] = {le, lh};
@@ -656,8 +890,10 @@ hipError_t launch_step_implicit(Fields<R> o, Fields<R> w, Mat<R> M, Geo geo, dou
     return hipGetLastError();
 }
 
-template hipError_t implicit_build_lists<float>(Mat<float>, Geo, int*, int*, int*, int*, int*, hipStream_t);
-template hipError_t implicit_build_lists<double>(Mat<double>, Geo, int*, int*, int*, int*, int*, hipStream_t);
+template hipError_t implicit_build_lists<float>(Mat<float>, Geo, int, const ImpWork<float>&, int*, int*, int*, int*, int*,
+                                                int*, hipStream_t);
+template hipError_t implicit_build_lists<double>(Mat<double>, Geo, int, const ImpWork<double>&, int*, int*, int*, int*, int*,
+                                                int*, hipStream_t);
 template hipError_t launch_step_implicit<float>(Fields<float>, Fields<float>, Mat<float>, Geo, double, double, float,
                                                 Src, ImpWork<float>, hipStream_t, hipEvent_t*);
 template hipError_t launch_step_implicit<double>(Fields<double>, Fields<double>, Mat<double>, Geo, double, double,

@@ -1,0 +1,32 @@
+"""The host-side launch choices of csrc/tete_plan.h, compiled by the host compiler
+alone and called through ctypes."""
+import ctypes as C
+import functools
+import os
+import subprocess
+import tempfile
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_0901_1053_amd", "csrc")
+
+SHIM = r'''
+#include "tete_plan.h"
+using namespace tete;
+extern "C" {
+int implicit(int real_bytes, int iters, int stages, int64_t rows, int64_t ie, int64_t ih, int xc)
+{
+    return implicit_passes(real_bytes, iters, stages, rows, ie, ih, xc);
+}
+}
+'''
+
+
+@functools.lru_cache(maxsize=None)
+def lib():
+    d = tempfile.mkdtemp(prefix="tete_plan_")
+    src, so = os.path.join(d, "shim.cpp"), os.path.join(d, "shim.so")
+    with open(src, "w") as f:
+        f.write(SHIM)
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, "-o", so, src])
+    L = C.CDLL(so)
+    L.implicit.argtypes = [C.c_int] * 3 + [C.c_int64] * 3 + [C.c_int]
+    return L
