@@ -184,8 +184,8 @@ struct Stage {
 // fit is kept in vector lanes at an instruction per use: so the stores take no
 // resources, the masks are bit operations on a history of three bits per row,
 // and the march of chunks without the ring or a wake line has no test for them.
-// Per step on 1000 x 18183, m = 1: FP32 121 us with two steps per launch, 60
-// with four; FP64 211, 101; 333 x 4001, m = 0, FP64 19.1, 11.0.
+// Per step on 1000 x 18183, m = 1: FP32 121 us with two steps per launch, 56
+// with four; FP64 211, 99; 333 x 4001, m = 0, FP64 19.1, 9.9.
 template <typename R, int PF, int NS>
 __global__ __launch_bounds__(kLanes * kWaves) void k_rz(RZArgs<R> A)
 {
@@ -672,6 +672,7 @@ struct tete_rz {
     int32_t kend;        // open-pipe run: the wake quadrature ends before edge kend (0: all edges)
     int kernel, chunk_rows, prefetch;   // TETE_KERNEL_AUTO / FUSED (one step) / FUSED2 (two)
     int order;                          // workgroup order (0: default)
+    int auto_rows;                      // rows per chunk of four-step launches where the tuning gives none
     int timing;
     hipEvent_t* ev;
     unsigned char* ev_nst;              // steps of each timed launch
@@ -736,33 +737,12 @@ int rz_nzt(const tete_rz_desc* d, int ns)
     return (d->nz + 1 + own - 1) / own;
 }
 
-// Rows per r-chunk.  One and two steps per launch are bound by HBM and take 16
-// (measured within 3 % of the best of 16 .. 256 on the 1000 x 18183 grid).  Four
-// steps are bound by issue: a wave marches its rows and 16 halo rows, each SIMD
-// holds `held` waves (the registers of the instance), which share its issue,
-// and below two waves a SIMD waits instead.  Taken are the rows with the
-// smallest sum over the rounds; they spend few halo rows and leave no round
-// nearly empty (1000 x 18183: 84 rows fill one round in FP32, 60 us per step
-// against 67 with 64 rows; 333 x 4001 FP64: 12 rows, 10.5 us against 14.7 with 32).
+// Rows per r-chunk: the tuning's, else 16 for one and two steps per launch, which
+// HBM bounds (within 3 % of the best of 16 .. 256 on the 1000 x 18183 grid), and for
+// four the rows chosen for the grid when it was made (rz_chunk_rows).
 int rz_rows(const tete_rz* g, int ns)
 {
-    if (g->chunk_rows > 0) return g->chunk_rows;
-    if (ns < 4) return 16;
-    const int nr1 = g->d.nr + 1, held = g->fp32 ? 4 : 2, simds = 1024;
-    const int64_t strips = rz_nzt(&g->d, ns);
-    int best = 16;
-    int64_t best_cost = 0;
-    for (int chunks = 1; chunks <= std::max(1, nr1 / 8); ++chunks) {
-        const int rows = std::max(8, (nr1 + chunks - 1) / chunks);
-        const int64_t waves = strips * ((nr1 + rows - 1) / rows), slots = (int64_t)simds * held;
-        const int64_t rem = waves % slots;
-        const int64_t cost = (rows + 4 * ns) * (waves / slots * held + (rem ? std::max<int64_t>(2, (rem + simds - 1) / simds) : 0));
-        if (best_cost == 0 || cost < best_cost) {
-            best = rows;
-            best_cost = cost;
-        }
-    }
-    return best;
+    return g->chunk_rows > 0 ? g->chunk_rows : ns < 4 ? 16 : g->auto_rows;
 }
 
 template <typename R, int NS>
@@ -880,6 +860,7 @@ tete_status tete_rz_create(const tete_rz_desc* d, void* dev_ws, size_t ws_bytes,
     g->ws = (char*)dev_ws;
     g->L = L;
     g->fp32 = d->precision == TETE_FP32;
+    g->auto_rows = rz_chunk_rows(d->nr + 1, (rz_nzt(d, 4) + kWaves - 1) / kWaves, g->fp32 != 0);
     if (hipGetDevice(&g->device) != hipSuccess) { free(g); return TETE_ERR_DEVICE; }
     for (int s = 0; s < 2; ++s)
         for (int c = 0; c < 6; ++c) g->f[s][c] = g->ws + L.field[6 * s + c];

@@ -16,6 +16,7 @@ int implicit(int real_bytes, int iters, int stages, int64_t rows, int64_t ie, in
 {
     return implicit_passes(real_bytes, iters, stages, rows, ie, ih, xc);
 }
+int rz_rows(int nr1, int64_t nzb, int fp32) { return rz_chunk_rows(nr1, nzb, fp32 != 0); }
 }
 '''
 
@@ -29,4 +30,5 @@ def lib():
     subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, "-o", so, src])
     L = C.CDLL(so)
     L.implicit.argtypes = [C.c_int] * 3 + [C.c_int64] * 3 + [C.c_int]
+    L.rz_rows.argtypes = [C.c_int, C.c_int64, C.c_int]
     return L
