@@ -35,8 +35,8 @@ inline bool implicit_passes(int real_bytes, int iters, int stages, int64_t rows,
 }
 
 // Rows per r-chunk of the r-z kernel taking four steps per launch, on nr1 rows and
-// nzb workgroups (of four z-strips) along z.  A wave marches its rows and 16 halo
-// rows.  With n workgroups a CU a row takes, us: FP32 1.1, 1.2, 1.2, 1.5, 1.9, 2.1
+// nzt z-strips, a wave each.  A wave marches its rows and 16 halo
+// rows.  With n waves a SIMD a row takes, us: FP32 1.1, 1.2, 1.2, 1.5, 1.9, 2.1
 // for n = 1 .. 6 (500 x 9000), as much as three for less and in proportion for more;
 // FP64, whose registers hold two, 1.45, 2.1, 3.5, 4.1, rounds of two.  Fewer than 12
 // rows spend most of the march on the halo, and the chunk after the first then holds
@@ -44,14 +44,14 @@ inline bool implicit_passes(int real_bytes, int iters, int stages, int64_t rows,
 // others: 1000 x 18183 FP32 112 rows 56.3, 84 60.1, 167 64.5, 28 61.1, FP64 167 99.1,
 // 84 101; 500 x 9000 FP32 28 rows 13.6, 42 17.5; 700 x 14000 FP32 59 rows 32.1, 88
 // 36.1; 1000 x 4000 FP32 24 rows 12.6, 36 13.0; 333 x 4001 FP64 12 rows 9.9, 32 15.0;
-// 300 x 300 FP32 12 rows 6.3, 9 8.1.
-inline int rz_chunk_rows(int nr1, int64_t nzb, bool fp32)
+// 300 x 300 FP32 12 rows 6.3, 9 7.8; 100000 x 40 FP32 33 rows 20.7, 131 37.3.
+inline int rz_chunk_rows(int nr1, int64_t nzt, bool fp32)
 {
     int best = 12;
     int64_t best_cost = 0;
     for (int64_t chunks = 1; chunks <= (nr1 + 11) / 12;) {
         const int rows = std::max(12, (int)((nr1 + chunks - 1) / chunks));
-        const int64_t n = (nzb * ((nr1 + rows - 1) / rows) + kRound - 1) / kRound;
+        const int64_t n = (nzt * ((nr1 + rows - 1) / rows) + 4 * kRound - 1) / (4 * kRound);
         const int64_t cost = (rows + 16) * (fp32 ? std::max<int64_t>(3, n) : (n + 1) / 2 * 2);
         if (best_cost == 0 || cost < best_cost) {
             best = rows;

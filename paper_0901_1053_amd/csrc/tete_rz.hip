@@ -860,7 +860,7 @@ tete_status tete_rz_create(const tete_rz_desc* d, void* dev_ws, size_t ws_bytes,
     g->ws = (char*)dev_ws;
     g->L = L;
     g->fp32 = d->precision == TETE_FP32;
-    g->auto_rows = rz_chunk_rows(d->nr + 1, (rz_nzt(d, 4) + kWaves - 1) / kWaves, g->fp32 != 0);
+    g->auto_rows = rz_chunk_rows(d->nr + 1, rz_nzt(d, 4), g->fp32 != 0);
     if (hipGetDevice(&g->device) != hipSuccess) { free(g); return TETE_ERR_DEVICE; }
     for (int s = 0; s < 2; ++s)
         for (int c = 0; c < 6; ++c) g->f[s][c] = g->ws + L.field[6 * s + c];

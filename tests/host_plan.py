@@ -16,7 +16,7 @@ int implicit(int real_bytes, int iters, int stages, int64_t rows, int64_t ie, in
 {
     return implicit_passes(real_bytes, iters, stages, rows, ie, ih, xc);
 }
-int rz_rows(int nr1, int64_t nzb, int fp32) { return rz_chunk_rows(nr1, nzb, fp32 != 0); }
+int rz_rows(int nr1, int64_t nzt, int fp32) { return rz_chunk_rows(nr1, nzt, fp32 != 0); }
 }
 '''
 

@@ -43,32 +43,33 @@ def test_implicit_solves_take_the_faster_way(case):
 
 # nr, nz, bytes, rows per chunk measured within a few percent of the best
 RZ = [
-    (1000, 18183, FP32, (84, 112, 126)), (1000, 18183, FP64, (84, 167)), (500, 9000, FP32, (28,)),
+    (1000, 18183, FP32, (84, 112, 126)), (1000, 18183, FP64, (84, 167)), (500, 9000, FP32, (27, 28)),
     (500, 9000, FP64, (42,)), (700, 14000, FP32, (59, 64)), (700, 14000, FP64, (88, 92)), (1000, 4000, FP32, (24, 36)),
     (1000, 4000, FP64, (36,)), (200, 18183, FP64, (34,)), (333, 4001, FP32, (12,)), (333, 4001, FP64, (12,)),
     (300, 300, FP32, (12,)), (300, 300, FP64, (12,)), (60, 700, FP32, (12, 13)), (5000, 100, FP64, (12,)),
+    (100000, 40, FP32, (33,)), (100000, 40, FP64, (49,)),
 ]
 
 
 @pytest.mark.parametrize("nr,nz,rb,good", RZ)
 def test_rows_of_the_rz_chunks(nr, nz, rb, good):
     strips = (nz + 1 + 55) // 56
-    assert host_plan.lib().rz_rows(nr + 1, (strips + 3) // 4, rb == FP32) in good
+    assert host_plan.lib().rz_rows(nr + 1, strips, rb == FP32) in good
     assert host_plan.lib().rz_rows(nr + 1, 1, rb == FP32) >= 12
 
 
 def test_rows_of_the_rz_chunks_from_all_counts():
     """The counts of chunks passed over have the rows of one that is tried."""
-    def every(nr1, nzb, fp32):
+    def every(nr1, nzt, fp32):
         best = None
         for chunks in range(1, (nr1 + 11) // 12 + 1):
             rows = max(12, -(-nr1 // chunks))
-            n = -(-nzb * -(-nr1 // rows) // 256)
+            n = -(-nzt * -(-nr1 // rows) // 1024)
             cost = (rows + 16) * (max(3, n) if fp32 else (n + 1) // 2 * 2)
             if best is None or cost < best[0]:
                 best = (cost, rows)
         return best[1]
     for nr1 in (3, 11, 12, 13, 24, 25, 100, 301, 1001, 1777, 20011):
-        for nzb in (1, 2, 17, 82, 300):
+        for nzt in (1, 2, 17, 82, 325, 1200):
             for fp32 in (False, True):
-                assert host_plan.lib().rz_rows(nr1, nzb, fp32) == every(nr1, nzb, fp32), (nr1, nzb, fp32)
+                assert host_plan.lib().rz_rows(nr1, nzt, fp32) == every(nr1, nzt, fp32), (nr1, nzt, fp32)
