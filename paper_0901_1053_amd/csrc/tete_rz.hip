@@ -35,7 +35,6 @@ constexpr int kWaves = 4;                    // waves (z-strips) per workgroup
 constexpr int kSteps = 4;                    // most steps per launch
 constexpr int kPad = 2 * kSteps + 4;         // coefficient rows below 0 and above nr
 constexpr int kRedBlocks = 2048, kRedThreads = 256;
-constexpr int kEnRows = 16;                  // rows a workgroup of the energy sum marches
 
 // Node code bits: e edge PEC or absent; HK = no h_phi / h_r at this k (k = nz).
 enum { C_EPHI = 1, C_ER = 2, C_EZ = 4, C_HK = 8, C_ALL = 15 };
@@ -419,23 +418,27 @@ __device__ double block_sum(double v)
 //   - a^2/2 [sum_{h_phi} mu_phi (P_r e_z)^2 + sum_{e_phi, kappa>0} kappa_phi (P_r^T h_z)^2]
 //   + a [sum_{h_phi} h_phi P_z e_r - sum_{h_r} h_r P_z e_phi]
 //
-// A work item is kRedThreads consecutive k over kEnRows rows, marched along r:
+// A wave's work item is kLanes consecutive k over `rows` rows, marched along r:
 // e_z of the next row is loaded ahead and h_z of the row before kept, the
 // coefficients and their reciprocals of a row are scalar loads, and no index is
-// divided per entry.  HBM bounds it (1000 x 18183, FP32: 294 -> 121 us
-// against a grid-stride sum with divisions, 3.8 TB/s).
+// divided per entry.  HBM bounds it on large grids (1000 x 18183, FP32: 294 -> 121 us
+// against a grid-stride sum with divisions, 3.8 TB/s), the march of one item on
+// small ones, which is why that is as short as the grid allows (rz_energy_rows).
 template <typename R>
 __global__ __launch_bounds__(kRedThreads) void k_rz_energy(Six<const R> f, const uint8_t* code, const Raw* rawp,
-                                                         int nr, int nz, int nzb, int items, double a, double* partial)
+                                                         int nr, int nz, int nzt, int items, int rows, double a,
+                                                         double* partial)
 {
     typedef const __attribute__((address_space(4))) Raw* CRaw;
     const CRaw raw = (CRaw)(const void*)rawp;
     const R *ep = f.c[0], *er = f.c[1], *ez = f.c[2], *hp = f.c[3], *hr = f.c[4], *hz = f.c[5];
     const int sz = nz + 1;
     double acc = 0.0;
-    for (int it = blockIdx.x; it < items; it += gridDim.x) {
-        const int k = it % nzb * kRedThreads + (int)threadIdx.x;
-        const int ja = it / nzb * kEnRows, jb = min(ja + kEnRows, nr + 1);
+    constexpr int NW = kRedThreads / kLanes;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+    for (int64_t it = blockIdx.x * (int64_t)NW + wave; it < items; it += gridDim.x * (int64_t)NW) {
+        const int k = (int)(it % nzt) * kLanes + (int)threadIdx.x % kLanes;
+        const int ja = (int)(it / nzt) * rows, jb = min(ja + rows, nr + 1);
         if (k > nz) continue;
         const int kn = k < nz ? 1 : 0;                    // the k-neighbour, or the entry itself
         int64_t idx = (int64_t)ja * sz + k;
@@ -1110,13 +1113,14 @@ tete_status tete_rz_energy(tete_rz* g, double* W, int64_t* n)
     Guard dg(g->device);
     if (!dg.ok) return TETE_ERR_DEVICE;
     const double a = 0.5 * g->d.cdt;
-    const int nzb = (g->d.nz + kRedThreads) / kRedThreads, items = nzb * ((g->d.nr + kEnRows) / kEnRows);
-    const int grid = std::min(items, (int)kRedBlocks);
+    const int nzt = (g->d.nz + kLanes) / kLanes, rows = rz_energy_rows(g->d.nr + 1, nzt);
+    const int items = nzt * ((g->d.nr + rows) / rows), nw = kRedThreads / kLanes;
+    const int grid = std::min((items + nw - 1) / nw, (int)kRedBlocks);
     auto run = [&](auto tag) {
         typedef decltype(tag) R;
         Six<const R> f;
         for (int c = 0; c < 6; ++c) f.c[c] = (const R*)g->f[g->cur][c];
-        k_rz_energy<R><<<grid, kRedThreads, 0, g->stream>>>(f, g->code, g->raw, g->d.nr, g->d.nz, nzb, items, a,
+        k_rz_energy<R><<<grid, kRedThreads, 0, g->stream>>>(f, g->code, g->raw, g->d.nr, g->d.nz, nzt, items, rows, a,
                                                             g->partial);
     };
     if (g->fp32) run(float(0));

@@ -17,6 +17,7 @@ int implicit(int real_bytes, int iters, int stages, int64_t rows, int64_t ie, in
     return implicit_passes(real_bytes, iters, stages, rows, ie, ih, xc);
 }
 int rz_rows(int nr1, int64_t nzt, int fp32) { return rz_chunk_rows(nr1, nzt, fp32 != 0); }
+int rz_energy(int nr1, int64_t nzt) { return rz_energy_rows(nr1, nzt); }
 }
 '''
 
@@ -31,4 +32,5 @@ def lib():
     L = C.CDLL(so)
     L.implicit.argtypes = [C.c_int] * 3 + [C.c_int64] * 3 + [C.c_int]
     L.rz_rows.argtypes = [C.c_int, C.c_int64, C.c_int]
+    L.rz_energy.argtypes = [C.c_int, C.c_int64]
     return L

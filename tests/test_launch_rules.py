@@ -73,3 +73,14 @@ def test_rows_of_the_rz_chunks_from_all_counts():
         for nzt in (1, 2, 17, 82, 325, 1200):
             for fp32 in (False, True):
                 assert host_plan.lib().rz_rows(nr1, nzt, fp32) == every(nr1, nzt, fp32), (nr1, nzt, fp32)
+
+
+def test_rows_of_the_rz_energy():
+    """No march longer than needed to give each of 8192 waves an item."""
+    f = host_plan.lib().rz_energy
+    assert f(25, 5) == f(301, 5) == f(61, 11) == 1
+    assert f(1001, 285) == 16 and f(100001, 1) == 12
+    for nr1 in (3, 100, 5000, 10 ** 6):
+        for nzt in (1, 7, 300):
+            rows = f(nr1, nzt)
+            assert 1 <= rows <= 16 and (rows == 1 or nzt * -(-nr1 // rows) >= 8192)
