@@ -11,6 +11,58 @@ namespace {
 
 constexpr int kRound = 256;   // workgroups running at a time: one per CU
 
+// X-chunks of a launch whose workgroups fill a CU each.  A workgroup's time is
+// the planes of its chunk and `fill` more (the pipeline's lead-in and drain),
+// in steps of `unroll` planes.  The launch takes as many rounds of kRound
+// workgroups; the items of a last, partly filled round are cut along x so that
+// they fill it (the tail).  Chosen is the count of chunks with the smallest
+// time; a quarter of the work over all CUs is added, which decides between
+// equal times for the fewer chunks.  Measured with chunks as few as fill half
+// the CUs against this rule, us per step (two-step kernel): 24 x 24 x 48
+// FP64 24.9, 10.6; 64 x 64 x 256 FP32 20.4, 16.4; 192 x 192 x 1024 FP32 371, 295;
+// 192 x 192 x 768 FP32 by class 363, 249; 97 x 131 x 801 FP64 179, 163; with the
+// rounds above 512 x 512 x 2048 FP32 4144, 3723.
+struct ChunkPlan {
+    int xchunk, nxc, nfull, nblk, tsplit, tchunk;
+};
+inline ChunkPlan plan_chunks(int64_t tiles, int nplanes, int64_t xmax, int fill, int unroll, bool tail)
+{
+    auto planes = [&](int xc) { return (double)((xc + fill + unroll - 1) / unroll * unroll); };
+    ChunkPlan best = {};
+    double best_cost = 0.0;
+    for (int xc = (int)std::min<int64_t>(nplanes, xmax); xc >= 1;) {
+        const int nxc = (nplanes + xc - 1) / xc;
+        xc = (nplanes + nxc - 1) / nxc;                 // equal chunks, as many
+        const int64_t items = tiles * nxc;
+        // beyond 32 rounds more chunks only add lead-in planes
+        if (best.nblk > 0 && items > 32 * (int64_t)kRound) break;
+        if (items > 0x3fffffff) break;
+        const int rem = (int)(items % kRound);
+        ChunkPlan p = {xc, nxc, (int)items, (int)items, 1, xc};
+        double rounds = (double)((items + kRound - 1) / kRound) * planes(xc);
+        if (tail && rem > 0 && items > kRound) {
+            const double base = (double)(items / kRound) * planes(xc);
+            for (int s = 2; s * rem <= kRound && s <= xc; ++s) {
+                const int tc = (xc + s - 1) / s;
+                if (base + planes(tc) < rounds) {
+                    rounds = base + planes(tc);
+                    p.nfull = (int)(items - rem);
+                    p.tsplit = (xc + tc - 1) / tc;
+                    p.tchunk = tc;
+                    p.nblk = p.nfull + rem * p.tsplit;
+                }
+            }
+        }
+        const double cost = rounds + 0.25 * (double)items * planes(xc) / kRound;
+        if (best.nblk == 0 || cost < best_cost) {
+            best = p;
+            best_cost = cost;
+        }
+        --xc;                                           // the next count of chunks that makes them shorter
+    }
+    return best;
+}
+
 // Whether a plane solve of the implicit scheme takes several Chebyshev iterations
 // per pass over memory (k_cheb_pass, `stages` of them, items_e and items_h work
 // items of xc planes) or one per launch over lists of rows (k_cheb_iter, `rows` of

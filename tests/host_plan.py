@@ -18,6 +18,12 @@ int implicit(int real_bytes, int iters, int stages, int64_t rows, int64_t ie, in
 }
 int rz_rows(int nr1, int64_t nzt, int fp32) { return rz_chunk_rows(nr1, nzt, fp32 != 0); }
 int rz_energy(int nr1, int64_t nzt) { return rz_energy_rows(nr1, nzt); }
+void plan(int64_t tiles, int nplanes, int64_t xmax, int fill, int unroll, int tail, int* out)
+{
+    const ChunkPlan p = plan_chunks(tiles, nplanes, xmax, fill, unroll, tail != 0);
+    const int v[6] = {p.xchunk, p.nxc, p.nfull, p.nblk, p.tsplit, p.tchunk};
+    for (int q = 0; q < 6; ++q) out[q] = v[q];
+}
 }
 '''
 
@@ -33,4 +39,12 @@ def lib():
     L.implicit.argtypes = [C.c_int] * 3 + [C.c_int64] * 3 + [C.c_int]
     L.rz_rows.argtypes = [C.c_int, C.c_int64, C.c_int]
     L.rz_energy.argtypes = [C.c_int, C.c_int64]
+    L.plan.argtypes = [C.c_int64, C.c_int, C.c_int64, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]
     return L
+
+
+def plan(tiles, nplanes, xmax, fill, unroll, tail):
+    """(xchunk, nxc, nfull, nblk, tsplit, tchunk)"""
+    out = (C.c_int * 6)()
+    lib().plan(tiles, nplanes, xmax, fill, unroll, tail, out)
+    return tuple(out)

@@ -1,5 +1,7 @@
 """Rules that choose a launch from sizes, on the CPU: each against the side that was
 measured to be the faster one."""
+import time
+
 import pytest
 
 from tests import host_plan
@@ -84,3 +86,52 @@ def test_rows_of_the_rz_energy():
         for nzt in (1, 7, 300):
             rows = f(nr1, nzt)
             assert 1 <= rows <= 16 and (rows == 1 or nzt * -(-nr1 // rows) >= 8192)
+
+
+def _every_plan(tiles, nplanes, xmax, fill, unroll, tail):
+    """The plan of the chunks from every count of them in turn."""
+    planes = lambda xc: float(-(-(xc + fill) // unroll) * unroll)
+    best = None
+    for nxc in range(-(-nplanes // xmax), nplanes + 1):
+        xc = -(-nplanes // nxc)
+        if -(-nplanes // xc) != nxc:
+            continue
+        items = tiles * nxc
+        if (best and items > 32 * 256) or items > 0x3fffffff:
+            break
+        rem = items % 256
+        p = (xc, nxc, items, items, 1, xc)
+        rounds = -(-items // 256) * planes(xc)
+        if tail and rem and items > 256:
+            base = items // 256 * planes(xc)
+            for s in range(2, min(256 // rem, xc) + 1):
+                tc = -(-xc // s)
+                if base + planes(tc) < rounds:
+                    rounds = base + planes(tc)
+                    split = -(-xc // tc)
+                    p = (xc, nxc, items - rem, items - rem + rem * split, split, tc)
+        cost = rounds + 0.25 * items * planes(xc) / 256
+        if best is None or cost < best[0]:
+            best = (cost, p)
+    return best[1]
+
+
+def test_chunk_plans_from_all_counts():
+    for tiles in (1, 2, 6, 35, 117, 257, 468, 1820):
+        for nplanes in (2, 3, 25, 97, 129, 513, 1001, 1777):
+            for xmax in (1, 5, 31, 64, 1 << 20):
+                for fill, unroll, tail in ((10, 1, 1), (2, 3, 0)):
+                    a = (tiles, nplanes, xmax, fill, unroll, tail)
+                    assert host_plan.plan(*a) == _every_plan(*a), a
+
+
+def test_chunk_plans_cost_no_launch():
+    """A plan is made for every launch: on a long thin grid it may not try every
+    count of chunks (77 us on one tile of 16001 planes)."""
+    best = 1.0
+    for _ in range(30):
+        t = time.perf_counter()
+        for _ in range(10):
+            host_plan.plan(1, 16001, 1 << 20, 10, 1, 1)
+        best = min(best, (time.perf_counter() - t) / 10)
+    assert best < 40e-6, best
