@@ -95,7 +95,7 @@ enum {
                                  * TETE_KERNEL_SPLIT and batches take all); with tuning
                                  * x-chunk 0 two-step launches take the chunk length
                                  * whose active tiles run in the fewest planes, single
-                                 * steps chunks of 32 planes.
+                                 * steps chunks of at most 32 planes.
                                  * The tile list is built, and the stream synchronised,
                                  * at the first such launch after the codes or the
                                  * tiling (rows, x-chunk, order; witness set or not)

@@ -294,15 +294,6 @@ int fused2_rows(const tete_grid* g)
     return r == 16 || ((r == 24 || r == 32) && g->fp32) ? r : 0;
 }
 
-// X-chunk of the fused single step: the tuning's, else for grids that skip
-// static tiles chunks of 32 planes (short chunks find more tiles wholly in
-// the metal, at seven halo planes per chunk), else the library's choice (0).
-// The two-step kernel's own choice counts the active tiles.
-int fused_xchunk(const tete_grid* g)
-{
-    return g->tune.xchunk != 0 ? g->tune.xchunk : g->skip ? 32 : 0;
-}
-
 // FP32 per-entry arrays: the two-step kernel's arrays instance, without
 // witness lines or a static-tile list.
 bool arrays_fused2(const tete_grid* g) { return g->fp32 && !g->skip; }
@@ -331,7 +322,7 @@ tete_status static_table(tete_grid* g, bool wit, bool single)
     int rows, xc, order = g->tune.order;
     if (single) {   // the fused single step's tiling; kappa marks the PEC edges of materials
         rows = g->mat_set || g->tune.rows == 24 || g->tune.rows == 32 ? 0 : g->tune.rows;
-        xc = fused_xchunk(g);
+        xc = g->tune.xchunk;
     } else {        // the instance that keeps witness lines has the default rows only
         rows = wit ? 0 : fused2_rows(g);
         xc = g->tune.xchunk;
@@ -459,7 +450,7 @@ tete_status do_steps(tete_grid* g, int64_t nsteps)
             }
             HIPCHK(launch_step_fused<R>(fields<R>(g, g->cur), fields<R>(g, 1 - g->cur), M, g->geo, (R)g->alpha,
                                         source(g, g->n), g->tune.rows == 24 || g->tune.rows == 32 ? 0 : g->tune.rows,
-                                        fused_xchunk(g), g->tune.depth, g->tune.order, g->stream, ev, act, g->skip_nact[1]));
+                                        g->tune.xchunk, g->tune.depth, g->tune.order, g->stream, ev, act, g->skip_nact[1]));
         }
         else
             HIPCHK(launch_step<R>(fields<R>(g, g->cur), fields<R>(g, 1 - g->cur), M, g->geo, (R)g->alpha,

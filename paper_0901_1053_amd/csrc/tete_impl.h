@@ -167,9 +167,10 @@ hipError_t fused_static_tiles(const R* const kap[3], const uint8_t* code, Geo g,
 template <typename R>
 FArgs<R> fused_args(Fields<R> oldf, Fields<R> newf, Mat<R> mat, Geo g, R alpha, Src src);
 // Fills the tiling of A for a launch shape; false if the shape is invalid or
-// the grid's planes are too large for the fused kernel.
+// the grid's planes are too large for the fused kernel.  longest: planes per chunk
+// at most where xchunk is 0 (0: no such limit).
 template <typename R>
-bool fused_setup(FArgs<R>& A, int rows, int xchunk, int order, bool member = false, bool mat = false);
+bool fused_setup(FArgs<R>& A, int rows, int xchunk, int order, bool member = false, bool mat = false, int longest = 0);
 int fused_default_rows(int real_bytes);
 // Two steps in one launch (tete_fused2.hip): the fused step temporally
 // blocked; xchunk and order as for the single step.
