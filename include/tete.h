@@ -451,10 +451,12 @@ tete_status tete_charges(tete_grid* g, double* max_res_e, double* max_abs_h);
  * FP32, of 32 lanes for FP64, the default) or 32 (FP32: 32 rows of 32
  * lanes); 32 leaves the single step at its default.  xchunk: x-planes
  * per workgroup of either fused kernel (0: chosen from the grid size so that the
- * workgroups fill whole rounds of 256, one per CU; at most 48 or 24 in the
- * two-step launches of a batch).
+ * workgroups fill whole rounds of 256, one per CU; in a batch, from the sizes of
+ * all members, at most 48 or 24 where a launch takes several rounds, and in the
+ * two-step launches of such a batch an xchunk asked for is cut to that).
  * depth: x-planes of old data the fused single step prefetches ahead, 1..3
- * (0: 2; FP64 takes 2 for 3; the two-step kernel prefetches one).  order: order in which the
+ * (0: 2; FP64 takes 2 for 3, while tete_get_tuning returns the 3 that was set;
+ * the two-step kernel prefetches one).  order: order in which the
  * fused kernels' tiles are scheduled: 1 (j-tiles first), 2 (k-tiles first),
  * 3, 4, 5 or 6 (blocks of 8 k-tiles by 4 j-tiles, 16 by 2, 4 by 8 or 2 by
  * 16); 0: 2.  tete_set_materials

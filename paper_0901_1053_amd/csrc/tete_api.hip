@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "tete_impl.h"
+#include "tete_plan.h"
 
 using namespace tete;
 
@@ -1323,31 +1324,44 @@ size_t batch_table_bytes() { return up(sizeof(BatchTable<R>)); }
 // the items of many grids share the persistent workgroups).
 int batch_order(const tete_grid* g) { return g->tune.order != 0 ? g->tune.order : 2; }
 
-// Planes per chunk of a batch's two-step items, at most: `tiles` of all members
-// over `grid` persistent workgroups.  The workgroups drift apart along x as a
-// launch goes on, and neighbouring tiles far apart read their halo rows from
-// memory again; short chunks keep them together.  ms for 16 steps with chunks of up
-// to 1000, 64, 48, 32, 24 planes: 64 members of 64 x 64 x 256 to 192 x 192 x 1024
-// (25 rounds of tiles) 152, 141, 119, 116, 109; 8 of them 14.2, 13.6, 13.3, 13.7,
-// 13.9; chunks chosen per member alone 145 and 13.6.  A longer chunk that a
-// member's tuning asks for (timed in a smaller batch, say) is cut to that.
+// Planes per chunk in several rounds of a batch's two-step items, at most: `tiles` of
+// all members over `grid` persistent workgroups (plan_batch).  ms for 16 steps with
+// chunks of up to 1000, 64, 48, 32, 24 planes: 64 members of 64 x 64 x 256 to 192 x
+// 192 x 1024 (25 rounds of tiles) 152, 141, 119, 116, 109; 8 of them 14.2, 13.6,
+// 13.3, 13.7, 13.9.  A longer chunk that a member's tuning asks for (timed alone or
+// in a smaller batch, say) is cut to that.
 int batch_chunk(int64_t tiles, int grid) { return tiles > 8 * (int64_t)grid ? 24 : 48; }
+// The same of its single steps; us per step with chunks of at most 16, 24, 32, 48, 200
+// planes: 48 members of 64 to 128 cells across FP32 2988, 2950, 3063, 3348, 3548, FP64
+// 4954, 4870, 5493, 5474, 6573; 8 of 64 to 160 FP64 1026, 1037, 1114, 1096, 1191.
+constexpr int kBatchChunk1 = 24;
 
-// Two-step arguments of one member for both parities, chunks of at most cmax planes.
+// Tiling of a batch's launches of one kind: the chunks planned for all members.
 template <typename R>
-bool batch_two_args(tete_grid* g, BatchItem<R>& it, int phase, int cmax, int& total2)
+bool batch_plan(const tete_batch* b, bool two, BatchPlan* plan, int* cap)
 {
-    FArgs<R> f2 = fused_args<R>(fields<R>(g, g->cur), fields<R>(g, 1 - g->cur), mats<R>(g), g->geo, (R)g->alpha,
-                                source(g, g->n));
-    FArgs<R> b2 = fused_args<R>(fields<R>(g, 1 - g->cur), fields<R>(g, g->cur), mats<R>(g), g->geo, (R)g->alpha,
-                                source(g, g->n));
-    const int xc = g->tune.kernel == TETE_KERNEL_FUSED2 ? std::min(g->tune.xchunk, cmax) : 0;
-    if (!fused2_setup<R>(f2, 0, xc, batch_order(g), 0, cmax) || !fused2_setup<R>(b2, 0, xc, batch_order(g), 0, cmax))
-        return false;
-    it.a2[phase] = f2;
-    it.a2[1 - phase] = b2;
-    total2 += f2.nblk;
+    int64_t tiles[TETE_MAX_BATCH], sum = 0;
+    int planes[TETE_MAX_BATCH], n = 0;
+    for (int s = 0; s < TETE_MAX_BATCH; ++s) {
+        const tete_grid* g = b->slot[s];
+        if (!g) continue;
+        FArgs<R> A = {};
+        A.g = g->geo;
+        if (two ? !fused2_setup<R>(A, 0, 1, batch_order(g)) : !fused_setup<R>(A, b->rows, 1, batch_order(g))) return false;
+        planes[n] = g->geo.nx + 1;
+        tiles[n] = A.nblk / A.nxc;      // chunks of one plane: nxc planes
+        sum += tiles[n++];
+    }
+    *cap = two ? batch_chunk(sum, b->grid) : kBatchChunk1;
+    *plan = plan_batch(tiles, planes, n, b->grid, *cap, two ? kFused2Fill : kFusedFill);
     return true;
+}
+
+// Planes per chunk of a member over np planes: equal chunks of at most c.
+int batch_equal(int np, int c)
+{
+    const int n = (np + c - 1) / c;
+    return (np + n - 1) / n;
 }
 
 template <typename R>
@@ -1365,16 +1379,9 @@ tete_status batch_build(tete_batch* b)
         batch_drop_graph(b);   // the captured block launches the other kernel
         b->two = two;
     }
-    int64_t tiles2 = 0;
-    for (int s = 0; s < TETE_MAX_BATCH && two; ++s) {
-        const tete_grid* g = b->slot[s];
-        if (!g) continue;
-        FArgs<R> A = {};
-        A.g = g->geo;
-        if (!fused2_setup<R>(A, 0, 1, batch_order(g))) return TETE_ERR_ARG;
-        tiles2 += (int64_t)A.nyt * A.nzt;
-    }
-    const int cmax = batch_chunk(tiles2, b->grid);
+    BatchPlan p1 = {1, false}, p2 = {1, false};
+    int cap1 = 1, cap2 = 1;
+    if (!batch_plan<R>(b, false, &p1, &cap1) || (two && !batch_plan<R>(b, true, &p2, &cap2))) return TETE_ERR_ARG;
     int total = 0, total2 = 0;
     for (int s = 0; s < TETE_MAX_BATCH; ++s) {
         tete_grid* g = b->slot[s];
@@ -1384,15 +1391,24 @@ tete_status batch_build(tete_batch* b)
         Src src = source(g, g->n);
         FArgs<R> fwd = fused_args<R>(fields<R>(g, g->cur), fields<R>(g, 1 - g->cur), M, g->geo, (R)g->alpha, src);
         FArgs<R> bwd = fused_args<R>(fields<R>(g, 1 - g->cur), fields<R>(g, g->cur), M, g->geo, (R)g->alpha, src);
-        if (!fused_setup<R>(fwd, b->rows, g->tune.xchunk, batch_order(g), true) ||
-            !fused_setup<R>(bwd, b->rows, g->tune.xchunk, batch_order(g), true))
+        const int np = g->geo.nx + 1, xc = g->tune.xchunk != 0 ? g->tune.xchunk : batch_equal(np, p1.chunk);
+        if (!fused_setup<R>(fwd, b->rows, xc, batch_order(g)) || !fused_setup<R>(bwd, b->rows, xc, batch_order(g)))
             return TETE_ERR_ARG;
         // at the current phase the grid reads its current set
         H->item[i].a[b->phase] = fwd;
         H->item[i].a[1 - b->phase] = bwd;
         H->offset[i] = total;
         H->offset2[i] = total2;
-        if (two && !batch_two_args<R>(g, H->item[i], b->phase, cmax, total2)) return TETE_ERR_ARG;
+        if (two) {
+            FArgs<R> f2 = fwd, b2 = bwd;
+            int xc2 = g->tune.kernel == TETE_KERNEL_FUSED2 ? g->tune.xchunk : 0;
+            xc2 = xc2 == 0 ? batch_equal(np, p2.chunk) : p2.one_round ? xc2 : std::min(xc2, cap2);
+            if (!fused2_setup<R>(f2, 0, xc2, batch_order(g)) || !fused2_setup<R>(b2, 0, xc2, batch_order(g)))
+                return TETE_ERR_ARG;
+            H->item[i].a2[b->phase] = f2;
+            H->item[i].a2[1 - b->phase] = b2;
+            total2 += f2.nblk;
+        }
         H->step[i] = g->n;
         total += fwd.nblk;
         b->seen_n[s] = g->n;

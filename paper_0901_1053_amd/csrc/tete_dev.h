@@ -176,20 +176,12 @@ __device__ __forceinline__ Tile listed_tile(const FArgs<R>& A, int e)
 }
 
 // Fills the tiling of A: the x-chunk asked for (clipped to xmax planes), or
-// where xchunk is 0 the plan above.  A member of a batch shares the rounds with
-// other members' items: as few chunks of at most xmax planes as possible, but at
-// least 128 items,
-// chunks of at least 16 planes, and each within xmax.
+// where xchunk is 0 the plan for a launch of this grid alone (plan_chunks).
 template <typename R>
-inline void set_chunks(FArgs<R>& A, int xchunk, int order, int64_t xmax, int fill, int unroll, bool member)
+inline void set_chunks(FArgs<R>& A, int xchunk, int order, int64_t xmax, int fill, int unroll)
 {
     A.order = order != 0 ? order : 2;
     const int nplanes = A.g.nx + 1, tiles = launch_tiles(A.order, A.nyt, A.nzt, 1);
-    if (xchunk <= 0 && member) {
-        int chunks = std::min((128 + tiles - 1) / tiles, std::max(1, nplanes / 16));
-        chunks = (int)std::max<int64_t>(chunks, (nplanes + xmax - 1) / xmax);
-        xchunk = (nplanes + chunks - 1) / chunks;
-    }
     if (xchunk <= 0) {
         const ChunkPlan p = plan_chunks(tiles, nplanes, xmax, fill, unroll, !blocked_order(A.order));
         A.xchunk = p.xchunk;

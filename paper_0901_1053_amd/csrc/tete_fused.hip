@@ -396,7 +396,7 @@ inline int mat_rows(int real_bytes) { return real_bytes == 8 ? 24 : 16; }
 inline int mat_lanes(int real_bytes) { return real_bytes == 8 ? 32 : 64; }
 
 template <typename R>
-bool fused_setup(FArgs<R>& A, int rows, int xchunk, int order, bool member, bool mat, int longest)
+bool fused_setup(FArgs<R>& A, int rows, int xchunk, int order, bool mat, int longest)
 {
     if (rows == 0) rows = fused_default_rows(sizeof(R));
     if (mat) rows = mat_rows(sizeof(R));
@@ -409,7 +409,7 @@ bool fused_setup(FArgs<R>& A, int rows, int xchunk, int order, bool member, bool
     int64_t xmax = ((int64_t(1) << 31) - 1) / plane_bytes - 4;
     if (xmax < 1) return false;
     if (xchunk == 0 && longest > 0) xmax = std::min<int64_t>(xmax, longest);
-    set_chunks(A, xchunk, order, xmax, 6, 1, member);   // planes xs-2 .. xe+3
+    set_chunks(A, xchunk, order, xmax, kFusedFill, 1);
     return true;
 }
 
@@ -482,7 +482,7 @@ hipError_t fused_static_tiles(const R* const kap[3], const uint8_t* code, Geo g,
     FArgs<R> A = fused_args<R>(Fields<R>{}, Fields<R>{}, Mat<R>{}, g, R(0), Src{});
     if (kap) rows = mat_rows(sizeof(R));   // the materials instance: its one shape
     else if (rows == 0) rows = fused_default_rows(sizeof(R));
-    if (!fused_setup<R>(A, rows, xchunk, order, false, kap != nullptr, kListChunk)) return hipErrorInvalidValue;
+    if (!fused_setup<R>(A, rows, xchunk, order, kap != nullptr, kListChunk)) return hipErrorInvalidValue;
     const int64_t nt = (int64_t)A.nyt * A.nzt * A.nxc;
     if (nt > cap || nt > 0x7fffffff) return hipErrorInvalidValue;
     if (!kap && !code) return hipErrorInvalidValue;
@@ -522,7 +522,7 @@ hipError_t launch_step_fused(Fields<R> o, Fields<R> nf, Mat<R> M, Geo g, R alpha
     FArgs<R> A = fused_args<R>(o, nf, M, g, alpha, src);
     const bool mat = M.arr[0] != nullptr;   // per-entry materials: one shape, one plane prefetched
     if (rows == 0) rows = fused_default_rows(sizeof(R));
-    if (!fused_setup<R>(A, rows, xchunk, order, false, mat, act ? kListChunk : 0)) return hipErrorInvalidValue;
+    if (!fused_setup<R>(A, rows, xchunk, order, mat, act ? kListChunk : 0)) return hipErrorInvalidValue;
     hipError_t e;
     if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return e;
     if (mat) {
@@ -553,7 +553,7 @@ hipError_t launch_step_fused(Fields<R> o, Fields<R> nf, Mat<R> M, Geo g, R alpha
 }
 
 #define TETE_FUSED_INST(R)                                                                                     \
-    template bool fused_setup<R>(FArgs<R>&, int, int, int, bool, bool, int);                                            \
+    template bool fused_setup<R>(FArgs<R>&, int, int, int, bool, int);                                            \
     template FArgs<R> fused_args<R>(Fields<R>, Fields<R>, Mat<R>, Geo, R, Src);                                 \
     template hipError_t launch_batch_step<R>(BatchTable<R>*, int, int, int, int, int, hipStream_t);            \
     template hipError_t launch_batch_advance<R>(BatchTable<R>*, int, int, hipStream_t);

@@ -792,7 +792,7 @@ hipError_t launch_batch_step2(BatchTable<R>* T, int grid, int flips, int steps, 
 }
 
 template <typename R>
-bool fused2_setup(FArgs<R>& A, int rows, int xchunk, int order, int lanes, int member)
+bool fused2_setup(FArgs<R>& A, int rows, int xchunk, int order, int lanes)
 {
     if (rows == 0) rows = Default2<R>::rows;
     if (rows != 16 && !((rows == 24 || rows == 32) && sizeof(R) == 4)) return false;
@@ -805,9 +805,7 @@ bool fused2_setup(FArgs<R>& A, int rows, int xchunk, int order, int lanes, int m
     const int64_t plane_bytes = (int64_t)A.g.sp * sizeof(R);
     const int64_t xmax = ((int64_t(1) << 31) - 1) / plane_bytes - 8;
     if (xmax < 1) return false;
-    // planes xs-4 .. xe+7, of which the first and the last few are cheaper
-    if (member > 0 && xchunk == 0) set_chunks(A, 0, order, std::min<int64_t>(xmax, member), 10, 1, true);
-    else set_chunks(A, xchunk, order, xmax, 10, 1, false);
+    set_chunks(A, xchunk, order, xmax, kFused2Fill, 1);
     return true;
 }
 
@@ -1058,7 +1056,7 @@ hipError_t launch_step_fused2(Fields<R> o, Fields<R> nf, Mat<R> M, Geo g, R alph
 
 #define TETE_FUSED2_INST(R)                                                                                    \
     template hipError_t launch_batch_step2<R>(BatchTable<R>*, int, int, int, hipStream_t);                     \
-    template bool fused2_setup<R>(FArgs<R>&, int, int, int, int, int);                                            \
+    template bool fused2_setup<R>(FArgs<R>&, int, int, int, int);                                            \
     template hipError_t launch_step_fused2<R>(Fields<R>, Fields<R>, Mat<R>, Geo, R, Src, const WitMid<R>*, int, \
                                               int, int, int, hipStream_t, hipEvent_t*, const int*, int,      \
                                               const EnergyPair*);                                            \

@@ -170,15 +170,14 @@ FArgs<R> fused_args(Fields<R> oldf, Fields<R> newf, Mat<R> mat, Geo g, R alpha, 
 // the grid's planes are too large for the fused kernel.  longest: planes per chunk
 // at most where xchunk is 0 (0: no such limit).
 template <typename R>
-bool fused_setup(FArgs<R>& A, int rows, int xchunk, int order, bool member = false, bool mat = false, int longest = 0);
+bool fused_setup(FArgs<R>& A, int rows, int xchunk, int order, bool mat = false, int longest = 0);
 int fused_default_rows(int real_bytes);
 // Two steps in one launch (tete_fused2.hip): the fused step temporally
 // blocked; xchunk and order as for the single step.
 bool fused2_fits(Geo g, int real_bytes);
 // rows: 0 (default), 16, or 24 or 32 (FP32 only: rows of 32 lanes).
-// member: planes per chunk at most as a member of a batch (0: no member).
 template <typename R>
-bool fused2_setup(FArgs<R>& A, int rows, int xchunk, int order, int lanes = 0, int member = 0);
+bool fused2_setup(FArgs<R>& A, int rows, int xchunk, int order, int lanes = 0);
 // Energy samples taken by a two-step launch: want bit 0 the energy of its
 // input y^n, bit 1 that of y^{n+1}; written to out[0], out[1] (only the ones
 // wanted, in that order); part: cap pairs of FP64 partial sums.

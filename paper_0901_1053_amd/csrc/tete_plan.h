@@ -10,6 +10,10 @@ namespace tete {
 namespace {
 
 constexpr int kRound = 256;   // workgroups running at a time: one per CU
+// lead-in and drain of a chunk, in planes: the single step's (planes xs-2 .. xe+3)
+// and the two-step kernel's (xs-4 .. xe+7, of which the first and the last few are
+// cheaper)
+constexpr int kFusedFill = 6, kFused2Fill = 10;
 
 // X-chunks of a launch whose workgroups fill a CU each.  A workgroup's time is
 // the planes of its chunk and `fill` more (the pipeline's lead-in and drain),
@@ -59,6 +63,51 @@ inline ChunkPlan plan_chunks(int64_t tiles, int nplanes, int64_t xmax, int fill,
             best_cost = cost;
         }
         --xc;                                           // the next count of chunks that makes them shorter
+    }
+    return best;
+}
+
+// Chunks of a batch's launch: planes per chunk of every member, at most, where `grid`
+// persistent workgroups take the items of n members of tiles[i] tiles over
+// planes[i] planes; `fill` as above.  Chosen is the count of rounds whose items are
+// the shortest in all.  In several rounds the workgroups drift apart along x, and
+// neighbouring tiles far apart read their halo rows from memory again: chunks are
+// then at most `cap` planes.
+struct BatchPlan {
+    int chunk;
+    bool one_round;
+};
+inline BatchPlan plan_batch(const int64_t* tiles, const int* planes, int n, int grid, int cap, int fill)
+{
+    int longest = 1;
+    for (int i = 0; i < n; ++i) longest = std::max(longest, planes[i]);
+    auto items = [&](int c) {
+        int64_t v = 0;
+        for (int i = 0; i < n; ++i) v += tiles[i] * ((planes[i] + c - 1) / c);
+        return v;
+    };
+    // shortest chunk of at most `most` planes with at most k rounds of items, or 0
+    auto shortest = [&](int64_t k, int most) {
+        if (items(most) > k * grid) return 0;
+        int lo = 1, hi = most;
+        while (lo < hi) {
+            const int mid = (lo + hi) / 2;
+            if (items(mid) <= k * grid) hi = mid;
+            else lo = mid + 1;
+        }
+        return lo;
+    };
+    const int c1 = shortest(1, longest);
+    BatchPlan best = {c1, c1 > 0};
+    int64_t best_cost = c1 + fill;
+    cap = std::min(cap, longest);
+    const int64_t k0 = std::max<int64_t>(2, (items(cap) + grid - 1) / grid);
+    for (int64_t k = k0; k < k0 + 4; ++k) {
+        const int c = shortest(k, cap);
+        if (c > 0 && (best.chunk == 0 || k * (c + fill) < best_cost)) {
+            best = {c, false};
+            best_cost = k * (c + fill);
+        }
     }
     return best;
 }

@@ -349,7 +349,7 @@ bool yee_setup(FArgs<R>& A, int xchunk, int order)
     const int64_t plane_bytes = (int64_t)A.g.sp * sizeof(R);
     const int64_t xmax = ((int64_t(1) << 31) - 1) / plane_bytes - 2;
     if (xmax < 1) return false;
-    set_chunks(A, xchunk, order, xmax, 2, 3, false);
+    set_chunks(A, xchunk, order, xmax, 2, 3);
     return true;
 }
 
@@ -384,7 +384,7 @@ bool yee2_setup(FArgs<R>& A, int xchunk, int order)
     const int64_t plane_bytes = (int64_t)A.g.sp * sizeof(R);
     const int64_t xmax = ((int64_t(1) << 31) - 1) / plane_bytes - 3;
     if (xmax < 1) return false;
-    set_chunks(A, xchunk, order, xmax, 4, 3, false);
+    set_chunks(A, xchunk, order, xmax, 4, 3);
     return true;
 }
 

@@ -24,6 +24,12 @@ void plan(int64_t tiles, int nplanes, int64_t xmax, int fill, int unroll, int ta
     const int v[6] = {p.xchunk, p.nxc, p.nfull, p.nblk, p.tsplit, p.tchunk};
     for (int q = 0; q < 6; ++q) out[q] = v[q];
 }
+int batch(const int64_t* tiles, const int* planes, int n, int grid, int cap, int fill, int* one)
+{
+    const BatchPlan p = plan_batch(tiles, planes, n, grid, cap, fill);
+    *one = p.one_round;
+    return p.chunk;
+}
 }
 '''
 
@@ -40,7 +46,16 @@ def lib():
     L.rz_rows.argtypes = [C.c_int, C.c_int64, C.c_int]
     L.rz_energy.argtypes = [C.c_int, C.c_int64]
     L.plan.argtypes = [C.c_int64, C.c_int, C.c_int64, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]
+    L.batch.argtypes = [C.POINTER(C.c_int64), C.POINTER(C.c_int), C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]
     return L
+
+
+def batch(members, grid, cap, fill):
+    """(planes per chunk, one round) for members (tiles, planes)"""
+    n, one = len(members), C.c_int()
+    c = lib().batch((C.c_int64 * n)(*[m[0] for m in members]), (C.c_int * n)(*[m[1] for m in members]), n, grid, cap,
+                    fill, C.byref(one))
+    return c, bool(one.value)
 
 
 def plan(tiles, nplanes, xmax, fill, unroll, tail):

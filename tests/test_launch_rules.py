@@ -1,5 +1,6 @@
 """Rules that choose a launch from sizes, on the CPU: each against the side that was
 measured to be the faster one."""
+import random
 import time
 
 import pytest
@@ -135,3 +136,32 @@ def test_chunk_plans_cost_no_launch():
             host_plan.plan(1, 16001, 1 << 20, 10, 1, 1)
         best = min(best, (time.perf_counter() - t) / 10)
     assert best < 40e-6, best
+
+
+def test_batch_chunks():
+    # one member that fits a round in two chunks is not cut to 48 planes
+    assert host_plan.batch([(117, 129)], 256, 48, 10) == (65, True)
+    # few tiles: chunks short enough to give every workgroup an item
+    c, one = host_plan.batch([(4, 30), (5, 41), (3, 26)], 256, 48, 10)
+    assert one and c <= 3
+    # many rounds: the longest chunks allowed, or nearly
+    c, one = host_plan.batch([(100, 129)] * 64, 256, 24, 10)
+    assert not one and 20 <= c <= 24
+    # single steps of a member longer than a chunk's limit
+    c, one = host_plan.batch([(81, 161)] * 8, 256, 24, 6)
+    assert not one and c <= 24
+
+
+def test_batch_chunks_are_the_shortest_in_all():
+    rng = random.Random(5)
+    for _ in range(200):
+        n, grid, cap, fill = rng.randint(1, 12), rng.choice((32, 256)), rng.choice((24, 48)), rng.choice((6, 10))
+        m = [(rng.choice((1, 4, 20, 117, 300)), rng.randint(2, 200)) for _ in range(n)]
+        c, one = host_plan.batch(m, grid, cap, fill)
+        items = lambda c: sum(t * -(-p // c) for t, p in m)
+        rounds = lambda c: max(1, -(-items(c) // grid))
+        assert 1 <= c <= max(p for _, p in m) and one == (items(c) <= grid) and (one or c <= cap), (m, c)
+        # no other chunk of as many rounds, or of up to three more, takes less
+        allowed = [q for q in range(1, max(p for _, p in m) + 1) if q <= cap or items(q) <= grid]
+        near = [q for q in allowed if rounds(q) <= rounds(min(max(allowed), cap)) + 3 or rounds(q) == 1]
+        assert rounds(c) * (c + fill) <= min(rounds(q) * (q + fill) for q in near), (m, c)
