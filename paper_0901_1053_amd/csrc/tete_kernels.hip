@@ -155,7 +155,8 @@ template <typename R, bool MAT>
 struct KeepXYZ {
     Mat<R> M;
     Geo g;
-    __device__ __forceinline__ void operator()(int64_t e, uint32_t (&m)[4]) const
+    template <int N>
+    __device__ __forceinline__ void operator()(int64_t e, uint32_t (&m)[N]) const
     {
         int i, j, k;
         decomp((int)e, g, i, j, k);
@@ -163,18 +164,18 @@ struct KeepXYZ {
         if constexpr (MAT) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                R v[4] = {};
-                if (e + 4 <= g.np) load4<true>(M.arr[c], e, v);
+                R v[N] = {};
+                if (e + N <= g.np) load_n<true, N>(M.arr[c], e, v);
                 else
                     for (int u = 0; e + u < g.np; ++u) v[u] = M.arr[c][e + u];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) cw |= v[u] != R(0) ? 0u : 1u << (8 * u + c);
+                for (int u = 0; u < N; ++u) cw |= v[u] != R(0) ? 0u : 1u << (8 * u + c);
             }
         } else {
-            cw = *(const uint32_t*)(M.code + e);
+            cw = load_codes<N>(M.code, e);
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < N; ++u) {
             uint32_t b = ~(cw >> (8 * u)) & 7u;
             if (j < g.ny && k < g.nz) b |= 8u;
             if (i < g.nx && k < g.nz) b |= 16u;

@@ -380,13 +380,14 @@ __global__ void k_rz_sanitize(R* const* f, const uint8_t* code, const Raw* raw, 
 struct KeepRZ {
     const uint8_t* code;
     int nr, nz, axis_ez;
-    __device__ __forceinline__ void operator()(int64_t e, uint32_t (&m)[4]) const
+    template <int N>
+    __device__ __forceinline__ void operator()(int64_t e, uint32_t (&m)[N]) const
     {
         const uint32_t sz = (uint32_t)nz + 1u;
         int j = (int)((uint32_t)e / sz), k = (int)((uint32_t)e - (uint32_t)j * sz);
-        const uint32_t cw = *(const uint32_t*)(code + e);
+        const uint32_t cw = load_codes<N>(code, e);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < N; ++u) {
             uint32_t b = ~(cw >> (8 * u)) & 7u;
             if (j == 0) b &= axis_ez ? 6u : 2u;
             if (j < nr && k < nz) b |= 8u;
