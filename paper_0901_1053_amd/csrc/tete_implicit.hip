@@ -781,7 +781,8 @@ int implicit_iters(const Geo& g, double dx, double dy, double alpha, int fp32, d
 int implicit_list_chunks(int64_t np) { return (int)((np + kListChunk - 1) / kListChunk); }
 
 // Lists of rows for one iteration per launch: free e_z edges and coupled h_z rows.
-// The directions of all other rows have to be zero, whatever the solves before left.
+// The directions of all other rows have to be zero: they are in a new workspace and
+// after every solve over lists, not after passes (wk.xc > 0).
 template <typename R>
 hipError_t build_row_lists(const Mat<R>& M, const IGeo& g, const ImpWork<R>& wk, int* cnt, int* le, int* lh, int* ne,
                            int* nh, hipStream_t s)
@@ -789,7 +790,7 @@ hipError_t build_row_lists(const Mat<R>& M, const IGeo& g, const ImpWork<R>& wk,
     const ICoef<R> c{M.k[0], M.k[1], M.k[2], M.m[0], M.m[1], M.m[2], (R)0, (R)0};
     const int nch = implicit_list_chunks(g.np);
     hipError_t e;
-    for (int q = 0; q < 2; ++q)
+    for (int q = 0; q < 2 && wk.xc > 0; ++q)
         if ((e = launch_zero_bytes(wk.d[q], sizeof(R) * (size_t)g.np, s)) != hipSuccess) return e;
     k_list_count<R><<<nch, TBI, 0, s>>>(M.code, g, c, kListChunk, cnt);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -825,6 +826,14 @@ hipError_t implicit_build_lists(Mat<R> M, Geo geo, int iters, const ImpWork<R>& 
     // with these.
     ChebTiles T = cheb_tiles(g, kOwn<R>, kStages<R>);
     hipError_t e;
+    auto by_rows = [&] {
+        const hipError_t r = build_row_lists<R>(M, g, wk, cnt, le, lh, ne, nh, s);
+        if (r == hipSuccess) *xc = 0;
+        return r;
+    };
+    // not even passes of a single plane would do for every row there can be: no need
+    // to look for items
+    if (!implicit_passes(sizeof(R), iters, kStages<R>, 2 * (int64_t)geo.np, 1, 1, 1)) return by_rows();
     std::vector<int> a[2];
     int64_t rows = 0;   // free e_z edges
     for (int turn = 0; turn < 2; ++turn) {
@@ -849,10 +858,8 @@ hipError_t implicit_build_lists(Mat<R> M, Geo geo, int iters, const ImpWork<R>& 
         T = S;
     }
     // the h_z system has about as many rows as e_z
-    if (!implicit_passes(sizeof(R), iters, kStages<R>, 2 * rows, (int64_t)a[0].size(), (int64_t)a[1].size(), T.xc)) {
-        *xc = 0;
-        return build_row_lists<R>(M, g, wk, cnt, le, lh, ne, nh, s);
-    }
+    if (!implicit_passes(sizeof(R), iters, kStages<R>, 2 * rows, (int64_t)a[0].size(), (int64_t)a[1].size(), T.xc))
+        return by_rows();
     *xc = T.xc;
     int* const out[2] = {le, lh};
     for (int b = 0; b < 2; ++b)
