@@ -323,8 +323,9 @@ __global__ void k_cheb_iter(R* X, R* Rr, R* D, R* Dn, const int* list, int n, co
 constexpr int kChebWaves = 8;
 constexpr int kMaxStages = 5;
 // Stages per pass and rows per thread: the state of a stage is four values per
-// row, and a workgroup of 16 waves has 128 registers a thread; the exchange
-// planes of five stages would fill the LDS in FP64.
+// row, and a workgroup of eight waves has 256 registers a thread.  FP64 with four
+// rows spills 2 to 14 of them in the passes between the first and the last and in
+// the last at four stages, 51 to 66 at five; with six rows 149 to 180 at four.
 template <typename R> constexpr int kStages = sizeof(R) == 4 ? 5 : 4;
 template <typename R> constexpr int kRJ = sizeof(R) == 4 ? 6 : 4;
 template <typename R> constexpr int kOwn = kRJ<R> * kChebWaves - 2 * kStages<R>;   // rows a tile owns
