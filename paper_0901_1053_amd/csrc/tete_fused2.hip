@@ -821,11 +821,6 @@ int64_t fused2_tile_cap(Geo g)
     return (int64_t)(g.nx + 1) * ((g.ny + 1 + 9) / 10) * ((g.nz + 1 + 27) / 28);
 }
 
-// Chunk length of the active tiles where the tuning gives none: the launch runs
-// them in rounds of kRound, each as long as a chunk and ten planes; equal chunks,
-// as many as make that shortest (a quarter of the work over all CUs added, as in
-// plan_chunks).  Chunks of 32 planes whatever the grid took 72.6 us per launch on
-// the 96 x 96 x 512 open pipe FP32, this rule 64.2.
 template <typename R>
 hipError_t fused2_static_tiles(const uint8_t* code, Geo g, int rows, int xchunk, int order, uint8_t* tab, int* act,
                                int64_t cap, int64_t* ntiles, int* nact, int* used, hipStream_t s)
@@ -848,28 +843,10 @@ hipError_t fused2_static_tiles(const uint8_t* code, Geo g, int rows, int xchunk,
     // next[q tiles + t]: the first plane from q on that is not static in tile t
     std::vector<int> next((size_t)n + tiles, planes);
     for (int64_t i = n; i-- > 0;) next[(size_t)i] = h[(size_t)i] ? (int)(i / tiles) : next[(size_t)(i + tiles)];
-    auto active = [&](int t, int cx, int xc) {
-        const int xs = cx * xc, xe = std::min(xs + xc, planes);
-        return next[(size_t)std::max(0, xs - 4) * tiles + t] <= std::min(xe + 3, g.nx);
-    };
+    const ActiveTiles act_of = {next.data(), tiles, planes};
     if (xchunk == 0) {
         const int64_t plane_bytes = (int64_t)g.sp * sizeof(R);
-        const int xmax = (int)std::min<int64_t>(planes, ((int64_t(1) << 31) - 1) / plane_bytes - 8);
-        double best = 0.0;
-        for (int c = (planes + xmax - 1) / xmax; c <= planes; ++c) {
-            const int xc = (planes + c - 1) / c;
-            if ((planes + xc - 1) / xc != c) continue;
-            int64_t items = 0;
-            for (int cx = 0; cx < c; ++cx)
-                for (int t = 0; t < tiles; ++t) items += active(t, cx, xc);
-            const double cost =
-                ((double)((items + kRound - 1) / kRound) + 0.25 * (double)items / kRound) * (double)(xc + 10);
-            if (best == 0.0 || cost < best) {
-                best = cost;
-                xchunk = xc;
-            }
-            if (items > 8 * (int64_t)kRound) break;   // more chunks only add lead-in planes
-        }
+        xchunk = active_chunk(act_of, (int)std::min<int64_t>(planes, ((int64_t(1) << 31) - 1) / plane_bytes - 8));
         if (!fused2_setup<R>(A, rows, xchunk, order)) return hipErrorInvalidValue;
     }
     // the active tiles in the order the full launch takes them
@@ -880,7 +857,7 @@ hipError_t fused2_static_tiles(const uint8_t* code, Geo g, int rows, int xchunk,
         int ty, tz, cx;
         if (!tile_of(lb, A.order, A.nyt, A.nzt, ty, tz, cx)) continue;
         const int t = ty * A.nzt + tz;
-        if (active(t, cx, A.xchunk)) list.push_back(cx * tiles + t);
+        if (act_of(t, cx, A.xchunk)) list.push_back(cx * tiles + t);
     }
     if (!list.empty()) {
         if ((e = hipMemcpyAsync(act, list.data(), sizeof(int) * list.size(), hipMemcpyHostToDevice, s)) !=

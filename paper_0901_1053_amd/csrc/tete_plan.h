@@ -67,6 +67,55 @@ inline ChunkPlan plan_chunks(int64_t tiles, int nplanes, int64_t xmax, int fill,
     return best;
 }
 
+// Tiles of the two-step kernel that are not static over a chunk: next[q tiles + t] is
+// the first plane from q on that is not static in tile t (planes where there is
+// none; a row past the last plane holds that too).  A chunk xs .. xe-1 loads planes
+// xs-4 .. xe+3.
+struct ActiveTiles {
+    const int* next;
+    int tiles, planes;
+    bool operator()(int t, int cx, int xc) const
+    {
+        const int xs = cx * xc, xe = std::min(xs + xc, planes);
+        return next[(int64_t)std::max(0, xs - 4) * tiles + t] <= std::min(xe + 3, planes - 1);
+    }
+    int64_t count(int xc) const
+    {
+        int64_t v = 0;
+        for (int cx = 0; cx * xc < planes; ++cx)
+            for (int t = 0; t < tiles; ++t) v += (*this)(t, cx, xc);
+        return v;
+    }
+};
+
+// Chunk length of the active tiles where the tuning gives none, at most xmax: the
+// launch runs them in rounds of kRound, each as long as a chunk and ten planes; equal
+// chunks, as many as make that shortest (a quarter of the work over all CUs added, as
+// in plan_chunks).  Shorter chunks leave out more metal, so several rounds are no
+// reason to stop before 32 planes; below, the ten planes weigh more.  us per launch
+// with 32 planes whatever the grid and with this rule: 96 x 96 x 512 open pipe FP32
+// 72.6, 64.2; 512 x 512 x 2048 taper FP64 1750, 1637 (129 planes, where a search that
+// stops at eight rounds ends, 2033), FP32 990, 890.
+inline int active_chunk(const ActiveTiles& a, int xmax)
+{
+    int best = 0;
+    double best_cost = 0.0;
+    for (int xc = std::min(a.planes, xmax); xc >= 1; --xc) {
+        const int c = (a.planes + xc - 1) / xc;
+        xc = (a.planes + c - 1) / c;                  // equal chunks, as many
+        const int64_t items = a.count(xc);
+        const double cost =
+            ((double)((items + kRound - 1) / kRound) + 0.25 * (double)items / kRound) * (double)(xc + kFused2Fill);
+        if (best == 0 || cost < best_cost) {
+            best_cost = cost;
+            best = xc;
+        }
+        if (items == 0) break;
+        if (items > 8 * (int64_t)kRound && xc <= 32) break;
+    }
+    return best;
+}
+
 // Chunks of a batch's launch: planes per chunk of every member, at most, where `grid`
 // persistent workgroups take the items of n members of tiles[i] tiles over
 // planes[i] planes; `fill` as above.  Chosen is the count of rounds whose items are

@@ -6,6 +6,8 @@ import os
 import subprocess
 import tempfile
 
+import numpy as np
+
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_0901_1053_amd", "csrc")
 
 SHIM = r'''
@@ -23,6 +25,10 @@ void plan(int64_t tiles, int nplanes, int64_t xmax, int fill, int unroll, int ta
     const ChunkPlan p = plan_chunks(tiles, nplanes, xmax, fill, unroll, tail != 0);
     const int v[6] = {p.xchunk, p.nxc, p.nfull, p.nblk, p.tsplit, p.tchunk};
     for (int q = 0; q < 6; ++q) out[q] = v[q];
+}
+int active(const int* next, int tiles, int planes, int xmax)
+{
+    return active_chunk(ActiveTiles{next, tiles, planes}, xmax);
 }
 int batch(const int64_t* tiles, const int* planes, int n, int grid, int cap, int fill, int* one)
 {
@@ -47,7 +53,17 @@ def lib():
     L.rz_energy.argtypes = [C.c_int, C.c_int64]
     L.plan.argtypes = [C.c_int64, C.c_int, C.c_int64, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]
     L.batch.argtypes = [C.POINTER(C.c_int64), C.POINTER(C.c_int), C.c_int, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int)]
+    L.active.argtypes = [C.c_void_p] + [C.c_int] * 3
     return L
+
+
+def active(on, xmax):
+    """Planes per chunk for on[plane, tile], True where the tile is not static."""
+    planes, tiles = on.shape
+    nxt = np.full((planes + 1, tiles), planes, np.int32)
+    for q in range(planes - 1, -1, -1):
+        nxt[q] = np.where(on[q], q, nxt[q + 1])
+    return lib().active(nxt.ctypes.data, tiles, planes, xmax)
 
 
 def batch(members, grid, cap, fill):

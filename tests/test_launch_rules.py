@@ -3,6 +3,7 @@ measured to be the faster one."""
 import random
 import time
 
+import numpy as np
 import pytest
 
 from tests import host_plan
@@ -165,3 +166,33 @@ def test_batch_chunks_are_the_shortest_in_all():
         allowed = [q for q in range(1, max(p for _, p in m) + 1) if q <= cap or items(q) <= grid]
         near = [q for q in allowed if rounds(q) <= rounds(min(max(allowed), cap)) + 3 or rounds(q) == 1]
         assert rounds(c) * (c + fill) <= min(rounds(q) * (q + fill) for q in near), (m, c)
+
+
+def _active_count(on, xc):
+    planes = on.shape[0]
+    return sum(int(on[max(0, xs - 4):min(xs + xc, planes) + 4].any(axis=0).sum()) for xs in range(0, planes, xc))
+
+
+# tiles on along a pipe with a wide entrance and exit and a narrow middle, over the
+# planes across it: the 512 x 512 x 2048 taper in tiles of 10 rows by 28 and 60
+# entries, a small one, and grids wholly on and off
+@pytest.mark.parametrize("planes,nyt,nzt,wide", [(513, 52, 74, 0.25), (513, 52, 35, 0.25), (97, 10, 9, 0.3), (201, 21, 15, 0.25),
+                                                 (129, 13, 18, 2.0), (129, 13, 18, 0.0), (41, 1, 1, 2.0)])
+def test_chunk_of_the_active_tiles(planes, nyt, nzt, wide):
+    x = (np.arange(planes) + 0.5) / planes - 0.5
+    y = (np.arange(nyt) + 0.5) / nyt - 0.5
+    z = np.abs((np.arange(nzt) + 0.5) / nzt - 0.5)
+    r = np.minimum(0.2 * wide + 1.5 * wide * z, wide)
+    on = (x[:, None, None] ** 2 + y[None, :, None] ** 2 < (r * r)[None, None, :]).reshape(planes, -1)
+    cost = {}
+    for c in range(1, planes + 1):
+        xc = -(-planes // c)
+        if -(-planes // xc) != c or xc in cost or (xc < 24 and c * on.shape[1] > 20000):
+            continue
+        items = _active_count(on, xc)
+        cost[xc] = (-(-items // 256) + 0.25 * items / 256) * (xc + 10)
+    got = host_plan.active(on, 1 << 30)
+    assert got in cost
+    # within 5 % of the least over all chunks of at least 24 planes, or of any that fill a round
+    assert cost[got] <= 1.05 * min(v for k, v in cost.items() if k >= 24 or v < 4 * 40)
+    assert host_plan.active(on, 30) <= 30
