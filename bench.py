@@ -737,7 +737,7 @@ def rz_section(steps=100, warmup=5):
         kms, n, nst = G.timing()
         G.set_timing(0)
         b = 4 if prec == "fp32" else 8
-        per = nst // n                                   # steps per launch (two-step kernel: 2)
+        per = nst // n                                   # steps per launch (4, or 2 and 1 at the end)
         kbytes = (12 * b + 1) * G.np * per               # one cell-update per entry and step
         achieved = kbytes / (kms / n / 1e3) / 1e9
         traffic = measured_traffic("k_rz", case.name, prec)
@@ -747,9 +747,9 @@ def rz_section(steps=100, warmup=5):
                                   "achieved": round(achieved, 1),
                                   "peak": PEAK_HBM_GBPS, "unit": "GB/s",
                                   "frac": round(achieved / PEAK_HBM_GBPS, 4), "bytes_per_launch": kbytes,
-                                  "basis": "algorithmic bytes of %d single steps per launch; the two-step launch "
-                                           "reads and writes the state once, so frac can exceed 1: it is not a "
-                                           "bandwidth fraction, traffic_frac is" % per,
+                                  "basis": "algorithmic bytes of %d single steps per launch; the launch reads and "
+                                           "writes the state once, so frac can exceed 1: it is not a bandwidth "
+                                           "fraction, traffic_frac is" % per,
                                   "ms_per_launch": round(kms / n, 4), "traffic": traffic,
                                   "traffic_gbps": round(traffic / (kms / n / 1e3) / 1e9, 1) if traffic else None,
                                   "traffic_frac": round(traffic / (kms / n / 1e3) / 1e9 / PEAK_HBM_GBPS, 4)

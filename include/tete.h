@@ -495,8 +495,9 @@ tete_status tete_timing(tete_grid* g, double* ms, int32_t nphase, int64_t* steps
 
 /* ------------------------------------------------------------------------
  * Batches: many grids (of one precision, uneven sizes, own geometries and
- * bunches) stepped together, one persistent launch per time step (FP32: per
- * two time steps, with the two-step kernel) covering every member's tiles;
+ * bunches) stepped together, one persistent launch per two time steps (per
+ * time step for an odd last one, or where single steps are asked for or a member
+ * does not fit the two-step kernel) covering every member's tiles;
  * blocks of steps are replayed from a captured HIP graph.  A batch owns a small device table (tete_batch_bytes) in caller
  * memory; membership can change between calls (continuous batching) without
  * re-capturing the graph.  Members use the fused kernel (no per-entry
@@ -537,7 +538,8 @@ tete_status tete_batch_set(tete_batch* b, int32_t slot, tete_grid* g);
  * a block of an odd number of steps ends with a single step.  rows (0, 12 or 16) and prefetch depth (0..3, 0 = 1)
  * of the single-step kernel; steps per captured graph block (0 = no graph).
  * With the two-step kernel a member uses its own tile order and, if its
- * tuning asks for TETE_KERNEL_FUSED2, its own x-chunk. */
+ * tuning asks for TETE_KERNEL_FUSED2, its own x-chunk (cut where a launch
+ * takes several rounds, see tete_set_tuning). */
 tete_status tete_batch_set_launch(tete_batch* b, int32_t kernel, int32_t rows, int32_t depth,
                                   int32_t graph_steps);
 

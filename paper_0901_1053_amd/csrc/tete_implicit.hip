@@ -316,8 +316,9 @@ __global__ void k_cheb_iter(R* X, R* Rr, R* D, R* Dn, const int* list, int n, co
 // Each stage costs one row at each edge of the tile and one plane at each end of
 // the chunk.  x, r and d are read and written once per pass: 24 bytes per row
 // and pass (FP32) instead of 28 per row and iteration over a list of rows.
-// The vector instructions bound it: 21 per row and stage for e_z, 31 for h_z,
-// two waves a SIMD.  160 x 160 x 512 on cubic cells (15 iterations), FP32: a solve
+// 21 vector instructions per row and stage for e_z, 31 for h_z, two waves a SIMD: on
+// the 512 x 512 x 2048 taper the vector units are 45 to 67 % busy while the passes move
+// 3.8 to 4.9 TB/s (a copy takes 5.0).  160 x 160 x 512 on cubic cells (15 iterations), FP32: a solve
 // of e_z 1.17 -> 0.35 ms, of h_z 1.43 -> 0.43 ms.  Eight waves of 256 registers
 // hold six rows a thread without spilling, 16 waves of 128 registers three.
 constexpr int kChebWaves = 8;

@@ -177,14 +177,15 @@ struct Stage {
 // the one before and takes its final rows as input, so that a cell is read and
 // written once per NS steps; each step costs two rows of halo on either side of
 // a chunk and one lane on either side of the strip.  HBM bounds one and two
-// steps per launch; with four it is the instructions issued, 244 vector
-// instructions per row and wave in FP32.  Scalar registers are short (the
+// steps per launch; with four the launch is near both limits, 1000 x 18183: FP32
+// 241 vector instructions per row and wave, the vector units 64 % busy, 4.2 TB/s (a
+// copy takes 5.0); FP64 45 %, 4.8 TB/s.  Scalar registers are short (the
 // arrays' resources, six coefficients per stage and row), and what does not
 // fit is kept in vector lanes at an instruction per use: so the stores take no
 // resources, the masks are bit operations on a history of three bits per row,
 // and the march of chunks without the ring or a wake line has no test for them.
-// Per step on 1000 x 18183, m = 1: FP32 121 us with two steps per launch, 56
-// with four; FP64 211, 99; 333 x 4001, m = 0, FP64 19.1, 9.9.
+// Per step on 1000 x 18183, m = 1: FP32 121 us with two steps per launch, 58
+// with four; FP64 211, 100; 333 x 4001, m = 0, FP64 19.1, 9.9.
 template <typename R, int PF, int NS>
 __global__ __launch_bounds__(kLanes * kWaves) void k_rz(RZArgs<R> A)
 {
@@ -674,7 +675,7 @@ struct tete_rz {
     int has_bunch;
     tete_rz_bunch b;
     int32_t kend;        // open-pipe run: the wake quadrature ends before edge kend (0: all edges)
-    int kernel, chunk_rows, prefetch;   // TETE_KERNEL_AUTO / FUSED (one step) / FUSED2 (two)
+    int kernel, chunk_rows, prefetch;   // TETE_KERNEL_AUTO / FUSED (one step) / FUSED2 (four)
     int order;                          // workgroup order (0: default)
     int auto_rows;                      // rows per chunk of four-step launches where the tuning gives none
     int timing;
